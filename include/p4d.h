@@ -297,8 +297,9 @@ p4d_status p4d_param_gradient(p4d_ctx *ctx, const double *d_x, const double *d_l
  * of a V-cycle's coarse correction, which run back to back, share one event
  * pair (an interval of cheb_degree - 1 or cheb_degree launches).
  * P4D_K_COUPLING: the kernels around the V-cycles of the block Gauss-Seidel
- * and Schur-complement preconditioners (right-hand sides with the
- * off-diagonal blocks, precision casts, output).                          */
+ * and Schur-complement preconditioners, and of the particle-Schur one inside
+ * a solve with an FP64 Z basis (right-hand sides with the off-diagonal
+ * blocks, precision casts, output).                          */
 typedef enum {
     P4D_K_OPERATOR = 1, P4D_K_MDOT = 2, P4D_K_ORTH = 3, P4D_K_RADIAL = 4,
     P4D_K_SMOOTH0 = 5, P4D_K_ZY = 6, P4D_K_BATCH_PC = 7, P4D_K_COUPLING = 8,

@@ -124,6 +124,45 @@ __global__ __launch_bounds__(kBlock) void k_bstage_radb(StageRun run)
     }
 }
 
+// the same stages for folded vectors: no particle column is touched, so one
+// list and one kernel serve all radial sizes
+template <typename T>
+__device__ inline void fold_fwd_unit(const PCell &Cm, int k, int transpose, bool first, int unit)
+{
+    const Geom g = Cm.g;
+    const RadArgs R = Cm.R;
+    const double *r = k == 0 ? (first ? Cm.b : Cm.V) : Cm.V + g.N + (long long)(k - 1) * g.Nm;
+    const double rs = Cm.invbeta[k];
+    const double zs = Cm.alpha[k] * rs;
+    if (transpose) rad_fwd_block<T, 1, true, 2>(g, R, r, rs, unit, zs);
+    else rad_fwd_block<T, 1, false, 2>(g, R, r, rs, unit, zs);
+}
+__device__ inline void fold_out_unit(const PCell &Cm, int k, bool first, int unit)
+{
+    const Geom g = Cm.g;
+    const RadArgs R = Cm.R;
+    const double *r = k == 0 ? (first ? Cm.b : Cm.V) : Cm.V + g.N + (long long)(k - 1) * g.Nm;
+    macro_out_block<double>(g, R, r, Cm.invbeta[k], (double *)Cm.Z + (long long)k * g.Nm, unit);
+}
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_bstage_fwd_fold(StageRun run)
+{
+    const UnitRef u = unit_of(run);
+    Ctab<PStage<T>> &S = ctab((const PStage<T> *)run.stages)[u.si];
+    if (!((run.active >> S.cell) & 1ULL)) return;
+    const PCell Cm = ld(ctab(run.cells)[S.cell]);
+    fold_fwd_unit<T>(Cm, run.k, run.transpose, (run.first >> S.cell) & 1ULL, u.unit);
+}
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_bstage_out_fold(StageRun run)
+{
+    const UnitRef u = unit_of(run);
+    Ctab<PStage<T>> &S = ctab((const PStage<T> *)run.stages)[u.si];
+    if (!((run.active >> S.cell) & 1ULL)) return;
+    const PCell Cm = ld(ctab(run.cells)[S.cell]);
+    fold_out_unit(Cm, run.k, (run.first >> S.cell) & 1ULL, u.unit);
+}
+
 // KINDS: the stage kinds in the list (1: smoothing steps only, 2: residuals
 // only, 3: both), so that a list of one kind carries the registers of that
 // kind's tile function only
@@ -187,11 +226,19 @@ void launch_batch_stage(const StageRun &run, int family, int nrmax, int kinds, h
     const dim3 grid(run.nitems), block(kBlock);
     switch (family) {
     case SF_RADF:
+        if (run.fold) {
+            hipLaunchKernelGGL((k_bstage_fwd_fold<T>), grid, block, 0, st, run);
+            break;
+        }
 #define P4D_BF(NR) hipLaunchKernelGGL((k_bstage_radf<T, NR>), grid, block, 0, st, run)
         P4D_NR_SWITCH(nrmax, P4D_BF)
 #undef P4D_BF
         break;
     case SF_RADB:
+        if (run.fold) {
+            hipLaunchKernelGGL((k_bstage_out_fold<T>), grid, block, 0, st, run);
+            break;
+        }
 #define P4D_BB(NR) hipLaunchKernelGGL((k_bstage_radb<T, TZ, NR>), grid, block, 0, st, run)
         P4D_NR_SWITCH(nrmax, P4D_BB)
 #undef P4D_BB
@@ -229,6 +276,10 @@ __device__ inline void persist_unit(const PersistRun &run, Ctab<PStage<T>> &S, i
     const PCell Cm = ld(ctab(run.cells)[S.cell]);
     switch (stage_family(S.kind)) {
     case SF_RADF: {
+        if (run.fold) {
+            fold_fwd_unit<T>(Cm, run.k, run.transpose, (run.first >> S.cell) & 1ULL, unit);
+            break;
+        }
         const Geom g = Cm.g;
         const RadArgs R = Cm.R;
         const double *r = Cm.V + (long long)run.k * g.N;
@@ -242,6 +293,10 @@ __device__ inline void persist_unit(const PersistRun &run, Ctab<PStage<T>> &S, i
         break;
     }
     case SF_RADB: {
+        if (run.fold) {
+            fold_out_unit(Cm, run.k, (run.first >> S.cell) & 1ULL, unit);
+            break;
+        }
         const Geom g = Cm.g;
         const RadArgs R = Cm.R;
         const double *r = Cm.V + (long long)run.k * g.N;
@@ -380,7 +435,7 @@ template int bstage_sm0_slots<float>();
 // kernels.
 // ---------------------------------------------------------------------------
 // the cell of batched workgroup b, by the offsets of one launch kind
-enum { SEL_OP = 0, SEL_ST, SEL_TILE, SEL_RAD };
+enum { SEL_OP = 0, SEL_ST, SEL_TILE, SEL_RAD, SEL_FS };
 template <int SEL>
 __device__ inline int find_cell(const BCell *cells, int ncells, int b)
 {
@@ -389,7 +444,9 @@ __device__ inline int find_cell(const BCell *cells, int ncells, int b)
         const int mid = (lo + hi + 1) >> 1;
         Ctab<BCell> &M = ctab(cells)[mid];
         const int b0 = SEL == SEL_OP ? M.op_blk0
-                                     : (SEL == SEL_ST ? M.st_blk0 : (SEL == SEL_TILE ? M.tile_blk0 : M.rad_blk0));
+                                     : (SEL == SEL_ST ? M.st_blk0
+                                                      : (SEL == SEL_TILE ? M.tile_blk0
+                                                                         : (SEL == SEL_FS ? M.fs_blk0 : M.rad_blk0)));
         if (b0 <= b) lo = mid;
         else hi = mid - 1;
     }
@@ -455,18 +512,91 @@ __global__ __launch_bounds__(kBlock) void k_bop_radial(const BCell *__restrict__
     operator_radial<TX, NRMAX, TRANS>(g, O, C.qbuf, je);
 }
 
+// folded: the electrode-level rows of V_{k+1} = A Z_k
+template <bool TRANS>
+__global__ __launch_bounds__(kBlock) void k_bop_tile_fold(const BCell *__restrict__ cells, int ncells,
+                                                          unsigned long long active, int k)
+{
+    __shared__ OpLds L;
+    const int gb = xcd_block(blockIdx.x, gridDim.x);
+    const int c = find_cell<SEL_TILE>(cells, ncells, gb);
+    const BCell C = ld(ctab(cells)[c]);
+    if (!((active >> c) & 1ULL)) return;
+    const Geom g = C.g;
+    OpArgs O = C.op;
+    O.x = (const double *)C.Z + (long long)k * g.Nm;
+    O.y = C.V + g.N + (long long)k * g.Nm;
+    O.b = nullptr;
+    O.za = ZetaArgs{C.zeta, C.invbeta + k, C.alpha + k};
+    operator_tile<double, TRANS, true>(g, O, nullptr, gb - C.tile_blk0, C.op_tx, C.op_cz, L);
+}
+
+// folded: the first vector of a cycle and its final sums
+template <int NRMAX, bool TRANS>
+__global__ __launch_bounds__(kBlock) void k_bfold_start(const BCell *__restrict__ cells, int ncells,
+                                                        unsigned long long active, unsigned long long first)
+{
+    __shared__ double red[4];
+    const int c = find_cell<SEL_FS>(cells, ncells, blockIdx.x);
+    const BCell C = ld(ctab(cells)[c]);
+    if (!((active >> c) & 1ULL)) return;
+    const Geom g = C.g;
+    const double *r = ((first >> c) & 1ULL) ? C.b : C.V;
+    const int lb = blockIdx.x - C.fs_blk0;
+    double sqy = 0.0, sqs = 0.0;
+    for (long long n = (long long)lb * kBlock + threadIdx.x; n < g.nnode; n += (long long)C.fs_n * kBlock)
+        fold_start_node<NRMAX, TRANS>(g, C.op.tabs, C.op.ss, r, C.zeta, n, sqy, sqs);
+    sqy = block_sum(sqy, red);
+    sqs = block_sum(sqs, red);
+    if (threadIdx.x == 0) {
+        C.red[2 * lb] = sqy;
+        C.red[2 * lb + 1] = sqs;
+    }
+}
+
+// (a restarted cycle's norm is known from its residual: only sig2 and alpha)
+__global__ __launch_bounds__(kBlock) void k_bfold_final(const BCell *__restrict__ cells, unsigned long long active,
+                                                        unsigned long long first)
+{
+    __shared__ double red[4];
+    const int c = blockIdx.x;
+    const BCell C = ld(ctab(cells)[c]);
+    if (!((active >> c) & 1ULL)) return;
+    const bool f = (first >> c) & 1ULL;
+    fold_final_block(C.red, C.fs_n, C.h + (f ? 128 : 200), C.sig2, C.alpha, f ? C.invbeta : nullptr, red);
+}
+
+template <int NRMAX, bool TRANS>
+__global__ __launch_bounds__(kBlock) void k_bred_back(const BCell *__restrict__ cells, int ncells,
+                                                      unsigned long long active, unsigned long long first)
+{
+    const int c = find_cell<SEL_OP>(cells, ncells, blockIdx.x);
+    const BCell C = ld(ctab(cells)[c]);
+    if (!((active >> c) & 1ULL)) return;
+    const Geom g = C.g;
+    const OpArgs &O = C.op;
+    const int lb = blockIdx.x - C.op_blk0;
+    const double gamma = *C.gamma;
+    if ((first >> c) & 1ULL)
+        red_back_block<NRMAX, TRANS, false>(g, O.tabs, O.gg, O.ss, O.ee, O.mm, gamma, C.b, C.x, C.x, lb);
+    else
+        red_back_block<NRMAX, TRANS, true>(g, O.tabs, O.gg, O.ss, O.ee, O.mm, gamma, C.V, C.V + g.N, C.x, lb);
+}
+
 template <int KMAX>
 __global__ __launch_bounds__(kBlock) void k_bmdot(const BCell *__restrict__ cells, int ncells,
-                                                  unsigned long long active, int k)
+                                                  unsigned long long active, unsigned long long first, int k)
 {
     __shared__ double red[4][KMAX];
     const int c = find_cell<SEL_ST>(cells, ncells, blockIdx.x);
     const BCell C = ld(ctab(cells)[c]);
     if (!((active >> c) & 1ULL)) return;
     const int lb = blockIdx.x - C.st_blk0, nb = C.st_nblk;
-    const long long N = C.g.N;
+    const long long N = C.nk;
     const int nv = k + 1;
-    const double *__restrict__ V = C.V;
+    // vector q at V + q N, vector 0 at v0 (folded: vector 0 is whole)
+    const double *__restrict__ V = C.V + (C.g.N - N);
+    const double *__restrict__ v0 = C.fold && ((first >> c) & 1ULL) ? C.b : C.V;
     const double *__restrict__ w = V + (long long)(k + 1) * N;
     double acc[KMAX];
 #pragma unroll
@@ -475,7 +605,7 @@ __global__ __launch_bounds__(kBlock) void k_bmdot(const BCell *__restrict__ cell
         const double wi = w[i];
 #pragma unroll
         for (int q = 0; q < KMAX; q++)
-            if (q < nv) acc[q] += wi * V[(long long)q * N + i];
+            if (q < nv) acc[q] += wi * (q == 0 ? v0 : V + (long long)q * N)[i];
     }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
@@ -493,7 +623,7 @@ __global__ __launch_bounds__(kBlock) void k_bmdot(const BCell *__restrict__ cell
 
 // grid (nv, ncells): h_q = invbeta_q * sum_b partial[q][b], c_q = h_q * invbeta_q
 __global__ __launch_bounds__(kBlock) void k_bmdot_final(const BCell *__restrict__ cells,
-                                                        unsigned long long active, int pass)
+                                                        unsigned long long active, int k, int pass)
 {
     __shared__ double red[4];
     const int q = blockIdx.x, c = blockIdx.y;
@@ -504,6 +634,7 @@ __global__ __launch_bounds__(kBlock) void k_bmdot_final(const BCell *__restrict_
     for (int b = threadIdx.x; b < nb; b += kBlock) s += C.red[(long long)q * nb + b];
     s = block_sum(s, red);
     if (threadIdx.x == 0) {
+        if (C.fold) s += fold_dot(fold_alpha(C.alpha, C.invbeta, k, pass), C.alpha[q], *C.sig2);
         const double hq = s * C.invbeta[q];
         C.h[64 * pass + q] = hq;
         C.coef[q] = hq * C.invbeta[q];
@@ -512,17 +643,23 @@ __global__ __launch_bounds__(kBlock) void k_bmdot_final(const BCell *__restrict_
 
 template <int KMAX>
 __global__ __launch_bounds__(kBlock) void k_borth(const BCell *__restrict__ cells, int ncells,
-                                                  unsigned long long active, int k)
+                                                  unsigned long long active, unsigned long long first, int k,
+                                                  int pass)
 {
     __shared__ double red[4];
     const int c = find_cell<SEL_ST>(cells, ncells, blockIdx.x);
     const BCell C = ld(ctab(cells)[c]);
     if (!((active >> c) & 1ULL)) return;
     const int lb = blockIdx.x - C.st_blk0, nb = C.st_nblk;
-    const long long N = C.g.N;
+    const long long N = C.nk;
     const int nv = k + 1;
-    const double *__restrict__ V = C.V;
-    double *__restrict__ w = C.V + (long long)(k + 1) * N;
+    if (C.fold && lb == 0 && threadIdx.x < 64) {
+        const double a = fold_update(fold_alpha(C.alpha, C.invbeta, k, pass), C.coef, C.alpha, nv);
+        if (threadIdx.x == 0) C.alpha[k + 1] = a;
+    }
+    const double *__restrict__ V = C.V + (C.g.N - N);
+    const double *__restrict__ v0 = C.fold && ((first >> c) & 1ULL) ? C.b : C.V;
+    double *__restrict__ w = C.V + (C.g.N - N) + (long long)(k + 1) * N;
     double cq[KMAX];
 #pragma unroll
     for (int q = 0; q < KMAX; q++) cq[q] = q < nv ? C.coef[q] : 0.0;
@@ -531,7 +668,7 @@ __global__ __launch_bounds__(kBlock) void k_borth(const BCell *__restrict__ cell
         double wi = w[i];
 #pragma unroll
         for (int q = 0; q < KMAX; q++)
-            if (q < nv) wi -= cq[q] * V[(long long)q * N + i];
+            if (q < nv) wi -= cq[q] * (q == 0 ? v0 : V + (long long)q * N)[i];
         w[i] = wi;
         sq += wi * wi;
     }
@@ -554,6 +691,7 @@ __global__ __launch_bounds__(kBlock) void k_bnorm_final(const BCell *__restrict_
     for (int b = threadIdx.x; b < nb; b += kBlock) s += C.red[b];
     s = block_sum(s, red);
     if (threadIdx.x == 0) {
+        if (C.fold && !op) s += fold_dot(C.alpha[slot], C.alpha[slot], *C.sig2);
         const double bt = sqrt(s);
         C.h[128] = bt;
         C.invbeta[slot] = bt > 0.0 ? 1.0 / bt : 0.0;
@@ -562,13 +700,13 @@ __global__ __launch_bounds__(kBlock) void k_bnorm_final(const BCell *__restrict_
 
 template <typename TZ, int KMAX>
 __global__ __launch_bounds__(kBlock) void k_bzy(const BCell *__restrict__ cells, int ncells,
-                                                unsigned long long active)
+                                                unsigned long long active, unsigned long long first)
 {
     const int c = find_cell<SEL_ST>(cells, ncells, blockIdx.x);
     const BCell C = ld(ctab(cells)[c]);
     if (!((active >> c) & 1ULL)) return;
     const int lb = blockIdx.x - C.st_blk0, nb = C.st_nblk;
-    const long long N = C.g.N;
+    const long long N = C.nk;
     const int nv = *C.kused;
     double yq[KMAX];
 #pragma unroll
@@ -576,11 +714,19 @@ __global__ __launch_bounds__(kBlock) void k_bzy(const BCell *__restrict__ cells,
     const TZ *__restrict__ Z = (const TZ *)C.Z;
     double *__restrict__ x = C.x;
     for (long long i = (long long)lb * kBlock + threadIdx.x; i < N; i += (long long)nb * kBlock) {
-        double xi = x[i];
+        // folded: the first update assigns x, a later one is also kept by
+        // itself at V_1 (the particle part follows from it)
+        const bool assign = C.fold && ((first >> c) & 1ULL), keep = C.fold && !assign;
+        double xi = assign ? 0.0 : x[i], di = 0.0;
 #pragma unroll
         for (int q = 0; q < KMAX; q++)
-            if (q < nv) xi += yq[q] * (double)Z[(long long)q * N + i];
+            if (q < nv) {
+                const double zq = (double)Z[(long long)q * N + i];
+                xi += yq[q] * zq;
+                if (keep) di += yq[q] * zq;
+            }
         x[i] = xi;
+        if (keep) C.V[C.g.N + i] = di;
     }
 }
 
@@ -649,27 +795,69 @@ template void launch_bop<double>(const BCell *, int, unsigned long long, int, in
 template void launch_bop<float>(const BCell *, int, unsigned long long, int, int, int, int, int, int,
                                 int, hipStream_t);
 
-void launch_bmdot(const BCell *cells, int ncells, unsigned long long active, int k, int nblk_st,
-                  int pass, hipStream_t st)
+void launch_bop_fold(const BCell *cells, int ncells, unsigned long long active, int k, int transpose,
+                     int nblk_tile, hipStream_t st)
+{
+    if (transpose)
+        hipLaunchKernelGGL((k_bop_tile_fold<true>), dim3(nblk_tile), dim3(kBlock), 0, st, cells, ncells, active, k);
+    else
+        hipLaunchKernelGGL((k_bop_tile_fold<false>), dim3(nblk_tile), dim3(kBlock), 0, st, cells, ncells, active, k);
+}
+
+void launch_bfold_start(const BCell *cells, int ncells, unsigned long long active, unsigned long long first,
+                        int transpose, int nblk, int nrmax, hipStream_t st)
+{
+#define P4D_BFS(NR)                                                                                            \
+    do {                                                                                                       \
+        if (transpose)                                                                                         \
+            hipLaunchKernelGGL((k_bfold_start<NR, true>), dim3(nblk), dim3(kBlock), 0, st, cells, ncells, active, \
+                               first);                                                                         \
+        else                                                                                                   \
+            hipLaunchKernelGGL((k_bfold_start<NR, false>), dim3(nblk), dim3(kBlock), 0, st, cells, ncells, active, \
+                               first);                                                                         \
+    } while (0)
+    P4D_NR_SWITCH(nrmax, P4D_BFS)
+#undef P4D_BFS
+    hipLaunchKernelGGL(k_bfold_final, dim3(ncells), dim3(kBlock), 0, st, cells, active, first);
+}
+
+void launch_bred_back(const BCell *cells, int ncells, unsigned long long active, unsigned long long first,
+                      int transpose, int nblk_op, int nrmax, hipStream_t st)
+{
+#define P4D_BRB(NR)                                                                                            \
+    do {                                                                                                       \
+        if (transpose)                                                                                         \
+            hipLaunchKernelGGL((k_bred_back<NR, true>), dim3(nblk_op), dim3(kBlock), 0, st, cells, ncells, active, \
+                               first);                                                                         \
+        else                                                                                                   \
+            hipLaunchKernelGGL((k_bred_back<NR, false>), dim3(nblk_op), dim3(kBlock), 0, st, cells, ncells, active, \
+                               first);                                                                         \
+    } while (0)
+    P4D_NR_SWITCH(nrmax, P4D_BRB)
+#undef P4D_BRB
+}
+
+void launch_bmdot(const BCell *cells, int ncells, unsigned long long active, unsigned long long first, int k,
+                  int nblk_st, int pass, hipStream_t st)
 {
     const int nv = k + 1;
 #define P4D_BM(K) \
-    hipLaunchKernelGGL((k_bmdot<K>), dim3(nblk_st), dim3(kBlock), 0, st, cells, ncells, active, k)
+    hipLaunchKernelGGL((k_bmdot<K>), dim3(nblk_st), dim3(kBlock), 0, st, cells, ncells, active, first, k)
     if (nv <= 4) P4D_BM(4);
     else if (nv <= 8) P4D_BM(8);
     else if (nv <= 16) P4D_BM(16);
     else if (nv <= 32) P4D_BM(32);
     else P4D_BM(64);
 #undef P4D_BM
-    hipLaunchKernelGGL(k_bmdot_final, dim3(nv, ncells), dim3(kBlock), 0, st, cells, active, pass);
+    hipLaunchKernelGGL(k_bmdot_final, dim3(nv, ncells), dim3(kBlock), 0, st, cells, active, k, pass);
 }
 
-void launch_borth(const BCell *cells, int ncells, unsigned long long active, int k, int nblk_st,
-                  hipStream_t st)
+void launch_borth(const BCell *cells, int ncells, unsigned long long active, unsigned long long first, int k,
+                  int nblk_st, int pass, hipStream_t st)
 {
     const int nv = k + 1;
 #define P4D_BR(K) \
-    hipLaunchKernelGGL((k_borth<K>), dim3(nblk_st), dim3(kBlock), 0, st, cells, ncells, active, k)
+    hipLaunchKernelGGL((k_borth<K>), dim3(nblk_st), dim3(kBlock), 0, st, cells, ncells, active, first, k, pass)
     if (nv <= 4) P4D_BR(4);
     else if (nv <= 8) P4D_BR(8);
     else if (nv <= 16) P4D_BR(16);
@@ -685,11 +873,11 @@ void launch_bnorm_final(const BCell *cells, int ncells, unsigned long long activ
 }
 
 template <typename TZ>
-void launch_bzy(const BCell *cells, int ncells, unsigned long long active, int kmax, int nblk_st,
-                hipStream_t st)
+void launch_bzy(const BCell *cells, int ncells, unsigned long long active, unsigned long long first, int kmax,
+                int nblk_st, hipStream_t st)
 {
 #define P4D_BZ(K) \
-    hipLaunchKernelGGL((k_bzy<TZ, K>), dim3(nblk_st), dim3(kBlock), 0, st, cells, ncells, active)
+    hipLaunchKernelGGL((k_bzy<TZ, K>), dim3(nblk_st), dim3(kBlock), 0, st, cells, ncells, active, first)
     if (kmax <= 4) P4D_BZ(4);
     else if (kmax <= 8) P4D_BZ(8);
     else if (kmax <= 16) P4D_BZ(16);
@@ -697,7 +885,7 @@ void launch_bzy(const BCell *cells, int ncells, unsigned long long active, int k
     else P4D_BZ(64);
 #undef P4D_BZ
 }
-template void launch_bzy<double>(const BCell *, int, unsigned long long, int, int, hipStream_t);
-template void launch_bzy<float>(const BCell *, int, unsigned long long, int, int, hipStream_t);
+template void launch_bzy<double>(const BCell *, int, unsigned long long, unsigned long long, int, int, hipStream_t);
+template void launch_bzy<float>(const BCell *, int, unsigned long long, unsigned long long, int, int, hipStream_t);
 
 }  // namespace p4d

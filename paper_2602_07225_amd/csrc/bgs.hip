@@ -187,19 +187,7 @@ template <typename TZ>
 __global__ __launch_bounds__(kBlock) void k_bgs_out(Geom g, BgsArgs B, const double *__restrict__ r,
                                                     const double *rscale_p, TZ *__restrict__ z)
 {
-    const double rscale = rscale_p ? *rscale_p : 1.0;
-    const long long n = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (n >= g.nnode) return;
-    const RadArgs &R = B.R;
-    z[g.off_pe + n] = (TZ)R.x0[2][g.off_pe + n];
-    z[g.off_ce + n] = (TZ)R.x0[3][g.off_ce + n];
-    const int k = (int)(n / ((long long)g.nx * g.ny));
-    const int el = node_mat(g, k);
-    if (el < 0) return;
-    const long long base = el == 0 ? 0 : g.nea;
-    const long long klo = el == 0 ? 0 : g.na + g.ns;
-    const long long je = base + n - klo * g.nx * g.ny;
-    z[je] = (TZ)(k == 0 ? r[je] * rscale : (el == 0 ? R.x0[0] : R.x0[1])[je]);
+    macro_out_block<TZ>(g, B.R, r, rscale_p ? *rscale_p : 1.0, z, blockIdx.x);
 }
 
 template <typename TZ>

@@ -67,7 +67,7 @@ void launch_mdot(long long n, const double *w, const double *V, const double *v0
 __global__ __launch_bounds__(kBlock) void k_mdot_final(int nv, const double *__restrict__ partial,
                                                        int nblk, const double *__restrict__ invbeta,
                                                        double *__restrict__ h,
-                                                       double *__restrict__ c)
+                                                       double *__restrict__ c, Fold F)
 {
     __shared__ double red[4];
     const int q = blockIdx.x;
@@ -75,6 +75,7 @@ __global__ __launch_bounds__(kBlock) void k_mdot_final(int nv, const double *__r
     for (int b = threadIdx.x; b < nblk; b += kBlock) s += partial[(long long)q * nblk + b];
     s = block_sum(s, red);
     if (threadIdx.x == 0) {
+        if (F.alpha) s += fold_dot(fold_alpha(F.alpha, F.invbeta, F.k, F.pass), F.alpha[q], *F.sig2);
         const double hq = s * invbeta[q];
         h[q] = hq;
         c[q] = hq * invbeta[q];
@@ -82,9 +83,9 @@ __global__ __launch_bounds__(kBlock) void k_mdot_final(int nv, const double *__r
 }
 
 void launch_mdot_final(int nv, const double *partial, int nblk, const double *invbeta, double *h,
-                       double *c, hipStream_t st)
+                       double *c, const Fold &F, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_mdot_final, dim3(nv), dim3(kBlock), 0, st, nv, partial, nblk, invbeta, h, c);
+    hipLaunchKernelGGL(k_mdot_final, dim3(nv), dim3(kBlock), 0, st, nv, partial, nblk, invbeta, h, c, F);
 }
 
 template <int KMAX>
@@ -92,9 +93,14 @@ __global__ __launch_bounds__(kBlock) void k_orth(long long n, double *__restrict
                                                  const double *__restrict__ V,
                                                  const double *__restrict__ v0, long long ldv,
                                                  int nv, const double *__restrict__ c,
-                                                 double *__restrict__ partial)
+                                                 double *__restrict__ partial, Fold F)
 {
     __shared__ double red[4];
+    // the folded rows: alpha_{k+1}, which no other workgroup of this launch reads
+    if (F.alpha && blockIdx.x == 0 && threadIdx.x < 64) {
+        const double a = fold_update(fold_alpha(F.alpha, F.invbeta, F.k, F.pass), c, F.alpha, nv);
+        if (threadIdx.x == 0) F.alpha[F.k + 1] = a;
+    }
     double cq[KMAX];
 #pragma unroll
     for (int q = 0; q < KMAX; q++) cq[q] = q < nv ? c[q] : 0.0;
@@ -113,10 +119,10 @@ __global__ __launch_bounds__(kBlock) void k_orth(long long n, double *__restrict
 }
 
 void launch_orth(long long n, double *w, const double *V, const double *v0, long long ldv, int nv,
-                 const double *c, double *partial, int nblk, hipStream_t st)
+                 const double *c, double *partial, int nblk, const Fold &F, hipStream_t st)
 {
 #define P4D_OR(K) \
-    hipLaunchKernelGGL((k_orth<K>), dim3(nblk), dim3(kBlock), 0, st, n, w, V, v0, ldv, nv, c, partial)
+    hipLaunchKernelGGL((k_orth<K>), dim3(nblk), dim3(kBlock), 0, st, n, w, V, v0, ldv, nv, c, partial, F)
     if (nv <= 4) P4D_OR(4);
     else if (nv <= 8) P4D_OR(8);
     else if (nv <= 16) P4D_OR(16);
@@ -128,23 +134,24 @@ void launch_orth(long long n, double *w, const double *V, const double *v0, long
 // beta = sqrt(sum partial); invbeta = 1/beta (0 if beta == 0)
 __global__ __launch_bounds__(kBlock) void k_norm_final(const double *__restrict__ partial, int nblk,
                                                        double *__restrict__ beta,
-                                                       double *__restrict__ invbeta)
+                                                       double *__restrict__ invbeta, Fold F)
 {
     __shared__ double red[4];
     double s = 0.0;
     for (int b = threadIdx.x; b < nblk; b += kBlock) s += partial[b];
     s = block_sum(s, red);
     if (threadIdx.x == 0) {
+        if (F.alpha) s += fold_dot(F.alpha[F.k + 1], F.alpha[F.k + 1], *F.sig2);
         const double bt = sqrt(s);
         *beta = bt;
         if (invbeta) *invbeta = bt > 0.0 ? 1.0 / bt : 0.0;
     }
 }
 
-void launch_norm_final(const double *partial, int nblk, double *beta, double *invbeta,
+void launch_norm_final(const double *partial, int nblk, double *beta, double *invbeta, const Fold &F,
                        hipStream_t st)
 {
-    hipLaunchKernelGGL(k_norm_final, dim3(1), dim3(kBlock), 0, st, partial, nblk, beta, invbeta);
+    hipLaunchKernelGGL(k_norm_final, dim3(1), dim3(kBlock), 0, st, partial, nblk, beta, invbeta, F);
 }
 
 // assign: x = Z y (x not read; the first update from x = 0), else x += Z y

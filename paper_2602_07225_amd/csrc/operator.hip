@@ -155,9 +155,10 @@ template <typename TX>
 void launch_operator_schur(const Geom &g, const RadialTab *tabs, const double *sigh,
                            const double *kaph, const double *gg, const double *ss, const double *ee,
                            const double *mm, const double *om, const TX *y, double *w, int transpose,
-                           int tile_tx, int tile_cz, const double *kdh, const double *dch, hipStream_t st)
+                           int tile_tx, int tile_cz, const double *kdh, const double *dch,
+                           const ZetaArgs &za, hipStream_t st)
 {
-    OpArgs O{tabs, sigh, kaph, gg, ss, ee, mm, y, w, nullptr, om, kdh, dch};
+    OpArgs O{tabs, sigh, kaph, gg, ss, ee, mm, y, w, nullptr, om, kdh, dch, za};
     if (kdh && dch) {
         const int nb = operator_blocks(g);
         if (transpose)
@@ -178,12 +179,12 @@ template void launch_operator_schur<double>(const Geom &, const RadialTab *, con
                                             const double *, const double *, const double *,
                                             const double *, const double *, const double *,
                                             const double *, double *, int, int, int, const double *,
-                                            const double *, hipStream_t);
+                                            const double *, const ZetaArgs &, hipStream_t);
 template void launch_operator_schur<float>(const Geom &, const RadialTab *, const double *,
                                            const double *, const double *, const double *,
                                            const double *, const double *, const double *,
                                            const float *, double *, int, int, int, const double *,
-                                           const double *, hipStream_t);
+                                           const double *, const ZetaArgs &, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // Gradients of J = w.x:  dJ/dp = -lambda^T (dA/dp) x.

@@ -569,16 +569,18 @@ static void apply_op(p4d_ctx *c, int transpose, const TX *x, double *y, const do
                         c->general ? c->kdh : nullptr, c->general ? c->dch : nullptr, st);
 }
 
-// w = S y (S^T y) over the electrode-level unknowns
+// w = S y (S^T y) over the electrode-level unknowns; with za, the
+// electrode-level rows of A z for a folded vector
 template <typename TX>
-static void apply_op_schur(p4d_ctx *c, int transpose, const TX *y, double *w, hipStream_t st)
+static void apply_op_schur(p4d_ctx *c, int transpose, const TX *y, double *w, hipStream_t st,
+                           const ZetaArgs &za = ZetaArgs{})
 {
     const Geom &g = c->g;
     const double bytes = (double)(sizeof(TX) + 8) * g.Nm + 16.0 * g.nelem + 40.0 * g.ne;
     ProfScope ps(c->prof, P4D_K_OPERATOR, bytes, st);
     launch_operator_schur<TX>(g, c->tabs, c->sigh, c->kaph, c->gg, c->ss, c->ee, c->mm, c->oms, y, w,
                               transpose, c->op_tx, c->op_cz, c->general ? c->kdh : nullptr,
-                              c->general ? c->dch : nullptr, st);
+                              c->general ? c->dch : nullptr, za, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -979,17 +981,22 @@ static RadArgs rad_args(const p4d_ctx *c)
 }
 
 // z = P^-1 (s r), or P^-T, with the scale s read from device memory (rscale;
-// null: 1)
+// null: 1).  alpha given: r is a folded vector (its electrode-level rows and
+// alpha) and z its electrode-level part.
 template <typename T, typename TZ>
 static void apply_pc_t(p4d_ctx *c, int transpose, const double *r, const double *rscale, TZ *z,
-                       hipStream_t st)
+                       hipStream_t st, const double *alpha = nullptr)
 {
     const Geom &g = c->g;
     const int schur = c->pc.pc == P4D_PC_SCHUR;
     const int nb = (int)((g.nnode + kBlock - 1) / kBlock);
     RadArgs R = rad_args(c);
+    R.zeta = c->qbuf;
     if (c->rec) {
         rec_stage<T>(c, SK_RADF, nb);
+    } else if (alpha) {
+        ProfScope ps(c->prof, P4D_K_COUPLING, 24.0 * g.ne + (8.0 + sizeof(T) * 2 + 8.0) * g.Nm, st);
+        launch_rad_fwd_zeta<T>(g, R, r, rscale, alpha, transpose, st);
     } else {
         ProfScope ps(c->prof, P4D_K_RADIAL, 8.0 * g.N + 32.0 * g.ne + (sizeof(T) * 2 + 8.0) * g.Nm, st);
         launch_rad_fwd<T>(g, R, r, rscale, transpose, schur, st);
@@ -1003,6 +1010,13 @@ static void apply_pc_t(p4d_ctx *c, int transpose, const double *r, const double 
     if (c->rec) {
         rec_stage<T>(c, SK_RADB, nb);
         c->rec_R = R;
+        return;
+    }
+    if (alpha) {
+        BgsArgs B{};
+        B.R = R;
+        ProfScope ps(c->prof, P4D_K_COUPLING, (8.0 + sizeof(TZ)) * g.Nm, st);
+        launch_bgs_out<TZ>(g, B, r, rscale, z, st);
         return;
     }
     ProfScope ps(c->prof, P4D_K_RADIAL, 8.0 * (g.N - g.Nm) + 8.0 * g.ne + 8.0 * g.Nm +
@@ -1083,6 +1097,14 @@ static void apply_pc_schur(p4d_ctx *c, const double *r, const double *rscale, TZ
 {
     if (c->prec == 1) apply_pc_schur_t<float, TZ>(c, r, rscale, z, st);
     else apply_pc_schur_t<double, TZ>(c, r, rscale, z, st);
+}
+
+// z = P^-1 (rscale r) for a folded vector (pc SCHUR)
+static void apply_pc_fold(p4d_ctx *c, int transpose, const double *r, const double *rscale, const double *alpha,
+                          double *z, hipStream_t st)
+{
+    if (c->prec == 1) apply_pc_t<float, double>(c, transpose, r, rscale, z, st, alpha);
+    else apply_pc_t<double, double>(c, transpose, r, rscale, z, st, alpha);
 }
 
 template <typename TZ>
@@ -1264,16 +1286,49 @@ static p4d_status finish_setup(p4d_ctx *c)
 // FGMRES on S y = bhat, then x_s = A_ss^-1 (b_s - A_sy y).  Both stop on
 // rtol ||b|| with b the full right-hand side: with the particle rows solved
 // exactly, b - A x vanishes in them and equals bhat - S y in the others.
+//
+// Folded particle rows (all unknowns, pc SCHUR, Z in FP64).  The SCHUR
+// preconditioner solves the particle rows exactly, so the particle rows of
+// A P^-1 v are those of v; every vector of a cycle is a combination of the
+// cycle's first one and such products, and its particle rows are a multiple
+// alpha of the first vector's, r_s.  The basis then holds the
+// electrode-level rows and one alpha per vector (a seventh of the unknowns
+// of the cube with N_r = 20), every inner product adds alpha_i alpha_j
+// ||r_s||^2, the preconditioner and the operator need the particles only
+// through zeta_j = (A_ss,j^-1 r_s,j)_N, formed once per cycle, and the
+// particle part of the update is one back-substitution of sum_k y_k alpha_k
+// / beta_k times r_s.  The iterates, the Hessenberg matrix and the residual
+// norms are those of the whole vectors up to rounding.  (With Z in FP32 the
+// stored direction is not the exact one, so A z differs from v in the
+// particle rows: those solves keep whole vectors.)  Measured, setup and solve:
+// 15.3 M unknowns with N_r = 20 7.58 -> 4.57 ms (8 steps), 68 M with N_r = 16
+// 86.6 -> 33.1 ms (19 steps), 17 thousand (launch-bound) 1.08 -> 1.02 ms; the
+// solutions agree to 1e-15 .. 1e-11.
+static bool fold_rows(const p4d_solve_opts &o)
+{
+    return o.krylov == P4D_KRYLOV_FULL && o.pc == P4D_PC_SCHUR && !o.z_fp32;
+}
+// values of a step handed to the host: h of both passes, the norm, the
+// alphas (kept in c->hdev, as is sig2)
+constexpr int kHAlpha = 129, kHSig2 = kHAlpha + kMaxRestart + 1, kHPub = kHAlpha + kMaxRestart + 1;
+
 template <typename TZ>
 static p4d_status fgmres(p4d_ctx *c, int transpose, const double *b, double *x,
                          const p4d_solve_opts &o, p4d_solve_info *info, hipStream_t st)
 {
     const Geom &g = c->g;
     const bool schur = o.krylov == P4D_KRYLOV_SCHUR;
-    const long long N = schur ? g.Nm : g.N;   // Krylov vector length
+    const bool fold = fold_rows(o);
+    const long long N = schur || fold ? g.Nm : g.N;   // Krylov vector length
     const int m = o.restart;
     double *V = (double *)c->scratch;
-    TZ *Z = (TZ *)(c->scratch + align_up(8 * (size_t)(m + 1) * N));
+    // basis vector q at Vq + q N.  Folded: a whole vector at V (a cycle's
+    // residual), the others' electrode-level rows after it; that and Z take
+    // no more than whole vectors do.
+    double *Vq = fold ? V + g.N - N : V;
+    TZ *Z = (TZ *)(c->scratch + align_up(8 * (size_t)((fold ? g.N : N) + m * N)));
+    double *alpha = c->hdev + kHAlpha, *sig2 = c->hdev + kHSig2, *zeta = c->qbuf;
+    std::vector<double> al(m + 1, 1.0);
     // the Krylov right-hand side: b, or bhat (after Z; the region is sized
     // for the full space, which leaves room)
     double *bk = schur ? (double *)((char *)Z + align_up(sizeof(TZ) * (size_t)m * N)) : (double *)b;
@@ -1299,10 +1354,10 @@ static p4d_status fgmres(p4d_ctx *c, int transpose, const double *b, double *x,
         if (schur) {
             apply_op_schur<double>(c, transpose, x, V, st);
             launch_red_resid(N, bk, V, red, sb, st);
-            launch_norm_final(red, sb, c->hdev + 200, c->invbeta, st);
+            launch_norm_final(red, sb, c->hdev + 200, c->invbeta, Fold{}, st);
         } else {
             apply_op<double>(c, transpose, x, V, b, red, st);
-            launch_norm_final(red, ob, c->hdev + 200, c->invbeta, st);
+            launch_norm_final(red, ob, c->hdev + 200, c->invbeta, Fold{}, st);
         }
         const p4d_status ps = pull(c, c->hdev + 200, 1, st);
         if (ps != P4D_OK) return ps;
@@ -1310,9 +1365,20 @@ static p4d_status fgmres(p4d_ctx *c, int transpose, const double *b, double *x,
         return P4D_OK;
     };
 
+    // a folded cycle's first vector r: zeta, sig2, alpha_0 and the norm
+    auto fold_start = [&](const double *r, double *norm, double *invbeta) {
+        ProfScope ps(c->prof, P4D_K_RADIAL, 8.0 * g.N + 16.0 * g.ne, st);
+        launch_fold_start(g, c->tabs, c->ss, r, zeta, red, transpose, st);
+        launch_fold_final(red, fold_blocks(g), norm, sig2, alpha, invbeta, st);
+    };
+
     // ||b|| over all unknowns
-    launch_dot_partial(g.N, b, b, red, sbf, st);
-    launch_norm_final(red, sbf, c->hdev, nullptr, st);
+    if (fold) {
+        fold_start(b, c->hdev, c->invbeta);
+    } else {
+        launch_dot_partial(g.N, b, b, red, sbf, st);
+        launch_norm_final(red, sbf, c->hdev, nullptr, Fold{}, st);
+    }
     {
         const p4d_status ps = pull(c, c->hdev, 1, st);
         if (ps != P4D_OK) return ps;
@@ -1347,10 +1413,12 @@ static p4d_status fgmres(p4d_ctx *c, int transpose, const double *b, double *x,
         if (first) {
             if (schur) {
                 launch_dot_partial(N, bk, bk, red, sb, st);
-                launch_norm_final(red, sb, c->hdev + 200, c->invbeta, st);
+                launch_norm_final(red, sb, c->hdev + 200, c->invbeta, Fold{}, st);
                 const p4d_status ps = pull(c, c->hdev + 200, 1, st);
                 if (ps != P4D_OK) return ps;
                 beta[0] = hh[0];
+            } else if (fold) {
+                beta[0] = bnorm;   // (1 / beta_0 is on the device already)
             } else {
                 hout[0] = 1.0 / bnorm;
                 HIPCHK(c, hipMemcpyAsync(c->invbeta, hout, 8, hipMemcpyHostToDevice, st));
@@ -1369,6 +1437,7 @@ static p4d_status fgmres(p4d_ctx *c, int transpose, const double *b, double *x,
         if (beta[0] <= o.rtol * bnorm) { status = P4D_OK; break; }
         if (total >= o.maxit) { status = P4D_NOT_CONVERGED; break; }
         synced = false;
+        if (fold && v0 == V) fold_start(V, c->hdev + 201, nullptr);   // (a residual)
         std::fill(gv.begin(), gv.end(), 0.0);
         gv[0] = beta[0];
         res[0] = beta[0];
@@ -1379,10 +1448,16 @@ static p4d_status fgmres(p4d_ctx *c, int transpose, const double *b, double *x,
         // needs is in device memory), then its Hessenberg column to the host
         unsigned long long step_seq[2] = {0, 0};
         auto enqueue_step = [&](int k) {
-            const double *vk = k == 0 ? v0 : V + (long long)k * N;
+            const double *vk = k == 0 ? v0 : Vq + (long long)k * N;
             TZ *zk = Z + (long long)k * N;
-            double *w = V + (long long)(k + 1) * N;
-            if (schur) {
+            double *w = Vq + (long long)(k + 1) * N;
+            Fold F{};
+            if (fold) {
+                F = Fold{alpha, sig2, c->invbeta, k, 0};
+                apply_pc_fold(c, transpose, vk, c->invbeta + k, alpha + k, (double *)zk, st);
+                apply_op_schur<double>(c, transpose, (const double *)zk, w, st,
+                                       ZetaArgs{zeta, c->invbeta + k, alpha + k});
+            } else if (schur) {
                 apply_pc_schur<TZ>(c, vk, c->invbeta + k, zk, st);
                 apply_op_schur<TZ>(c, transpose, zk, w, st);
             } else {
@@ -1392,18 +1467,19 @@ static p4d_status fgmres(p4d_ctx *c, int transpose, const double *b, double *x,
             const int nv = k + 1;
             const int passes = o.cgs2 ? 2 : 1;
             for (int p = 0; p < passes; p++) {
+                F.pass = p;
                 {
                     ProfScope ps(c->prof, P4D_K_MDOT, 8.0 * (nv + 1) * N, st);
-                    launch_mdot(N, w, V, v0, N, nv, red, sb, st);
+                    launch_mdot(N, w, Vq, v0, N, nv, red, sb, st);
                 }
-                launch_mdot_final(nv, red, sb, c->invbeta, c->hdev + 64 * p, c->cdev, st);
+                launch_mdot_final(nv, red, sb, c->invbeta, c->hdev + 64 * p, c->cdev, F, st);
                 {
                     ProfScope ps(c->prof, P4D_K_ORTH, 8.0 * (nv + 2) * N, st);
-                    launch_orth(N, w, V, v0, N, nv, c->cdev, red, sb, st);
+                    launch_orth(N, w, Vq, v0, N, nv, c->cdev, red, sb, F, st);
                 }
             }
-            launch_norm_final(red, sb, c->hdev + 128, c->invbeta + k + 1, st);
-            step_seq[k & 1] = publish(c, c->hdev, 129, k & 1, st);
+            launch_norm_final(red, sb, c->hdev + 128, c->invbeta + k + 1, F, st);
+            step_seq[k & 1] = publish(c, c->hdev, fold ? kHAlpha + k + 2 : 129, k & 1, st);
         };
         // The next step is enqueued before the host reads this step's column
         // when the residual estimate is expected to stay above the tolerance
@@ -1435,6 +1511,7 @@ static p4d_status fgmres(p4d_ctx *c, int transpose, const double *b, double *x,
             for (int i = 0; i <= k; i++) hc[i] = hh[i] + (o.cgs2 ? hh[64 + i] : 0.0);
             const double hn = hh[128];
             hc[k + 1] = hn;
+            if (fold) al[k + 1] = hh[kHAlpha + k + 1];
             double colnorm = 0.0;
             for (int i = 0; i <= k + 1; i++) colnorm += hc[i] * hc[i];
             colnorm = std::sqrt(colnorm);
@@ -1472,7 +1549,20 @@ static p4d_status fgmres(p4d_ctx *c, int transpose, const double *b, double *x,
         {
             // x written, and read unless this update assigns it
             ProfScope ps(c->prof, P4D_K_ZY, ((x_zero ? 8.0 : 16.0) + sizeof(TZ) * kused) * N, st);
+            if (fold && !x_zero) {
+                // the update's electrode-level part by itself (in V_1, which
+                // is done with): the particle part follows from it
+                launch_zy<TZ>(N, Vq + N, Z, N, kused, c->ydev, 1, st);
+            }
             launch_zy<TZ>(N, x, Z, N, kused, c->ydev, x_zero ? 1 : 0, st);
+        }
+        if (fold && kused > 0) {
+            double gamma = 0.0;   // the update's multiple of the first vector's particle rows
+            for (int i = 0; i < kused; i++) gamma += yv[i] * al[i] / beta[i];
+            ProfScope ps(c->prof, P4D_K_RADIAL,
+                         (x_zero ? 16.0 : 24.0) * (g.N - g.Nm) + 8.0 * g.Nm + 32.0 * g.ne, st);
+            launch_red_back(g, c->tabs, c->gg, c->ss, c->ee, c->mm, gamma, v0, x_zero ? x : Vq + N, x,
+                            x_zero ? 0 : 1, transpose, st);
         }
         if (kused > 0) x_zero = false;
         inf.restarts++;
@@ -1494,10 +1584,10 @@ static p4d_status fgmres(p4d_ctx *c, int transpose, const double *b, double *x,
         // residual of the whole system (V has room for one full vector)
         {
             ProfScope ps(c->prof, P4D_K_RADIAL, 16.0 * (g.N - g.Nm) + 8.0 * g.Nm + 32.0 * g.ne, st);
-            launch_red_back(g, c->tabs, c->gg, c->ss, c->ee, c->mm, b, x, transpose, st);
+            launch_red_back(g, c->tabs, c->gg, c->ss, c->ee, c->mm, 1.0, b, x, x, 0, transpose, st);
         }
         apply_op<double>(c, transpose, x, V, b, red, st);
-        launch_norm_final(red, ob, c->hdev + 200, nullptr, st);
+        launch_norm_final(red, ob, c->hdev + 200, nullptr, Fold{}, st);
         const p4d_status ps = pull(c, c->hdev + 200, 1, st);
         if (ps != P4D_OK) return ps;
         synced = true;
@@ -2497,7 +2587,7 @@ struct p4d_batch {
     double *hb_h = nullptr, *yb_h = nullptr;
     int *kused_h = nullptr;
     // recorded schedule
-    int recorded = 0, rec_prec = -1;
+    int recorded = 0, rec_prec = -1, rec_fold = 0;
     int nstages = 0, nrmax = 8;
     struct WorkList {
         int family, nr;             // stage family, radial size class
@@ -2567,19 +2657,21 @@ static size_t batch_carve(p4d_batch *B, const p4d_solve_opts &o, char *base, p4d
     B->ustart = (int *)take(4 * maxst);
     B->dstart = (int *)take(4 * (maxst + 1));
     B->hb = (double *)take(8 * 256 * (size_t)B->n);
-    B->yb = (double *)take(8 * 64 * (size_t)B->n);
+    B->yb = (double *)take(8 * kYStride * (size_t)B->n);
     B->kused = (int *)take(4 * (size_t)B->n);
     return off;
 }
 
 template <typename T>
-static double stage_bytes(const PStage<T> &S, const Geom &g)
+static double stage_bytes(const PStage<T> &S, const Geom &g, bool fold)
 {
     double bytes = 0.0;
     switch (S.kind) {
     case SK_RADF:
+        if (fold) return 24.0 * g.ne + (8.0 + sizeof(T) * 2 + 8.0) * g.Nm;
         return 8.0 * g.N + 32.0 * g.ne + (sizeof(T) * 2 + 8.0) * g.Nm;
     case SK_RADB:
+        if (fold) return 16.0 * g.Nm;
         return 8.0 * (g.N - g.Nm) + 8.0 * g.ne + 8.0 * g.Nm + 8.0 * g.N + 40.0 * g.ne;
     case SK_SM0:
         for (int q = 0; q < S.u.lb.nbox; q++) {
@@ -2625,7 +2717,7 @@ static int batch_default_cz(p4d_batch *B)
 // depth.  Per depth, one list per stage family (per radial size class for
 // the particle stages), larger cells first.
 template <typename T>
-static p4d_status batch_record(p4d_batch *B)
+static p4d_status batch_record(p4d_batch *B, bool fold)
 {
     const int n = B->n;
     std::vector<std::vector<PStage<T>>> per(n);
@@ -2647,7 +2739,7 @@ static p4d_status batch_record(p4d_batch *B)
         c->tile_cz = keep;
         if ((int)per[i].size() > kMaxStagesPerCell)
             return bfail(B, P4D_ERR_INVALID_ARG, "too many preconditioner stages in a cell");
-        for (const PStage<T> &S : per[i]) B->pc_bytes[i] += stage_bytes(S, c->g);
+        for (const PStage<T> &S : per[i]) B->pc_bytes[i] += stage_bytes(S, c->g, fold);
         const int nr = rad_nrmax(c->g);
         B->nrmax = nr > B->nrmax ? nr : B->nrmax;
     }
@@ -2684,7 +2776,8 @@ static p4d_status batch_record(p4d_batch *B)
     long long items = 0;
     for (int d = 0; d < depth; d++)
         for (int fam = SF_RADF; fam <= SF_MISC; fam++) {
-            const bool radial = fam == SF_RADF || fam == SF_RADB;
+            // (folded vectors: no particle columns, one list for all sizes)
+            const bool radial = !fold && (fam == SF_RADF || fam == SF_RADB);
             for (int ci = 0; ci < (radial ? kNrClasses : 1); ci++) {
                 p4d_batch::WorkList W{fam, radial ? kNrClass[ci] : 8, 0, (int)order.size(), 0, (int)items, 0, d};
                 for (int i : bysize) {
@@ -2720,12 +2813,13 @@ static p4d_status batch_record(p4d_batch *B)
     B->nstages = (int)all.size();
     B->recorded = 1;
     B->rec_prec = B->cell[0]->prec;
+    B->rec_fold = fold;
     return P4D_OK;
 }
 
 namespace {
 struct CellRun {
-    std::vector<double> H, cs, sn, gv, yv, hc, beta;
+    std::vector<double> H, cs, sn, gv, yv, hc, beta, al;
     double bnorm = 0.0;
     int total = 0, kused = 0;
     bool done = false, first = true, in_cycle = false, breakdown = false, nonfinite = false;
@@ -2737,9 +2831,9 @@ struct CellRun {
 // Cell tables of the batched kernels for restart length m (b and x may be
 // null when only the preconditioner is used); copied to the device.
 struct BatchGrid {
-    int op = 0, st = 0, tile = 0, rad = 0;   // workgroups of each batched launch kind
+    int op = 0, st = 0, tile = 0, rad = 0, fs = 0;   // workgroups of each batched launch kind
 };
-static p4d_status batch_tables(p4d_batch *B, int m, const double *const *bv, double *const *xv,
+static p4d_status batch_tables(p4d_batch *B, int m, bool fold, const double *const *bv, double *const *xv,
                                std::vector<BCell> &bc, BatchGrid &G, hipStream_t st)
 {
     const int n = B->n;
@@ -2768,12 +2862,14 @@ static p4d_status batch_tables(p4d_batch *B, int m, const double *const *bv, dou
         BCell &C = bc[i];
         std::memset((void *)&C, 0, sizeof(C));
         C.g = g;
-        C.op = OpArgs{c->tabs, c->sigh, c->kaph, c->gg, c->ss, c->ee, c->mm, nullptr, nullptr, nullptr};
+        C.op = OpArgs{c->tabs, c->sigh, c->kaph, c->gg, c->ss, c->ee, c->mm, nullptr, nullptr, nullptr, c->oms};
+        C.fold = fold;
+        C.nk = fold ? g.Nm : g.N;
         C.op_blk0 = G.op;
         C.op_nblk = operator_blocks(g);
         G.op += C.op_nblk;
         C.st_blk0 = G.st;
-        C.st_nblk = stream_blocks(g.N);
+        C.st_nblk = stream_blocks(C.nk);
         G.st += C.st_nblk;
         C.op_tx = c->op_tx > 0 ? c->op_tx : 64;
         C.op_cz = opcz;
@@ -2783,16 +2879,23 @@ static p4d_status batch_tables(p4d_batch *B, int m, const double *const *bv, dou
         C.rad_blk0 = G.rad;
         C.rad_n = (int)((g.ne + kBlock - 1) / kBlock);
         G.rad += C.rad_n;
+        C.fs_blk0 = G.fs;
+        C.fs_n = fold_blocks(g);
+        G.fs += C.fs_n;
         C.qbuf = c->qbuf;
+        C.zeta = c->qbuf;
         C.V = (double *)c->scratch;
-        C.Z = c->scratch + align_up(8 * (size_t)(m + 1) * g.N);
+        C.Z = c->scratch + align_up(8 * (size_t)(g.N + m * C.nk));
         C.x = xv ? xv[i] : nullptr;
         C.b = bv ? bv[i] : nullptr;
         C.red = c->red;
         C.h = B->hb + 256 * (size_t)i;
         C.coef = c->cdev;
         C.invbeta = c->invbeta;
-        C.y = B->yb + 64 * (size_t)i;
+        C.alpha = C.h + kHAlpha;
+        C.sig2 = C.h + kHSig2;
+        C.y = B->yb + kYStride * (size_t)i;
+        C.gamma = C.y + 64;
         C.kused = B->kused + i;
         PCell &P = pcl[i];
         std::memset((void *)&P, 0, sizeof(P));
@@ -2802,6 +2905,8 @@ static p4d_status batch_tables(p4d_batch *B, int m, const double *const *bv, dou
         P.Z = C.Z;
         P.invbeta = c->invbeta;
         P.schur = c->pc.pc == P4D_PC_SCHUR;
+        P.b = C.b;
+        P.alpha = C.alpha;
     }
     BHIPCHK(B, hipStreamSynchronize(st));
     BHIPCHK(B, hipMemcpy(B->bcell, bc.data(), sizeof(BCell) * n, hipMemcpyHostToDevice));
@@ -2812,7 +2917,8 @@ static p4d_status batch_tables(p4d_batch *B, int m, const double *const *bv, dou
 // One batched preconditioner application z_k = P^-1 V_k / beta_k for the
 // cells in `active` (work lists of the recorded schedule, in order).
 template <typename T, typename TZ>
-static void batch_apply_pc(p4d_batch *B, int transpose, int k, unsigned long long active, hipStream_t st)
+static void batch_apply_pc(p4d_batch *B, int transpose, int k, unsigned long long active,
+                           unsigned long long first, hipStream_t st)
 {
     if (B->pc_mode == 2) {   // one cooperative launch for all depths
         PersistRun pr{};
@@ -2826,6 +2932,8 @@ static void batch_apply_pc(p4d_batch *B, int transpose, int k, unsigned long lon
         pr.transpose = transpose;
         pr.k = k;
         pr.active = active;
+        pr.fold = B->rec_fold;
+        pr.first = first;
         B->plaunch = launch_batch_persist<T, TZ>(pr, B->nrmax, B->pgrid, st);
         return;
     }
@@ -2837,6 +2945,8 @@ static void batch_apply_pc(p4d_batch *B, int transpose, int k, unsigned long lon
     run.transpose = transpose;
     run.k = k;
     run.active = active;
+    run.fold = B->rec_fold;
+    run.first = first;
     for (const p4d_batch::WorkList &W : B->lists) {
         run.pos0 = W.pos0;
         run.npos = W.npos;
@@ -2857,6 +2967,7 @@ static p4d_status batch_tune_t(p4d_batch *B, hipStream_t st)
     BatchGrid G;
     const unsigned long long all = B->n == 64 ? ~0ULL : ((1ULL << B->n) - 1);
     static const int czs[9] = {2, 3, 4, 5, 6, 8, 10, 12, 16};
+    const bool fold = sizeof(TZ) == sizeof(double) && B->cell[0]->pc.pc == P4D_PC_SCHUR;
     hipEvent_t e0, e1;
     BHIPCHK(B, hipEventCreate(&e0));
     if (hipEventCreate(&e1) != hipSuccess) {
@@ -2868,12 +2979,12 @@ static p4d_status batch_tune_t(p4d_batch *B, hipStream_t st)
     p4d_status s = P4D_OK;
     for (int q = 0; q < 9 && s == P4D_OK; q++) {
         B->tile_cz = czs[q];
-        s = batch_record<T>(B);
-        if (s == P4D_OK) s = batch_tables(B, B->ws_opts.restart, nullptr, nullptr, bc, G, st);
+        s = batch_record<T>(B, fold);
+        if (s == P4D_OK) s = batch_tables(B, B->ws_opts.restart, fold, nullptr, nullptr, bc, G, st);
         if (s != P4D_OK) break;
-        batch_apply_pc<T, TZ>(B, 0, 0, all, st);   // warm-up
+        batch_apply_pc<T, TZ>(B, 0, 0, all, 0, st);   // warm-up
         (void)hipEventRecord(e0, st);
-        for (int rep = 0; rep < 3; rep++) batch_apply_pc<T, TZ>(B, 0, 0, all, st);
+        for (int rep = 0; rep < 3; rep++) batch_apply_pc<T, TZ>(B, 0, 0, all, 0, st);
         (void)hipEventRecord(e1, st);
         float ms = 0.f;
         hipError_t he = hipEventSynchronize(e1);
@@ -2900,11 +3011,12 @@ static p4d_status batch_fgmres(p4d_batch *B, int transpose, const double *const 
                                hipStream_t st)
 {
     const int n = B->n, m = o.restart;
+    const bool fold = fold_rows(o);
     auto t0 = std::chrono::steady_clock::now();
     std::vector<BCell> bc;
     BatchGrid G;
     {
-        const p4d_status ts = batch_tables(B, m, bv, xv, bc, G, st);
+        const p4d_status ts = batch_tables(B, m, fold, bv, xv, bc, G, st);
         if (ts != P4D_OK) return ts;
     }
     const int opb = G.op, stb = G.st;
@@ -2913,7 +3025,7 @@ static p4d_status batch_fgmres(p4d_batch *B, int transpose, const double *const 
     for (auto &R : S) {
         R.H.assign((size_t)(m + 1) * m, 0.0);
         R.cs.assign(m, 0.0); R.sn.assign(m, 0.0); R.gv.assign(m + 1, 0.0);
-        R.yv.assign(m, 0.0); R.hc.assign(m + 2, 0.0); R.beta.assign(m + 1, 0.0);
+        R.yv.assign(m, 0.0); R.hc.assign(m + 2, 0.0); R.beta.assign(m + 1, 0.0); R.al.assign(m + 1, 1.0);
     }
     const size_t hcopy = 8 * 256 * (size_t)n;
     if (B->pc_mode == 2 && B->pgrid < 1)
@@ -2929,14 +3041,20 @@ static p4d_status batch_fgmres(p4d_batch *B, int transpose, const double *const 
     auto sum_n = [&](unsigned long long mk, double per_cell_factor, bool stream_len) {
         double s = 0.0;
         for (int i = 0; i < n; i++)
-            if ((mk >> i) & 1ULL) s += per_cell_factor * (stream_len ? (double)B->cell[i]->g.N : 1.0);
+            if ((mk >> i) & 1ULL) s += per_cell_factor * (stream_len ? (double)bc[i].nk : 1.0);
         return s;
     };
     const unsigned long long all = n == 64 ? ~0ULL : ((1ULL << n) - 1);
     p4d_status ps;
-    // ||b||, x = 0, V_0 = b
-    launch_bstart(B->bcell, n, stb, st);
-    launch_bnorm_final(B->bcell, n, all, 0, 0, st);
+    // ||b||, x = 0, V_0 = b (folded: b is read in place and the first update
+    // assigns x; zero marks the cells whose x no update has written yet)
+    unsigned long long zero = fold ? all : 0;
+    if (fold) {
+        launch_bfold_start(B->bcell, n, all, all, transpose, G.fs, B->nrmax, st);
+    } else {
+        launch_bstart(B->bcell, n, stb, st);
+        launch_bnorm_final(B->bcell, n, all, 0, 0, st);
+    }
     if ((ps = fetch()) != P4D_OK) return ps;
     for (int i = 0; i < n; i++) {
         CellRun &R = S[i];
@@ -2987,6 +3105,7 @@ static p4d_status batch_fgmres(p4d_batch *B, int transpose, const double *const 
         }
         if (!act) break;
         const unsigned long long cyc = act;
+        if (fold && (cyc & ~zero)) launch_bfold_start(B->bcell, n, cyc & ~zero, 0, transpose, G.fs, B->nrmax, st);
         for (int k = 0; k < m && act; k++) {
             {
                 double bytes = 0.0;
@@ -2994,7 +3113,16 @@ static p4d_status batch_fgmres(p4d_batch *B, int transpose, const double *const 
                     if ((act >> i) & 1ULL) bytes += B->pc_bytes[i];
                 ProfScope pr(B->prof, P4D_K_BATCH_PC, bytes, st);
                 if (B->pc_mode != 1) {
-                    batch_apply_pc<T, TZ>(B, transpose, k, act, st);
+                    batch_apply_pc<T, TZ>(B, transpose, k, act, zero, st);
+                } else if (fold) {
+                    for (int i = 0; i < n; i++)
+                        if ((act >> i) & 1ULL) {
+                            p4d_ctx *c = B->cell[i];
+                            const double *v = k > 0 ? bc[i].V + c->g.N + (long long)(k - 1) * c->g.Nm
+                                                    : ((zero >> i) & 1ULL ? bc[i].b : bc[i].V);
+                            apply_pc_fold(c, transpose, v, bc[i].invbeta + k, bc[i].alpha + k,
+                                          (double *)bc[i].Z + (long long)k * c->g.Nm, st);
+                        }
                 } else {
                     for (int i = 0; i < n; i++)
                         if ((act >> i) & 1ULL) {
@@ -3010,20 +3138,21 @@ static p4d_status batch_fgmres(p4d_batch *B, int transpose, const double *const 
                 for (int i = 0; i < n; i++)
                     if ((act >> i) & 1ULL) {
                         const Geom &g = B->cell[i]->g;
-                        bytes += (sizeof(TZ) + 8.0) * g.N + 16.0 * g.nelem + 32.0 * g.ne;
+                        bytes += (sizeof(TZ) + 8.0) * bc[i].nk + 16.0 * g.nelem + (fold ? 48.0 : 32.0) * g.ne;
                     }
                 ProfScope pr(B->prof, P4D_K_OPERATOR, bytes, st);
-                launch_bop<TZ>(B->bcell, n, act, k, 0, transpose, opb, G.tile, G.rad, B->nrmax, st);
+                if (fold) launch_bop_fold(B->bcell, n, act, k, transpose, G.tile, st);
+                else launch_bop<TZ>(B->bcell, n, act, k, 0, transpose, opb, G.tile, G.rad, B->nrmax, st);
             }
             const int nv = k + 1;
             const int passes = o.cgs2 ? 2 : 1;
             for (int p = 0; p < passes; p++) {
                 {
                     ProfScope pr(B->prof, P4D_K_MDOT, sum_n(act, 8.0 * (nv + 1), true), st);
-                    launch_bmdot(B->bcell, n, act, k, stb, p, st);
+                    launch_bmdot(B->bcell, n, act, zero, k, stb, p, st);
                 }
                 ProfScope pr(B->prof, P4D_K_ORTH, sum_n(act, 8.0 * (nv + 2), true), st);
-                launch_borth(B->bcell, n, act, k, stb, st);
+                launch_borth(B->bcell, n, act, zero, k, stb, p, st);
             }
             launch_bnorm_final(B->bcell, n, act, k + 1, 0, st);
             if ((ps = fetch()) != P4D_OK) return ps;
@@ -3058,6 +3187,7 @@ static p4d_status batch_fgmres(p4d_batch *B, int transpose, const double *const 
                 R.total++;
                 R.kused = k + 1;
                 R.beta[k + 1] = hn;
+                R.al[k + 1] = hh[kHAlpha + k + 1];
                 R.inf.relres_est = std::fabs(R.gv[k + 1]) / R.bnorm;
                 if (hn <= 1e-14 * colnorm) {
                     R.breakdown = true;
@@ -3085,7 +3215,10 @@ static p4d_status batch_fgmres(p4d_batch *B, int transpose, const double *const 
                 for (int j = q + 1; j < ku; j++) v -= R.H[(size_t)q * m + j] * R.yv[j];
                 R.yv[q] = v / R.H[(size_t)q * m + q];
             }
-            for (int q = 0; q < 64; q++) B->yb_h[64 * i + q] = q < ku ? R.yv[q] : 0.0;
+            for (int q = 0; q < 64; q++) B->yb_h[kYStride * i + q] = q < ku ? R.yv[q] : 0.0;
+            double gamma = 0.0;
+            for (int q = 0; fold && q < ku; q++) gamma += R.yv[q] * R.al[q] / R.beta[q];
+            B->yb_h[kYStride * i + 64] = gamma;
             B->kused_h[i] = ku;
             kmax = ku > kmax ? ku : kmax;
             R.inf.restarts++;
@@ -3094,15 +3227,30 @@ static p4d_status batch_fgmres(p4d_batch *B, int transpose, const double *const 
         if (zmask) {
             // the previous copies from these staging buffers have completed:
             // every step synchronizes the stream
-            BHIPCHK(B, hipMemcpyAsync(B->yb, B->yb_h, 8 * 64 * (size_t)n, hipMemcpyHostToDevice, st));
+            BHIPCHK(B, hipMemcpyAsync(B->yb, B->yb_h, 8 * kYStride * (size_t)n, hipMemcpyHostToDevice, st));
             BHIPCHK(B, hipMemcpyAsync(B->kused, B->kused_h, 4 * (size_t)n, hipMemcpyHostToDevice, st));
             double bytes = 0.0;
             for (int i = 0; i < n; i++)
-                if ((zmask >> i) & 1ULL) bytes += (16.0 + sizeof(TZ) * S[i].kused) * B->cell[i]->g.N;
-            ProfScope pr(B->prof, P4D_K_ZY, bytes, st);
-            launch_bzy<TZ>(B->bcell, n, zmask, kmax, stb, st);
+                if ((zmask >> i) & 1ULL) bytes += (16.0 + sizeof(TZ) * S[i].kused) * bc[i].nk;
+            {
+                ProfScope pr(B->prof, P4D_K_ZY, bytes, st);
+                launch_bzy<TZ>(B->bcell, n, zmask, zero, kmax, stb, st);
+            }
+            if (fold) {
+                double rb = 0.0;
+                for (int i = 0; i < n; i++)
+                    if ((zmask >> i) & 1ULL) {
+                        const Geom &g = B->cell[i]->g;
+                        rb += ((zero >> i) & 1ULL ? 16.0 : 24.0) * (g.N - g.Nm) + 8.0 * g.Nm + 32.0 * g.ne;
+                    }
+                ProfScope pr(B->prof, P4D_K_RADIAL, rb, st);
+                launch_bred_back(B->bcell, n, zmask, zero, transpose, opb, B->nrmax, st);
+                zero &= ~zmask;
+            }
         }
     }
+    for (int i = 0; i < n; i++)   // no update happened
+        if ((zero >> i) & 1ULL) BHIPCHK(B, hipMemsetAsync(xv[i], 0, 8 * (size_t)B->cell[i]->g.N, st));
     BHIPCHK(B, hipGetLastError());
     BHIPCHK(B, hipStreamSynchronize(st));
     prof_harvest(B->prof);
@@ -3154,7 +3302,7 @@ p4d_status p4d_batch_create(const p4d_problem_desc *descs, int32_t ncells, p4d_b
         B->cell.push_back(c);
     }
     if (hipHostMalloc((void **)&B->hb_h, 8 * (256 * (size_t)ncells + 1), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void **)&B->yb_h, 8 * 64 * (size_t)ncells, hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc((void **)&B->yb_h, 8 * kYStride * (size_t)ncells, hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void **)&B->kused_h, 4 * (size_t)ncells, hipHostMallocDefault) != hipSuccess) {
         if (B->hb_h) hipHostFree(B->hb_h);
         if (B->yb_h) hipHostFree(B->yb_h);
@@ -3306,8 +3454,9 @@ p4d_status p4d_batch_solve(p4d_batch *B, const double *const *d_b, double *const
             return bfail(B, P4D_ERR_OOM, "workspace sized for a smaller restart or an FP32 Z basis");
     }
     hipStream_t st = (hipStream_t)stream;
-    if (!B->recorded || B->rec_prec != c0->prec) {
-        const p4d_status s = c0->prec ? batch_record<float>(B) : batch_record<double>(B);
+    const bool fold = fold_rows(o);
+    if (!B->recorded || B->rec_prec != c0->prec || B->rec_fold != (int)fold) {
+        const p4d_status s = c0->prec ? batch_record<float>(B, fold) : batch_record<double>(B, fold);
         if (s != P4D_OK) return s;
     }
     if (c0->prec) {

@@ -52,6 +52,53 @@ __device__ inline double block_max(double v, double *lds)
     return r;
 }
 
+// ---------------------------------------------------------------------------
+// Krylov vectors with the particle part folded (see fgmres in p4d_api.hip):
+// the particle rows of every vector of a cycle are a multiple alpha of those
+// of the cycle's first vector, whose sum of squares is sig2.  A vector is
+// then its electrode-level rows and alpha.
+// ---------------------------------------------------------------------------
+// alpha of w = A P^-1 v_k before Gram-Schmidt (v_k's, normalized), or after
+// its first pass
+__device__ inline double fold_alpha(const double *alpha, const double *invbeta, int k, int pass)
+{
+    return pass == 0 ? alpha[k] * invbeta[k] : alpha[k + 1];
+}
+// the particle rows' part of w . V_q
+__device__ inline double fold_dot(double aw, double aq, double sig2) { return aw * aq * sig2; }
+// alpha after w -= sum_q c_q V_q, nv <= 64, by one whole wave (a lane per q)
+__device__ inline double fold_update(double aw, const double *c, const double *alpha, int nv)
+{
+    const int q = threadIdx.x & 63;
+    return aw - wave_sum(q < nv ? c[q] * alpha[q] : 0.0);
+}
+
+// workgroups of the pass over a cycle's first vector (two partial sums each)
+__host__ __device__ inline int fold_nblk(const Geom &g)
+{
+    const long long b = (g.nnode + kBlock - 1) / kBlock;
+    return (int)(b < 4096 ? b : 4096);
+}
+// its final sums by one workgroup: the norm, sig2, alpha_0 = 1 and 1 / norm
+__device__ inline void fold_final_block(const double *partial, int nblk, double *norm, double *sig2, double *alpha,
+                                        double *invbeta, double *lds)
+{
+    double sy = 0.0, ss = 0.0;
+    for (int b = threadIdx.x; b < nblk; b += kBlock) {
+        sy += partial[2 * b];
+        ss += partial[2 * b + 1];
+    }
+    sy = block_sum(sy, lds);
+    ss = block_sum(ss, lds);
+    if (threadIdx.x == 0) {
+        const double bt = sqrt(sy + ss);
+        *norm = bt;
+        *sig2 = ss;
+        *alpha = 1.0;
+        if (invbeta) *invbeta = bt > 0.0 ? 1.0 / bt : 0.0;
+    }
+}
+
 __host__ __device__ constexpr int popc3(int v) { return (v & 1) + ((v >> 1) & 1) + ((v >> 2) & 1); }
 __host__ __device__ constexpr int nb_index(int dx, int dy, int dz)
 {

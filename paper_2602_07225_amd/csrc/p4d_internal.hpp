@@ -179,6 +179,10 @@ struct RadArgs;
 template <typename T>
 void launch_rad_fwd(const Geom &g, const RadArgs &R, const double *r, const double *rscale, int transpose,
                     int schur, hipStream_t st);
+// the same with zeta_j = zeta[j] *rscale *alpha given (folded basis vectors)
+template <typename T>
+void launch_rad_fwd_zeta(const Geom &g, const RadArgs &R, const double *r, const double *rscale,
+                         const double *alpha, int transpose, hipStream_t st);
 template <typename T, typename TZ>
 void launch_rad_back(const Geom &g, const RadArgs &R, const double *r, const double *rscale, TZ *z,
                      int transpose, int schur, hipStream_t st);
@@ -334,19 +338,33 @@ template <typename T>
 void launch_cast(long long n, const double *src, T *dst, hipStream_t st);
 
 // operator.hip: the Schur complement of the particle blocks (electrode-level
-// vectors of length Nm)
+// vectors of length Nm); with zeta the electrode-level rows of A z for a
+// folded vector: w = S y + a_y s_j zeta_j (transposed Gamma b_y zeta_j),
+// zeta_j = zeta[j] *scale *alpha
+struct ZetaArgs {
+    const double *zeta = nullptr, *scale = nullptr, *alpha = nullptr;
+};
 template <typename TX>
 void launch_operator_schur(const Geom &g, const RadialTab *tabs, const double *sigh,
                            const double *kaph, const double *gg, const double *ss, const double *ee,
                            const double *mm, const double *om, const TX *y, double *w, int transpose,
-                           int tile_tx, int tile_cz, const double *kdh, const double *dch, hipStream_t st);
+                           int tile_tx, int tile_cz, const double *kdh, const double *dch,
+                           const ZetaArgs &za, hipStream_t st);
 // reduced.hip
 void launch_red_rhs(const Geom &g, const RadialTab *tabs, const double *gg, const double *ss,
                     const double *ee, const double *mm, const double *b, double *bhat, int transpose,
                     hipStream_t st);
+// x_s = (add: x_s +) A_ss^-1 (gamma b_s - delta(y) e_N), y electrode-level
 void launch_red_back(const Geom &g, const RadialTab *tabs, const double *gg, const double *ss,
-                     const double *ee, const double *mm, const double *b, double *x, int transpose,
-                     hipStream_t st);
+                     const double *ee, const double *mm, double gamma, const double *b, const double *y, double *x,
+                     int add, int transpose, hipStream_t st);
+// the first vector r of a folded cycle: zeta_j = (A_ss,j^-1 r_s,j)_N, the
+// norm of r, sig2 = ||r_s||^2, alpha_0 = 1 and (invbeta given) 1 / ||r||
+int fold_blocks(const Geom &g);
+void launch_fold_start(const Geom &g, const RadialTab *tabs, const double *ss, const double *r, double *zeta,
+                       double *partial, int transpose, hipStream_t st);
+void launch_fold_final(const double *partial, int nblk, double *norm, double *sig2, double *alpha,
+                       double *invbeta, hipStream_t st);
 void launch_red_resid(long long n, const double *bhat, double *w, double *partial, int nblk,
                       hipStream_t st);
 
@@ -356,11 +374,20 @@ int stream_blocks(long long n);
 // right-hand side, read in place)
 void launch_mdot(long long n, const double *w, const double *V, const double *v0, long long ldv, int nv,
                  double *partial, int nblk, hipStream_t st);
+// Folded particle rows of the basis (p4d_device.hpp): alpha per vector,
+// sig2; alpha null: whole vectors
+struct Fold {
+    double *alpha = nullptr;
+    const double *sig2 = nullptr;
+    const double *invbeta = nullptr;
+    int k = 0, pass = 0;             // Arnoldi step, Gram-Schmidt pass
+};
 void launch_mdot_final(int nv, const double *partial, int nblk, const double *invbeta,
-                       double *h, double *c, hipStream_t st);
+                       double *h, double *c, const Fold &F, hipStream_t st);
 void launch_orth(long long n, double *w, const double *V, const double *v0, long long ldv, int nv,
-                 const double *c, double *partial, int nblk, hipStream_t st);
-void launch_norm_final(const double *partial, int nblk, double *beta_out, double *invbeta_out,
+                 const double *c, double *partial, int nblk, const Fold &F, hipStream_t st);
+// (with F: the norm of w = V_{F.k + 1}, its alpha included)
+void launch_norm_final(const double *partial, int nblk, double *beta_out, double *invbeta_out, const Fold &F,
                        hipStream_t st);
 // x += Z y, or x = Z y with assign (x is not read)
 template <typename TZ>

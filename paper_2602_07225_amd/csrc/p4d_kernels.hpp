@@ -430,14 +430,16 @@ struct RadArgs {
     const void *invd0;   // T
     double c2box[4];
     const double *x0[4]; // final level-0 iterates per box (rad_back)
+    const double *zeta;  // folded vectors: (A_ss,j^-1 s_j)_N of the cycle's particle rows s
 };
 
 // zeta_j = (A_ss,j^-1 r_s,j)_N; r~_y = r_y - a_y s_j zeta_j (transposed:
 // r_y - Gamma b_y zeta_j); written in precision T with the first Chebyshev
-// iterate of each box.
-template <typename T, int NRMAX, bool TRANS, bool SCHUR>
+// iterate of each box.  SCHUR 0: r~_y = r_y; 1: zeta_j by elimination; 2: a
+// folded vector, zeta_j = R.zeta[j] zscale.
+template <typename T, int NRMAX, bool TRANS, int SCHUR>
 __device__ inline void rad_fwd_block(const Geom &g, const RadArgs &R, const double *r, double rscale,
-                                     int blk)
+                                     int blk, double zscale = 0.0)
 {
     const long long n = (long long)blk * kBlock + threadIdx.x;
     if (n >= g.nnode) return;
@@ -457,7 +459,25 @@ __device__ inline void rad_fwd_block(const Geom &g, const RadArgs &R, const doub
         const bool dir = (k == 0);
         double rps = r[je] * rscale;
         const double idps = dir ? 0.0 : (double)invd0[je];
-        if (SCHUR) {
+        // r~ from zeta_j; Gam is only used transposed
+        auto couple = [&](double zeta, double Gam, double sj) {
+            const double m = R.mm[je];
+            if (!TRANS) {   // a_y s_j zeta, a_y = (m, -m, -tc m)
+                const double f = sj * zeta;
+                if (!dir) rps -= m * f;
+                rpe += m * f;
+                rce += g.tc * m * f;
+            } else {        // Gamma b_y zeta, b_y = (g, -g, e)
+                const double f = Gam * zeta;
+                const double gj = R.gg[je];
+                if (!dir) rps -= gj * f;
+                rpe += gj * f;
+                rce -= R.ee[je] * f;
+            }
+        };
+        if (SCHUR == 2) {
+            couple(R.zeta[je] * zscale, el == 0 ? R.tabs[0].Gamma : R.tabs[1].Gamma, R.ss[je]);
+        } else if (SCHUR) {
             auto elim = [&](const auto &Tb) {
                 const int N = Tb.N;
                 const long long nn = el == 0 ? g.nea : g.nec;
@@ -477,20 +497,7 @@ __device__ inline void rad_fwd_block(const Geom &g, const RadArgs &R, const doub
                 }
                 const double sj = R.ss[je];
                 const T pivN = (T)(Tb.piv[N - 1] + Tb.Gamma * sj);
-                const double zeta = (double)(y / pivN);
-                const double m = R.mm[je];
-                if (!TRANS) {   // a_y s_j zeta, a_y = (m, -m, -tc m)
-                    const double f = sj * zeta;
-                    if (!dir) rps -= m * f;
-                    rpe += m * f;
-                    rce += g.tc * m * f;
-                } else {        // Gamma b_y zeta, b_y = (g, -g, e)
-                    const double f = Tb.Gamma * zeta;
-                    const double gj = R.gg[je];
-                    if (!dir) rps -= gj * f;
-                    rpe += gj * f;
-                    rce -= R.ee[je] * f;
-                }
+                couple((double)(y / pivN), Tb.Gamma, sj);
             };
             // the tables of the node's electrode: through a wave-uniform pointer
             // in the constant address space (scalar loads) when the whole wave
@@ -591,6 +598,134 @@ __device__ inline void rad_back_block(const Geom &g, const RadArgs &R, const dou
     else solve(R.tabs[el]);
 }
 
+// The electrode-level part of z = P^-1 (rscale r): the final level-0
+// iterates, identity on the grounded layer
+template <typename TZ>
+__device__ inline void macro_out_block(const Geom &g, const RadArgs &R, const double *r, double rscale, TZ *z,
+                                       int blk)
+{
+    const long long n = (long long)blk * kBlock + threadIdx.x;
+    if (n >= g.nnode) return;
+    z[g.off_pe + n] = (TZ)R.x0[2][g.off_pe + n];
+    z[g.off_ce + n] = (TZ)R.x0[3][g.off_ce + n];
+    const int k = (int)(n / ((long long)g.nx * g.ny));
+    const int el = node_mat(g, k);
+    if (el < 0) return;
+    const long long base = el == 0 ? 0 : g.nea;
+    const long long klo = el == 0 ? 0 : g.na + g.ns;
+    const long long je = base + n - klo * g.nx * g.ny;
+    z[je] = (TZ)(k == 0 ? r[je] * rscale : (el == 0 ? R.x0[0] : R.x0[1])[je]);
+}
+
+// The first vector r of a folded cycle at one node: zeta_j = (A_ss,j^-1
+// r_s,j)_N (FP64) and the squares of its electrode-level and particle rows
+template <int NRMAX, bool TRANS>
+__device__ inline void fold_start_node(const Geom &g, const RadialTab *tabs, const double *ss, const double *r,
+                                       double *zeta, long long n, double &sqy, double &sqs)
+{
+    const int k = (int)(n / ((long long)g.nx * g.ny));
+    const double rpe = r[g.off_pe + n], rce = r[g.off_ce + n];
+    sqy += rpe * rpe + rce * rce;
+    const int el = node_mat(g, k);
+    if (el < 0) return;
+    const long long base = el == 0 ? 0 : g.nea;
+    const long long klo = el == 0 ? 0 : g.na + g.ns;
+    const long long je = base + n - klo * g.nx * g.ny;
+    const double rps = r[je];
+    sqy += rps * rps;
+    auto elim = [&](const auto &Tb) {
+        const int N = Tb.N;
+        const long long nn = el == 0 ? g.nea : g.nec;
+        const double *rs = r + (el == 0 ? g.off_cs[0] : g.off_cs[1]) + (je - base);
+        double rv[NRMAX];
+#pragma unroll
+        for (int q = 0; q < NRMAX; q++) rv[q] = rs[(long long)(q < N ? q : N - 1) * nn];
+        double y = rv[0];
+        double sq = rv[0] * rv[0];
+#pragma unroll
+        for (int q = 1; q < NRMAX; q++) {
+            if (q < N) {
+                y = rv[q] - (TRANS ? Tb.lT[q] : Tb.l[q]) * y;
+                sq += rv[q] * rv[q];
+            }
+        }
+        sqs += sq;
+        zeta[je] = y / (Tb.piv[N - 1] + Tb.Gamma * ss[je]);
+    };
+    const int elw = __builtin_amdgcn_readfirstlane(el);
+    if (__builtin_amdgcn_ballot_w64(el != elw) == 0) elim(*(const ConstTab *)(tabs + elw));
+    else elim(tabs[el]);
+}
+
+// x_s,j = (ADD: x_s,j +) A_ss,j^-1 (gamma b_s,j - delta_j e_N), delta_j =
+// Gamma b_y . y (transposed s_j a_y . y), all in FP64
+template <int NRMAX, bool TRANS, bool ADD>
+__device__ inline void red_back_block(const Geom &g, const RadialTab *tabs, const double *gg, const double *ss,
+                                      const double *ee, const double *mm, double gamma, const double *b,
+                                      const double *y, double *x, int blk)
+{
+    const long long n = (long long)blk * kBlock + threadIdx.x;
+    if (n >= g.nnode) return;
+    const int k = (int)(n / ((long long)g.nx * g.ny));
+    const int el = node_mat(g, k);
+    if (el < 0) return;
+    const long long base = el == 0 ? 0 : g.nea;
+    const long long klo = el == 0 ? 0 : g.na + g.ns;
+    const long long je = base + n - klo * g.nx * g.ny;
+    const bool dir = (k == 0);
+    auto solve = [&](const auto &Tb) {
+        const int N = Tb.N;
+        const long long nn = el == 0 ? g.nea : g.nec;
+        const long long offs = el == 0 ? g.off_cs[0] : g.off_cs[1];
+        const double *bs = b + offs + (je - base);
+        double *xs = x + offs + (je - base);
+        const double yps = dir ? 0.0 : y[je], ype = y[g.off_pe + n], yce = y[g.off_ce + n];
+        const double sj = ss[je], m = mm[je], gj = gg[je];
+        const double delta = TRANS ? sj * (m * yps - m * ype - g.tc * m * yce)
+                                   : Tb.Gamma * (gj * yps - gj * ype + ee[je] * yce);
+        double rv[NRMAX], xo[NRMAX];
+#pragma unroll
+        for (int q = 0; q < NRMAX; q++) rv[q] = bs[(long long)(q < N ? q : N - 1) * nn];
+        if (ADD) {
+#pragma unroll
+            for (int q = 0; q < NRMAX; q++) xo[q] = xs[(long long)(q < N ? q : N - 1) * nn];
+        }
+        // forward elimination with the shared unit-lower factor; the surface
+        // entry carries -delta
+        double yv[NRMAX];
+        yv[0] = gamma * rv[0];   // N >= 3: the surface entry is not the first
+        double ylast = yv[0];
+#pragma unroll
+        for (int q = 1; q < NRMAX; q++) {
+            if (q < N) {
+                const double rq = q == N - 1 ? gamma * rv[q] - delta : gamma * rv[q];
+                yv[q] = rq - (TRANS ? Tb.lT[q] : Tb.l[q]) * yv[q - 1];
+                ylast = yv[q];
+            }
+        }
+        double zn = ylast / (Tb.piv[N - 1] + Tb.Gamma * sj);
+        double xlast = 0.0;
+        if (ADD) {
+#pragma unroll
+            for (int q = 0; q < NRMAX; q++)
+                if (q == N - 1) xlast = xo[q];
+        }
+        xs[(long long)(N - 1) * nn] = ADD ? xlast + zn : zn;
+#pragma unroll
+        for (int q = NRMAX - 2; q >= 0; q--) {
+            if (q < N - 1) {
+                zn = (yv[q] - (TRANS ? Tb.tsub[q + 1] : Tb.tsup[q]) * zn) * Tb.ipiv[q];
+                xs[(long long)q * nn] = ADD ? xo[q] + zn : zn;
+            }
+        }
+    };
+    // the electrode's table through a wave-uniform pointer (scalar loads) when
+    // the whole wave lies in one electrode, per lane otherwise
+    const int elw = __builtin_amdgcn_readfirstlane(el);
+    if (__builtin_amdgcn_ballot_w64(el != elw) == 0) solve(*(const ConstTab *)(tabs + elw));
+    else solve(tabs[el]);
+}
+
 // ---------------------------------------------------------------------------
 // The operator y = A x (or A^T x, or b - A x) for the nodes of one block,
 // with the sum of squares of what the thread writes (paper Sec. 4.1,
@@ -605,7 +740,20 @@ struct OpArgs {
     const double *om;    // omega per electrode node (Schur complement operator)
     const double *kdh;   // h * diffusion-potential coefficient per element (GEN)
     const double *dch;   // h * c_e diffusion coefficient per element (GEN)
+    ZetaArgs za;         // RED: the folded particle rows' part (zeta null: none)
 };
+
+// q of the RED forms: omega_j times the electrode-level reaction, plus s_j
+// (transposed Gamma) times the surface value zeta_j of the folded particle
+// rows, the two adding up to the reaction with the particle solved for
+template <bool TRANS>
+__device__ inline double red_reaction(const OpArgs &O, double q, long long je, double Gam, double sj, double zsc)
+{
+    q *= O.om[je];
+    if (O.za.zeta) q += (TRANS ? Gam : sj) * (O.za.zeta[je] * zsc);
+    return q;
+}
+__device__ inline double zeta_scale(const OpArgs &O) { return O.za.zeta ? *O.za.scale * *O.za.alpha : 0.0; }
 
 template <typename TX>
 __device__ inline double ldx(const TX *p) { return (double)*p; }
@@ -793,7 +941,8 @@ __device__ inline double operator_finish(const Geom &g, const OpArgs &O, long lo
             }
             if (RESID) bps = b[je];
             const OpCoupling cp = op_coupling<TRANS>(g, T, dir, m, gj, sj, ej, P.xpsc, xpe, xce, xsN);
-            const double q = RED ? cp.q * O.om[je] : cp.q, r3 = cp.r3;
+            const double q = RED ? red_reaction<TRANS>(O, cp.q, je, T.Gamma, sj, zeta_scale(O)) : cp.q;
+            const double r3 = cp.r3;
             double yps = dir ? xps : P.Kps + cp.r0 * q;
             ype += cp.r1 * q;
             yce += cp.r2 * q;
@@ -955,6 +1104,7 @@ __device__ inline void operator_tile(const Geom &g, const OpArgs &O, double *qou
                                      int CZ, OpLds &L)
 {
     const TX_T *x = (const TX_T *)O.x;
+    const double zsc = RED ? zeta_scale(O) : 0.0;
     const int TY = kBlock / TX;
     const int PX = TX + 2, PY = TY + 2;
     const int EX = TX + 1, EY = TY + 1;
@@ -1126,9 +1276,10 @@ __device__ inline void operator_tile(const Geom &g, const OpArgs &O, double *qou
                     const long long offs = el == 0 ? g.off_cs[0] : g.off_cs[1];
                     xsN = ldx(x + offs + (je - base) + (long long)(T.N - 1) * nn);
                 }
-                const OpCoupling cp = op_coupling<TRANS>(g, T, dir, O.mm[je], O.gg[je], O.ss[je],
+                const double sj = O.ss[je];
+                const OpCoupling cp = op_coupling<TRANS>(g, T, dir, O.mm[je], O.gg[je], sj,
                                                          O.ee[je], P.xpsc, P.xpe, P.xce, xsN);
-                const double q = RED ? cp.q * O.om[je] : cp.q;
+                const double q = RED ? red_reaction<TRANS>(O, cp.q, je, T.Gamma, sj, zsc) : cp.q;
                 O.y[je] = dir ? ldx(x + je) : P.Kps + cp.r0 * q;
                 ype += cp.r1 * q;
                 yce += cp.r2 * q;

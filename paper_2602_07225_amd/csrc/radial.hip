@@ -9,7 +9,7 @@
 
 namespace p4d {
 
-template <typename T, int NRMAX, bool TRANS, bool SCHUR>
+template <typename T, int NRMAX, bool TRANS, int SCHUR>
 __global__ __launch_bounds__(kBlock) void k_rad_fwd(Geom g, RadArgs R, const double *r, const double *rscale)
 {
     rad_fwd_block<T, NRMAX, TRANS, SCHUR>(g, R, r, rscale ? *rscale : 1.0, blockIdx.x);
@@ -33,10 +33,10 @@ void launch_rad_fwd(const Geom &g, const RadArgs &R, const double *r, const doub
 #define P4D_RF2(NR)                                  \
     do {                                             \
         if (schur) {                                 \
-            if (transpose) P4D_RF(NR, true, true);   \
-            else P4D_RF(NR, false, true);            \
+            if (transpose) P4D_RF(NR, true, 1);      \
+            else P4D_RF(NR, false, 1);               \
         } else {                                     \
-            P4D_RF(NR, false, false);                \
+            P4D_RF(NR, false, 0);                    \
         }                                            \
     } while (0)
     P4D_NR_SWITCH(rad_nrmax(g), P4D_RF2)
@@ -47,6 +47,27 @@ template void launch_rad_fwd<double>(const Geom &, const RadArgs &, const double
                                      int, hipStream_t);
 template void launch_rad_fwd<float>(const Geom &, const RadArgs &, const double *, const double *, int, int,
                                     hipStream_t);
+
+template <typename T, bool TRANS>
+__global__ __launch_bounds__(kBlock) void k_rad_fwd_zeta(Geom g, RadArgs R, const double *r, const double *rscale,
+                                                         const double *alpha)
+{
+    const double rs = *rscale;
+    rad_fwd_block<T, 1, TRANS, 2>(g, R, r, rs, blockIdx.x, *alpha * rs);
+}
+
+template <typename T>
+void launch_rad_fwd_zeta(const Geom &g, const RadArgs &R, const double *r, const double *rscale,
+                         const double *alpha, int transpose, hipStream_t st)
+{
+    const int nb = (int)((g.nnode + kBlock - 1) / kBlock);
+    if (transpose) hipLaunchKernelGGL((k_rad_fwd_zeta<T, true>), dim3(nb), dim3(kBlock), 0, st, g, R, r, rscale, alpha);
+    else hipLaunchKernelGGL((k_rad_fwd_zeta<T, false>), dim3(nb), dim3(kBlock), 0, st, g, R, r, rscale, alpha);
+}
+template void launch_rad_fwd_zeta<double>(const Geom &, const RadArgs &, const double *, const double *,
+                                          const double *, int, hipStream_t);
+template void launch_rad_fwd_zeta<float>(const Geom &, const RadArgs &, const double *, const double *,
+                                         const double *, int, hipStream_t);
 
 template <typename T, typename TZ, int NRMAX, bool TRANS, bool SCHUR>
 __global__ __launch_bounds__(kBlock) void k_rad_back(Geom g, RadArgs R, const double *r,
