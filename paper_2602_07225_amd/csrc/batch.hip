@@ -126,23 +126,33 @@ __global__ __launch_bounds__(kBlock) void k_bstage_radb(StageRun run)
 
 // the same stages for folded vectors: no particle column is touched, so one
 // list and one kernel serve all radial sizes
+template <typename Cell>
+__device__ inline const double *fold_basis(const Cell &C, const Geom &g, int k, bool first)
+{
+    return k == 0 ? (first ? C.b : C.V) : C.V + g.N + (long long)(k - 1) * (g.Nm + g.ne);
+}
+template <typename Cell>
+__device__ inline FoldVec fold_vec(const Cell &C, const Geom &g, int k, bool first)
+{
+    return FoldVec{C.invbeta + k, C.alpha + k, k > 0 ? fold_basis(C, g, k, first) + g.Nm : nullptr,
+                   first ? C.b : C.V, C.u0, C.u1};
+}
 template <typename T>
 __device__ inline void fold_fwd_unit(const PCell &Cm, int k, int transpose, bool first, int unit)
 {
     const Geom g = Cm.g;
     const RadArgs R = Cm.R;
-    const double *r = k == 0 ? (first ? Cm.b : Cm.V) : Cm.V + g.N + (long long)(k - 1) * g.Nm;
-    const double rs = Cm.invbeta[k];
-    const double zs = Cm.alpha[k] * rs;
-    if (transpose) rad_fwd_block<T, 1, true, 2>(g, R, r, rs, unit, zs);
-    else rad_fwd_block<T, 1, false, 2>(g, R, r, rs, unit, zs);
+    const FoldVec F = fold_vec(Cm, g, k, first);
+    const double *r = fold_basis(Cm, g, k, first);
+    if (transpose) rad_fwd_block<T, 1, true, 2>(g, R, r, *F.scale, unit, F);
+    else rad_fwd_block<T, 1, false, 2>(g, R, r, *F.scale, unit, F);
 }
 __device__ inline void fold_out_unit(const PCell &Cm, int k, bool first, int unit)
 {
     const Geom g = Cm.g;
     const RadArgs R = Cm.R;
-    const double *r = k == 0 ? (first ? Cm.b : Cm.V) : Cm.V + g.N + (long long)(k - 1) * g.Nm;
-    macro_out_block<double>(g, R, r, Cm.invbeta[k], (double *)Cm.Z + (long long)k * g.Nm, unit);
+    macro_out_block<double>(g, R, fold_basis(Cm, g, k, first), Cm.invbeta[k],
+                            (double *)Cm.Z + (long long)k * g.Nm, unit);
 }
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_bstage_fwd_fold(StageRun run)
@@ -512,10 +522,10 @@ __global__ __launch_bounds__(kBlock) void k_bop_radial(const BCell *__restrict__
     operator_radial<TX, NRMAX, TRANS>(g, O, C.qbuf, je);
 }
 
-// folded: the electrode-level rows of V_{k+1} = A Z_k
+// folded: V_{k+1} = A Z_k
 template <bool TRANS>
 __global__ __launch_bounds__(kBlock) void k_bop_tile_fold(const BCell *__restrict__ cells, int ncells,
-                                                          unsigned long long active, int k)
+                                                          unsigned long long active, unsigned long long first, int k)
 {
     __shared__ OpLds L;
     const int gb = xcd_block(blockIdx.x, gridDim.x);
@@ -525,10 +535,10 @@ __global__ __launch_bounds__(kBlock) void k_bop_tile_fold(const BCell *__restric
     const Geom g = C.g;
     OpArgs O = C.op;
     O.x = (const double *)C.Z + (long long)k * g.Nm;
-    O.y = C.V + g.N + (long long)k * g.Nm;
+    O.y = C.V + g.N + (long long)k * (g.Nm + g.ne);
     O.b = nullptr;
-    O.za = ZetaArgs{C.zeta, C.invbeta + k, C.alpha + k};
-    operator_tile<double, TRANS, true>(g, O, nullptr, gb - C.tile_blk0, C.op_tx, C.op_cz, L);
+    O.fv = fold_vec(C, g, k, (first >> c) & 1ULL);
+    operator_tile<double, TRANS, OP_FOLD>(g, O, nullptr, gb - C.tile_blk0, C.op_tx, C.op_cz, L);
 }
 
 // folded: the first vector of a cycle and its final sums
@@ -545,7 +555,7 @@ __global__ __launch_bounds__(kBlock) void k_bfold_start(const BCell *__restrict_
     const int lb = blockIdx.x - C.fs_blk0;
     double sqy = 0.0, sqs = 0.0;
     for (long long n = (long long)lb * kBlock + threadIdx.x; n < g.nnode; n += (long long)C.fs_n * kBlock)
-        fold_start_node<NRMAX, TRANS>(g, C.op.tabs, C.op.ss, r, C.zeta, n, sqy, sqs);
+        fold_start_node<NRMAX, TRANS>(g, C.op.tabs, C.op.ss, r, C.u0, C.u1, n, sqy, sqs);
     sqy = block_sum(sqy, red);
     sqs = block_sum(sqs, red);
     if (threadIdx.x == 0) {
@@ -567,20 +577,19 @@ __global__ __launch_bounds__(kBlock) void k_bfold_final(const BCell *__restrict_
 }
 
 template <int NRMAX, bool TRANS>
-__global__ __launch_bounds__(kBlock) void k_bred_back(const BCell *__restrict__ cells, int ncells,
-                                                      unsigned long long active, unsigned long long first)
+__global__ __launch_bounds__(kBlock) void k_bfold_update(const BCell *__restrict__ cells, int ncells,
+                                                         unsigned long long active, unsigned long long first)
 {
     const int c = find_cell<SEL_OP>(cells, ncells, blockIdx.x);
     const BCell C = ld(ctab(cells)[c]);
     if (!((active >> c) & 1ULL)) return;
     const Geom g = C.g;
     const OpArgs &O = C.op;
-    const int lb = blockIdx.x - C.op_blk0;
-    const double gamma = *C.gamma;
-    if ((first >> c) & 1ULL)
-        red_back_block<NRMAX, TRANS, false>(g, O.tabs, O.gg, O.ss, O.ee, O.mm, gamma, C.b, C.x, C.x, lb);
-    else
-        red_back_block<NRMAX, TRANS, true>(g, O.tabs, O.gg, O.ss, O.ee, O.mm, gamma, C.V, C.V + g.N, C.x, lb);
+    const bool f = (first >> c) & 1ULL;
+    const FoldUpdate U{O.tabs, O.gg, O.ss, O.ee, O.mm, C.omega, f ? C.b : C.V, C.V + (g.N - C.nk),
+                       (const double *)C.Z, C.y, C.alpha, C.invbeta, C.x, *C.kused, f ? 0 : 1};
+    const long long n = (long long)(blockIdx.x - C.op_blk0) * kBlock + threadIdx.x;
+    if (n < g.nnode) fold_update_node<NRMAX, TRANS>(g, U, n);
 }
 
 template <int KMAX>
@@ -597,15 +606,17 @@ __global__ __launch_bounds__(kBlock) void k_bmdot(const BCell *__restrict__ cell
     // vector q at V + q N, vector 0 at v0 (folded: vector 0 is whole)
     const double *__restrict__ V = C.V + (C.g.N - N);
     const double *__restrict__ v0 = C.fold && ((first >> c) & 1ULL) ? C.b : C.V;
+    const FoldMap M = C.fold ? fold_map(C.g) : FoldMap{};
     const double *__restrict__ w = V + (long long)(k + 1) * N;
     double acc[KMAX];
 #pragma unroll
     for (int q = 0; q < KMAX; q++) acc[q] = 0.0;
     for (long long i = (long long)lb * kBlock + threadIdx.x; i < N; i += (long long)nb * kBlock) {
         const double wi = w[i];
+        const double *p0 = v0 + fold_at(M, i);
 #pragma unroll
         for (int q = 0; q < KMAX; q++)
-            if (q < nv) acc[q] += wi * (q == 0 ? v0 : V + (long long)q * N)[i];
+            if (q < nv) acc[q] += wi * *(q == 0 ? p0 : V + (long long)q * N + i);
     }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
@@ -659,6 +670,7 @@ __global__ __launch_bounds__(kBlock) void k_borth(const BCell *__restrict__ cell
     }
     const double *__restrict__ V = C.V + (C.g.N - N);
     const double *__restrict__ v0 = C.fold && ((first >> c) & 1ULL) ? C.b : C.V;
+    const FoldMap M = C.fold ? fold_map(C.g) : FoldMap{};
     double *__restrict__ w = C.V + (C.g.N - N) + (long long)(k + 1) * N;
     double cq[KMAX];
 #pragma unroll
@@ -666,9 +678,10 @@ __global__ __launch_bounds__(kBlock) void k_borth(const BCell *__restrict__ cell
     double sq = 0.0;
     for (long long i = (long long)lb * kBlock + threadIdx.x; i < N; i += (long long)nb * kBlock) {
         double wi = w[i];
+        const double *p0 = v0 + fold_at(M, i);
 #pragma unroll
         for (int q = 0; q < KMAX; q++)
-            if (q < nv) wi -= cq[q] * (q == 0 ? v0 : V + (long long)q * N)[i];
+            if (q < nv) wi -= cq[q] * *(q == 0 ? p0 : V + (long long)q * N + i);
         w[i] = wi;
         sq += wi * wi;
     }
@@ -700,13 +713,13 @@ __global__ __launch_bounds__(kBlock) void k_bnorm_final(const BCell *__restrict_
 
 template <typename TZ, int KMAX>
 __global__ __launch_bounds__(kBlock) void k_bzy(const BCell *__restrict__ cells, int ncells,
-                                                unsigned long long active, unsigned long long first)
+                                                unsigned long long active)
 {
     const int c = find_cell<SEL_ST>(cells, ncells, blockIdx.x);
     const BCell C = ld(ctab(cells)[c]);
     if (!((active >> c) & 1ULL)) return;
     const int lb = blockIdx.x - C.st_blk0, nb = C.st_nblk;
-    const long long N = C.nk;
+    const long long N = C.g.N;
     const int nv = *C.kused;
     double yq[KMAX];
 #pragma unroll
@@ -714,19 +727,11 @@ __global__ __launch_bounds__(kBlock) void k_bzy(const BCell *__restrict__ cells,
     const TZ *__restrict__ Z = (const TZ *)C.Z;
     double *__restrict__ x = C.x;
     for (long long i = (long long)lb * kBlock + threadIdx.x; i < N; i += (long long)nb * kBlock) {
-        // folded: the first update assigns x, a later one is also kept by
-        // itself at V_1 (the particle part follows from it)
-        const bool assign = C.fold && ((first >> c) & 1ULL), keep = C.fold && !assign;
-        double xi = assign ? 0.0 : x[i], di = 0.0;
+        double xi = x[i];
 #pragma unroll
         for (int q = 0; q < KMAX; q++)
-            if (q < nv) {
-                const double zq = (double)Z[(long long)q * N + i];
-                xi += yq[q] * zq;
-                if (keep) di += yq[q] * zq;
-            }
+            if (q < nv) xi += yq[q] * (double)Z[(long long)q * N + i];
         x[i] = xi;
-        if (keep) C.V[C.g.N + i] = di;
     }
 }
 
@@ -795,13 +800,15 @@ template void launch_bop<double>(const BCell *, int, unsigned long long, int, in
 template void launch_bop<float>(const BCell *, int, unsigned long long, int, int, int, int, int, int,
                                 int, hipStream_t);
 
-void launch_bop_fold(const BCell *cells, int ncells, unsigned long long active, int k, int transpose,
-                     int nblk_tile, hipStream_t st)
+void launch_bop_fold(const BCell *cells, int ncells, unsigned long long active, unsigned long long first, int k,
+                     int transpose, int nblk_tile, hipStream_t st)
 {
     if (transpose)
-        hipLaunchKernelGGL((k_bop_tile_fold<true>), dim3(nblk_tile), dim3(kBlock), 0, st, cells, ncells, active, k);
+        hipLaunchKernelGGL((k_bop_tile_fold<true>), dim3(nblk_tile), dim3(kBlock), 0, st, cells, ncells, active,
+                           first, k);
     else
-        hipLaunchKernelGGL((k_bop_tile_fold<false>), dim3(nblk_tile), dim3(kBlock), 0, st, cells, ncells, active, k);
+        hipLaunchKernelGGL((k_bop_tile_fold<false>), dim3(nblk_tile), dim3(kBlock), 0, st, cells, ncells, active,
+                           first, k);
 }
 
 void launch_bfold_start(const BCell *cells, int ncells, unsigned long long active, unsigned long long first,
@@ -821,20 +828,20 @@ void launch_bfold_start(const BCell *cells, int ncells, unsigned long long activ
     hipLaunchKernelGGL(k_bfold_final, dim3(ncells), dim3(kBlock), 0, st, cells, active, first);
 }
 
-void launch_bred_back(const BCell *cells, int ncells, unsigned long long active, unsigned long long first,
+void launch_bfold_update(const BCell *cells, int ncells, unsigned long long active, unsigned long long first,
                       int transpose, int nblk_op, int nrmax, hipStream_t st)
 {
-#define P4D_BRB(NR)                                                                                            \
+#define P4D_BFU(NR)                                                                                            \
     do {                                                                                                       \
         if (transpose)                                                                                         \
-            hipLaunchKernelGGL((k_bred_back<NR, true>), dim3(nblk_op), dim3(kBlock), 0, st, cells, ncells, active, \
+            hipLaunchKernelGGL((k_bfold_update<NR, true>), dim3(nblk_op), dim3(kBlock), 0, st, cells, ncells, active, \
                                first);                                                                         \
         else                                                                                                   \
-            hipLaunchKernelGGL((k_bred_back<NR, false>), dim3(nblk_op), dim3(kBlock), 0, st, cells, ncells, active, \
+            hipLaunchKernelGGL((k_bfold_update<NR, false>), dim3(nblk_op), dim3(kBlock), 0, st, cells, ncells, active, \
                                first);                                                                         \
     } while (0)
-    P4D_NR_SWITCH(nrmax, P4D_BRB)
-#undef P4D_BRB
+    P4D_NR_SWITCH(nrmax, P4D_BFU)
+#undef P4D_BFU
 }
 
 void launch_bmdot(const BCell *cells, int ncells, unsigned long long active, unsigned long long first, int k,
@@ -873,11 +880,11 @@ void launch_bnorm_final(const BCell *cells, int ncells, unsigned long long activ
 }
 
 template <typename TZ>
-void launch_bzy(const BCell *cells, int ncells, unsigned long long active, unsigned long long first, int kmax,
-                int nblk_st, hipStream_t st)
+void launch_bzy(const BCell *cells, int ncells, unsigned long long active, int kmax, int nblk_st,
+                hipStream_t st)
 {
 #define P4D_BZ(K) \
-    hipLaunchKernelGGL((k_bzy<TZ, K>), dim3(nblk_st), dim3(kBlock), 0, st, cells, ncells, active, first)
+    hipLaunchKernelGGL((k_bzy<TZ, K>), dim3(nblk_st), dim3(kBlock), 0, st, cells, ncells, active)
     if (kmax <= 4) P4D_BZ(4);
     else if (kmax <= 8) P4D_BZ(8);
     else if (kmax <= 16) P4D_BZ(16);
@@ -885,7 +892,7 @@ void launch_bzy(const BCell *cells, int ncells, unsigned long long active, unsig
     else P4D_BZ(64);
 #undef P4D_BZ
 }
-template void launch_bzy<double>(const BCell *, int, unsigned long long, unsigned long long, int, int, hipStream_t);
-template void launch_bzy<float>(const BCell *, int, unsigned long long, unsigned long long, int, int, hipStream_t);
+template void launch_bzy<double>(const BCell *, int, unsigned long long, int, int, hipStream_t);
+template void launch_bzy<float>(const BCell *, int, unsigned long long, int, int, hipStream_t);
 
 }  // namespace p4d

@@ -19,7 +19,7 @@ int stream_blocks(long long n)
 template <int KMAX>
 __global__ __launch_bounds__(kBlock) void k_mdot(long long n, const double *__restrict__ w,
                                                  const double *__restrict__ V,
-                                                 const double *__restrict__ v0, long long ldv,
+                                                 const double *__restrict__ v0, FoldMap M, long long ldv,
                                                  int nv, double *__restrict__ partial)
 {
     __shared__ double red[4][KMAX];
@@ -29,9 +29,10 @@ __global__ __launch_bounds__(kBlock) void k_mdot(long long n, const double *__re
     const long long stride = (long long)gridDim.x * kBlock;
     for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) {
         const double wi = w[i];
+        const double *p0 = v0 + fold_at(M, i);
 #pragma unroll
         for (int q = 0; q < KMAX; q++)
-            if (q < nv) acc[q] += wi * (q == 0 ? v0 : V + (long long)q * ldv)[i];
+            if (q < nv) acc[q] += wi * *(q == 0 ? p0 : V + (long long)q * ldv + i);
     }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
@@ -49,11 +50,11 @@ __global__ __launch_bounds__(kBlock) void k_mdot(long long n, const double *__re
             (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
 }
 
-void launch_mdot(long long n, const double *w, const double *V, const double *v0, long long ldv, int nv,
-                 double *partial, int nblk, hipStream_t st)
+void launch_mdot(long long n, const double *w, const double *V, const double *v0, const FoldMap &M, long long ldv,
+                 int nv, double *partial, int nblk, hipStream_t st)
 {
 #define P4D_MD(K) \
-    hipLaunchKernelGGL((k_mdot<K>), dim3(nblk), dim3(kBlock), 0, st, n, w, V, v0, ldv, nv, partial)
+    hipLaunchKernelGGL((k_mdot<K>), dim3(nblk), dim3(kBlock), 0, st, n, w, V, v0, M, ldv, nv, partial)
     if (nv <= 4) P4D_MD(4);
     else if (nv <= 8) P4D_MD(8);
     else if (nv <= 16) P4D_MD(16);
@@ -91,7 +92,7 @@ void launch_mdot_final(int nv, const double *partial, int nblk, const double *in
 template <int KMAX>
 __global__ __launch_bounds__(kBlock) void k_orth(long long n, double *__restrict__ w,
                                                  const double *__restrict__ V,
-                                                 const double *__restrict__ v0, long long ldv,
+                                                 const double *__restrict__ v0, FoldMap M, long long ldv,
                                                  int nv, const double *__restrict__ c,
                                                  double *__restrict__ partial, Fold F)
 {
@@ -108,9 +109,10 @@ __global__ __launch_bounds__(kBlock) void k_orth(long long n, double *__restrict
     const long long stride = (long long)gridDim.x * kBlock;
     for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) {
         double wi = w[i];
+        const double *p0 = v0 + fold_at(M, i);
 #pragma unroll
         for (int q = 0; q < KMAX; q++)
-            if (q < nv) wi -= cq[q] * (q == 0 ? v0 : V + (long long)q * ldv)[i];
+            if (q < nv) wi -= cq[q] * *(q == 0 ? p0 : V + (long long)q * ldv + i);
         w[i] = wi;
         sq += wi * wi;
     }
@@ -118,11 +120,11 @@ __global__ __launch_bounds__(kBlock) void k_orth(long long n, double *__restrict
     if (threadIdx.x == 0) partial[blockIdx.x] = s;
 }
 
-void launch_orth(long long n, double *w, const double *V, const double *v0, long long ldv, int nv,
+void launch_orth(long long n, double *w, const double *V, const double *v0, const FoldMap &M, long long ldv, int nv,
                  const double *c, double *partial, int nblk, const Fold &F, hipStream_t st)
 {
 #define P4D_OR(K) \
-    hipLaunchKernelGGL((k_orth<K>), dim3(nblk), dim3(kBlock), 0, st, n, w, V, v0, ldv, nv, c, partial, F)
+    hipLaunchKernelGGL((k_orth<K>), dim3(nblk), dim3(kBlock), 0, st, n, w, V, v0, M, ldv, nv, c, partial, F)
     if (nv <= 4) P4D_OR(4);
     else if (nv <= 8) P4D_OR(8);
     else if (nv <= 16) P4D_OR(16);

@@ -127,117 +127,273 @@ void launch_coarse(const CoarseBatch<T> &cb, hipStream_t st)
 template void launch_coarse<double>(const CoarseBatch<double> &, hipStream_t);
 template void launch_coarse<float>(const CoarseBatch<float> &, hipStream_t);
 
-// Tail of the V-cycle, one 1024-thread workgroup per box (see TailArgs).  The
-// per-stage device functions run here on LDS arrays through generic
-// pointers: node n of a stage is base + threadIdx.x over bases stepping by
-// the workgroup size, which is what smooth_block / restrict_block /
-// prolong_block compute from a block index base / kBlock.
-template <typename T>
+// the value, of which the compiler knows nothing
+__device__ inline int opaque(int v)
+{
+    __asm__ volatile("" : "+v"(v));
+    return v;
+}
+
+// Tail of the V-cycle, one 512-thread workgroup per box (see TailArgs).  A
+// stage of these levels as a launch of its own costs 4-5 us, nearly all of it
+// the launch and one dependent memory latency; here it is one pass over LDS
+// and two barriers.  The upper level's couplings stay in registers, so that
+// their sizes are what they leave room for: two nodes of the upper and one of
+// the lower per thread (162 of the 256 VGPRs that 8 waves have in FP64; one
+// and one with 16 waves and 128 spilled 82;
+// four in FP32 took five times as long).  The iterates have a one-node halo in LDS, so that a neighbour is one
+// uniform offset away.
+// Measured: levels of 325 and 63 nodes 18.7 -> 10.9 us (the earlier kernel read
+// the couplings from LDS); levels of 729, 125 and 27 nodes 21.5 us, where the
+// first took six launches (27 us) before the tail of the others (17 us).
+// Indices are taken through opaque(): what a stage derives from them is formed
+// anew there, not kept in registers across the others.
+// The stages' code is one loop per level (steps 2..deg, residual and coarse
+// correction, steps 1..deg): laid out one after the other the kernel was 6000
+// instructions, which a launch fetched anew each time.
+template <typename T, int R>
 __global__ __launch_bounds__(kTailThreads) void k_tail(TailBatch<T> tb)
 {
-    __shared__ __align__(16) char lds[kTailLds];
+    __shared__ __align__(16) double lds[kTailLds / 8];
     if ((int)blockIdx.x >= tb.nbox) return;
-    const TailArgs<T> &A = tb.a[blockIdx.x];
-    const int n = A.n, nc = A.nc, deg = tb.deg;
-    // doubles: x1 and the coarse inverse first (filled together), then the
-    // second iterate buffer, the coarse solution and the partial sums; then
-    // the stencil, inverse diagonal and right-hand side (filled together),
-    // direction, residual and coarse right-hand side in T
-    double *xa = (double *)lds;
-    double *Ainv = xa + n;             // [nc][nc] coarse inverse
-    double *xb = Ainv + nc * nc;
-    double *xc = xb + n;
-    double *part = xc + nc;            // [4][nc] partial sums of the coarse solve
-    T *S = (T *)(part + 4 * nc);
-    T *invd = S + 14 * n;
-    T *b = invd + n;
-    T *d = b + n;
-    T *r = d + n;
-    T *bc = r + n;
-    {   // every global load is issued, kU per thread and array group, before
-        // any of them is stored to LDS (a load-store loop waits for each)
+    // the box's arguments where the launch left them, through the constant
+    // address space: scalar loads, no private copy of the whole batch
+    typedef __attribute__((address_space(4))) const TailBatch<T> Batch;
+    typedef __attribute__((address_space(4))) const TailArgs<T> Args;
+    typedef __attribute__((address_space(4))) const TailLevel<T> Lev;
+    Args &A = ((Batch *)__builtin_amdgcn_kernarg_segment_ptr())->a[blockIdx.x];
+    Lev &E = A.top, &F = A.sub;
+    // (the pointers there are to global memory: said so, the loads are no flat
+    // ones)
+    typedef __attribute__((address_space(1))) const T *GT;
+    typedef __attribute__((address_space(1))) const double *GD;
+    const GT ES = (GT)E.S, Eb = (GT)E.b, Eid = (GT)E.invd, FS = (GT)F.S, Fid = (GT)F.invd;
+    const GD Ax1 = (GD)A.x1, AA = (GD)A.Ainv;
+    const int deg = tb.deg, t = threadIdx.x;
+    const int n = E.n, m = F.n, nc = A.nc;
+    const int px = E.nx + 2, pxy = px * (E.ny + 2), P = pxy * (E.nz + 2);
+    const int qx = F.nx + 2, qxy = qx * (F.ny + 2), Q = m > 0 ? qxy * (F.nz + 2) : 0;
+    typedef __attribute__((address_space(3))) double LD;
+    LD *x = (LD *)lds, *y = x + P;          // iterates of both levels, with halo
+    LD *Ainv = y + Q;                       // [nc][nc]
+    LD *r = Ainv + nc * nc, *rs = r + n;
+    LD *bc = rs + m, *xc = bc + nc, *part = xc + nc;   // part: [4][nc]
+    // nodes t + 512 q of the upper level, node t of the lower one: couplings,
+    // place in the halo layout, right-hand side, inverse diagonal, direction
+    T sv[R][27], sf[27];
+    double b[R], id[R], x1[R];
+    T d[R], dF = T(0);
+    int p[R], has[R], hasF = 0;
+    // every global load is issued before the first barrier
+    auto fetch = [&](GT S, int nn, int nx, int ny, int nz, int i, int j, int k, T (&c)[27]) {
+        const NbMask M(i, j, k, nx, ny, nz);
+        const int nl = nx * ny * nz;
+        int hm = 0;
+#pragma unroll
+        for (int o = 0; o < 27; o++) {
+            const int h = M.has(o), off = (o % 3 - 1) + nx * ((o / 3) % 3 - 1 + ny * (o / 9 - 1));
+            c[o] = S[o >= 13 ? (o - 13) * nl + nn : (13 - o) * nl + nn + (off & -h)];
+            hm |= h << o;
+        }
+        return hm;
+    };
+    auto drop = [&](int hm, T (&c)[27]) {   // no coupling to a missing neighbour
+#pragma unroll
+        for (int o = 0; o < 27; o++) {
+            // (taken whole first: a load that only one side of the select
+            // needs would be moved behind a branch, one wait for each)
+            __asm__ volatile("" : "+v"(c[o]));
+            c[o] = (hm >> o) & 1 ? c[o] : T(0);
+        }
+    };
+#pragma unroll
+    for (int q = 0; q < R; q++) {
+        const int nn = t + q * kTailThreads < n ? t + q * kTailThreads : 0;
+        const int i = nn % E.nx, u = nn / E.nx, j = u % E.ny, k = u / E.ny;
+        p[q] = (i + 1) + px * (j + 1) + pxy * (k + 1);
+        has[q] = fetch(ES, nn, E.nx, E.ny, E.nz, i, j, k, sv[q]);
+        b[q] = (double)Eb[nn];
+        id[q] = (double)Eid[nn];
+        x1[q] = Ax1[nn];
+        d[q] = T(0);
+    }
+    const bool ownF = t < m;
+    int pF = 0;
+    double idF = 0.0, bF = 0.0;
+    if (ownF) {
+        const int iF = t % F.nx, jF = t / F.nx % F.ny, kF = t / F.nx / F.ny;
+        pF = (iF + 1) + qx * (jF + 1) + qxy * (kF + 1);
+        hasF = fetch(FS, t, F.nx, F.ny, F.nz, iF, jF, kF, sf);
+        idF = (double)Fid[t];
+    }
+    for (int q = t; q < P + Q; q += kTailThreads) lds[q] = 0.0;
+    {   // the coarse inverse: kU loads per thread are issued before any is
+        // stored (a load-store loop waits for each); clamped indices, so that
+        // the loads need no branch
         constexpr int kU = 8;
-        const int cT = 16 * n, cD = n + nc * nc;
-        const int cmax = cT > cD ? cT : cD;
-        for (int base = 0; base < cmax; base += kU * kTailThreads) {
-            T vt[kU];
+        const int cD = nc * nc;
+        for (int base = 0; base < cD; base += kU * kTailThreads) {
             double vd[kU];
 #pragma unroll
             for (int u = 0; u < kU; u++) {
-                // indexes clamped into range and sources chosen by select, so
-                // that the loads are issued without branches (stored only if
-                // q is in range)
-                const int q = base + u * kTailThreads + (int)threadIdx.x;
-                const int qt = q < cT ? q : cT - 1, qd = q < cD ? q : cD - 1;
-                const T *pt = qt < 14 * n ? A.S + qt : (qt < 15 * n ? A.invd + (qt - 14 * n) : A.b + (qt - 15 * n));
-                const double *pd = qd < n ? A.x1 + qd : A.Ainv + (qd - n);
-                vt[u] = *pt;
-                vd[u] = *pd;
+                const int q = base + u * kTailThreads + t;
+                vd[u] = AA[q < cD ? q : 0];
             }
 #pragma unroll
             for (int u = 0; u < kU; u++) {
-                const int q = base + u * kTailThreads + (int)threadIdx.x;
-                if (q < cT) S[q] = vt[u];
-                if (q < cD) xa[q] = vd[u];
+                const int q = base + u * kTailThreads + t;
+                if (q < cD) Ainv[q] = vd[u];
             }
         }
     }
     __syncthreads();
-    LevelArgs<T> L{};
-    L.nx = A.nx; L.ny = A.ny; L.nz = A.nz; L.n = n;
-    L.S = S; L.invd = invd; L.b = b; L.din = d;
-    int cur = 0;   // 0: the iterate is in xa
-    auto smooth = [&](int t, bool post) {
-        L.xin = cur ? xb : xa;
-        L.xout = cur ? xa : xb;
-        L.c1 = A.c1[t];
-        L.c2 = A.c2[t];
-        // (first pre-smoothing step from x = 0: its direction is x itself)
-        L.din_x = (!post && t == 2) ? 1 : 0;
-        L.dout = t < deg ? d : nullptr;
-        L.rout = nullptr;
-        for (int base = 0; base < n; base += kTailThreads) smooth_block<T, false>(L, base / kBlock);
-        __syncthreads();
-        cur ^= 1;
-    };
-    for (int t = 2; t <= deg; t++) smooth(t, false);
-    L.xin = cur ? xb : xa;
-    L.rout = r;
-    for (int base = 0; base < n; base += kTailThreads) smooth_block<T, true>(L, base / kBlock);
-    __syncthreads();
-    TransferArgs<T> P{};
-    P.fx = A.nx; P.fy = A.ny; P.fz = A.nz;
-    P.cx = A.cx; P.cy = A.cy; P.cz = A.cz;
-    P.rf = r;
-    P.bc = bc;
-    P.xc1 = nullptr;
-    for (int base = 0; base < nc; base += kTailThreads) restrict_block<T>(P, base / kBlock);
-    __syncthreads();
-    // x_c = Ainv b_c with the per-stage coarse kernel's summation: four
-    // partial sums over the columns c = w (mod 4), ascending, then paired
-    for (int q = threadIdx.x; q < 4 * nc; q += kTailThreads) {
-        const int w = q / nc, row = q - w * nc;
-        double acc = 0.0;
-        for (int c = w; c < nc; c += 4) acc += Ainv[c * nc + row] * (double)bc[c];
-        part[w * nc + row] = acc;
+#pragma unroll
+    for (int q = 0; q < R; q++) {
+        if (t + q * kTailThreads < n) x[p[q]] = x1[q];
+        drop(has[q], sv[q]);
     }
+    if (m > 0) drop(hasF, sf);
     __syncthreads();
-    for (int q = threadIdx.x; q < nc; q += kTailThreads)
-        xc[q] = (part[q] + part[nc + q]) + (part[2 * nc + q] + part[3 * nc + q]);
-    __syncthreads();
-    P.xc = xc;
-    P.xf = cur ? xb : xa;
-    for (int base = 0; base < n; base += kTailThreads) prolong_block<T>(P, base / kBlock);
-    __syncthreads();
-    for (int t = 1; t <= deg; t++) smooth(t, true);
-    const double *xf = cur ? xb : xa;
-    for (int q = threadIdx.x; q < n; q += kTailThreads) A.xout[q] = xf[q];
+    // stencil_row on the halo layout for nodes at[0..K) at once, a plane of
+    // neighbours at a time (the scheduling barrier keeps the next plane's
+    // values out of registers)
+    auto rows = [&](const auto &c, const LD *v, const auto &place, auto &Sx, int sy, int sz) {
+        constexpr int K = sizeof(Sx) / sizeof(double);
+        double vc[K];
+        int at[K];
+#pragma unroll
+        for (int q = 0; q < K; q++) {
+            at[q] = opaque(place[q]);
+            vc[q] = v[at[q]];
+            Sx[q] = (double)c[q][13] * vc[q];
+        }
+#pragma unroll
+        for (int z = 0; z < 3; z++) {
+            double xv[K][9];
+#pragma unroll
+            for (int o = 0; o < 9; o++)
+#pragma unroll
+                for (int q = 0; q < K; q++) xv[q][o] = v[at[q] + (o % 3 - 1) + sy * (o / 3 - 1) + sz * (z - 1)];
+#pragma unroll
+            for (int o = 0; o < 9; o++)
+#pragma unroll
+                for (int q = 0; q < K; q++)
+                    if (9 * z + o != 13) Sx[q] += (double)c[q][9 * z + o] * (xv[q][o] - vc[q]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // (places of the second node past the level's end: the first node's)
+#pragma unroll
+    for (int q = 1; q < R; q++)
+        if (t + q * kTailThreads >= n) p[q] = p[0];
+    // b_c of the coarsest level by the threads t < nc, from the residual v of
+    // the level above; its dense solve x_c = Ainv b_c with the per-stage
+    // coarse kernel's summation: four partial sums over the columns c = w (mod
+    // 4), ascending, then paired
+    auto coarsest = [&](int fx, int fy, int fz, const LD *v) {
+        if (t < nc) bc[t] = (double)(T)restrict_value(fx, fy, fz, A.cx, A.cy, A.cz, opaque(t), v);
+        __syncthreads();
+        for (int q = t; q < 4 * nc; q += kTailThreads) {
+            const int w = q / nc, rw = q - w * nc;
+            double acc = 0.0;
+#pragma unroll 4
+            for (int c = w; c < nc; c += 4) acc += Ainv[c * nc + rw] * bc[c];
+            part[q] = acc;
+        }
+        __syncthreads();
+        if (t < nc) xc[t] = (part[t] + part[nc + t]) + (part[2 * nc + t] + part[3 * nc + t]);
+        __syncthreads();
+    };
+    // the lower level's cycle: its right-hand side from r, its iterate to y
+    auto lower = [&]() {
+        if (ownF) {
+            const T bt = (T)restrict_value(E.nx, E.ny, E.nz, F.nx, F.ny, F.nz, opaque(t), r);
+            bF = (double)bt;
+            y[pF] = F.c2[1] * idF * bF;
+        }
+        __syncthreads();
+        T(&c1)[1][27] = *(T(*)[1][27])&sf;
+        const int at[1] = {pF};
+#pragma unroll 1
+        for (int s = 2, post = 0; s <= deg || !post; s++) {
+            double Sx[1];
+            rows(c1, y, at, Sx, qx, qxy);
+            if (!post && s > deg) {
+                if (ownF) rs[t] = (double)(T)(bF - Sx[0]);
+                __syncthreads();
+                coarsest(F.nx, F.ny, F.nz, rs);
+                const int nn = opaque(t), u = nn / F.nx;
+                if (ownF)
+                    y[pF] += prolong_value(F.nx, F.ny, F.nz, false, nn % F.nx, u % F.ny, u / F.ny, xc, A.cx, A.cx * A.cy);
+                __syncthreads();
+                post = 1;
+                s = 0;
+                continue;
+            }
+            const double c = y[pF];
+            // (after the first step from x = 0 the direction was x itself)
+            const double dn = cheb_dir(F.c1[s], F.c2[s], idF, bF - Sx[0], !post && s == 2 ? c : (double)dF);
+            dF = (T)dn;
+            __syncthreads();
+            if (ownF) y[pF] = c + dn;
+            __syncthreads();
+        }
+    };
+#pragma unroll 1
+    for (int s = 2, post = 0; s <= deg || !post; s++) {
+        double Sx[R];
+        rows(sv, x, p, Sx, px, pxy);
+        if (!post && s > deg) {
+#pragma unroll
+            for (int q = 0; q < R; q++)
+                if (t + q * kTailThreads < n) r[t + q * kTailThreads] = (double)(T)(b[q] - Sx[q]);
+            __syncthreads();
+            if (m > 0) lower();
+            else coarsest(E.nx, E.ny, E.nz, r);
+            // the level below: the lower level from its first node on in the
+            // halo layout, or the coarsest
+            const LD *xb = m > 0 ? y + 1 + qx + qxy : xc;
+            const int sy = m > 0 ? qx : A.cx, sz = m > 0 ? qxy : A.cx * A.cy;
+#pragma unroll
+            for (int q = 0; q < R; q++) {
+                const int nn = opaque(t + q * kTailThreads), u = nn / E.nx;
+                if (nn < n)
+                    x[p[q]] += prolong_value(E.nx, E.ny, E.nz, false, nn % E.nx, u % E.ny, u / E.ny, xb, sy, sz);
+            }
+            __syncthreads();
+            post = 1;
+            s = 0;
+            continue;
+        }
+        double a[R];
+#pragma unroll
+        for (int q = 0; q < R; q++) {
+            const double c = x[p[q]];
+            const double dn = cheb_dir(E.c1[s], E.c2[s], id[q], b[q] - Sx[q], !post && s == 2 ? c : (double)d[q]);
+            a[q] = c + dn;
+            d[q] = (T)dn;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < R; q++)
+            if (t + q * kTailThreads < n) x[p[q]] = a[q];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int q = 0; q < R; q++)
+        if (t + q * kTailThreads < n)
+            ((__attribute__((address_space(1))) double *)A.xout)[t + q * kTailThreads] = x[p[q]];
 }
 
 template <typename T>
 void launch_tail(const TailBatch<T> &tb, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_tail<T>), dim3(tb.nbox), dim3(kTailThreads), 0, st, tb);
+    int nmax = 0;
+    for (int b = 0; b < tb.nbox; b++) nmax = tb.a[b].top.n > nmax ? tb.a[b].top.n : nmax;
+    if (nmax <= kTailThreads)
+        hipLaunchKernelGGL((k_tail<T, 1>), dim3(tb.nbox), dim3(kTailThreads), 0, st, tb);
+    else
+        hipLaunchKernelGGL((k_tail<T, kTailNodes>), dim3(tb.nbox), dim3(kTailThreads), 0, st, tb);
 }
 template void launch_tail<double>(const TailBatch<double> &, hipStream_t);
 template void launch_tail<float>(const TailBatch<float> &, hipStream_t);

@@ -43,7 +43,7 @@ template <typename TX, bool TRANS>
 __global__ __launch_bounds__(kBlock) void k_operator_schur(Geom g, OpArgs O, int TXn, int CZ)
 {
     __shared__ OpLds L;
-    operator_tile<TX, TRANS, true>(g, O, nullptr, xcd_block(blockIdx.x, gridDim.x), TXn, CZ, L);
+    operator_tile<TX, TRANS, OP_RED>(g, O, nullptr, xcd_block(blockIdx.x, gridDim.x), TXn, CZ, L);
 }
 
 template <typename TX, int NRMAX, bool TRANS>
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(kBlock) void k_operator_schur_gen(Geom g, OpArgs O)
 {
     const int lb = xcd_block(blockIdx.x, gridDim.x);
     const long long n = (long long)lb * kBlock + threadIdx.x;
-    if (n < g.nnode) operator_node<TX, 1, TRANS, false, true, true>(g, O, n);
+    if (n < g.nnode) operator_node<TX, 1, TRANS, false, true, OP_RED>(g, O, n);
 }
 
 // w = S y (or S^T y), S = A_yy - A_ys A_ss^-1 A_sy: y and w hold the
@@ -155,10 +155,9 @@ template <typename TX>
 void launch_operator_schur(const Geom &g, const RadialTab *tabs, const double *sigh,
                            const double *kaph, const double *gg, const double *ss, const double *ee,
                            const double *mm, const double *om, const TX *y, double *w, int transpose,
-                           int tile_tx, int tile_cz, const double *kdh, const double *dch,
-                           const ZetaArgs &za, hipStream_t st)
+                           int tile_tx, int tile_cz, const double *kdh, const double *dch, hipStream_t st)
 {
-    OpArgs O{tabs, sigh, kaph, gg, ss, ee, mm, y, w, nullptr, om, kdh, dch, za};
+    OpArgs O{tabs, sigh, kaph, gg, ss, ee, mm, y, w, nullptr, om, kdh, dch};
     if (kdh && dch) {
         const int nb = operator_blocks(g);
         if (transpose)
@@ -179,12 +178,47 @@ template void launch_operator_schur<double>(const Geom &, const RadialTab *, con
                                             const double *, const double *, const double *,
                                             const double *, const double *, const double *,
                                             const double *, double *, int, int, int, const double *,
-                                            const double *, const ZetaArgs &, hipStream_t);
+                                            const double *, hipStream_t);
 template void launch_operator_schur<float>(const Geom &, const RadialTab *, const double *,
                                            const double *, const double *, const double *,
                                            const double *, const double *, const double *,
                                            const float *, double *, int, int, int, const double *,
-                                           const double *, const ZetaArgs &, hipStream_t);
+                                           const double *, hipStream_t);
+
+// A on the direction of a folded vector: by tiles, or one thread per node with
+// the separate element arrays
+template <bool TRANS>
+__global__ __launch_bounds__(kBlock) void k_operator_fold(Geom g, OpArgs O, int TXn, int CZ)
+{
+    __shared__ OpLds L;
+    operator_tile<double, TRANS, OP_FOLD>(g, O, nullptr, xcd_block(blockIdx.x, gridDim.x), TXn, CZ, L);
+}
+template <bool TRANS>
+__global__ __launch_bounds__(kBlock) void k_operator_fold_gen(Geom g, OpArgs O)
+{
+    const int lb = xcd_block(blockIdx.x, gridDim.x);
+    const long long n = (long long)lb * kBlock + threadIdx.x;
+    if (n < g.nnode) operator_node<double, 1, TRANS, false, true, OP_FOLD>(g, O, n);
+}
+
+void launch_operator_fold(const Geom &g, const RadialTab *tabs, const double *sigh, const double *kaph,
+                          const double *gg, const double *ss, const double *ee, const double *mm, const double *om,
+                          const FoldVec &F, const double *y, double *w, int transpose, int tile_tx, int tile_cz,
+                          const double *kdh, const double *dch, hipStream_t st)
+{
+    OpArgs O{tabs, sigh, kaph, gg, ss, ee, mm, y, w, nullptr, om, kdh, dch, F};
+    if (kdh && dch) {
+        const int nb = operator_blocks(g);
+        if (transpose) hipLaunchKernelGGL((k_operator_fold_gen<true>), dim3(nb), dim3(kBlock), 0, st, g, O);
+        else hipLaunchKernelGGL((k_operator_fold_gen<false>), dim3(nb), dim3(kBlock), 0, st, g, O);
+        return;
+    }
+    const int nt = operator_tiles(g, tile_tx, tile_cz);
+    if (transpose)
+        hipLaunchKernelGGL((k_operator_fold<true>), dim3(nt), dim3(kBlock), 0, st, g, O, tile_tx, tile_cz);
+    else
+        hipLaunchKernelGGL((k_operator_fold<false>), dim3(nt), dim3(kBlock), 0, st, g, O, tile_tx, tile_cz);
+}
 
 // ---------------------------------------------------------------------------
 // Gradients of J = w.x:  dJ/dp = -lambda^T (dA/dp) x.

@@ -569,18 +569,26 @@ static void apply_op(p4d_ctx *c, int transpose, const TX *x, double *y, const do
                         c->general ? c->kdh : nullptr, c->general ? c->dch : nullptr, st);
 }
 
-// w = S y (S^T y) over the electrode-level unknowns; with za, the
-// electrode-level rows of A z for a folded vector
+// w = S y (S^T y) over the electrode-level unknowns
 template <typename TX>
-static void apply_op_schur(p4d_ctx *c, int transpose, const TX *y, double *w, hipStream_t st,
-                           const ZetaArgs &za = ZetaArgs{})
+static void apply_op_schur(p4d_ctx *c, int transpose, const TX *y, double *w, hipStream_t st)
 {
     const Geom &g = c->g;
     const double bytes = (double)(sizeof(TX) + 8) * g.Nm + 16.0 * g.nelem + 40.0 * g.ne;
     ProfScope ps(c->prof, P4D_K_OPERATOR, bytes, st);
     launch_operator_schur<TX>(g, c->tabs, c->sigh, c->kaph, c->gg, c->ss, c->ee, c->mm, c->oms, y, w,
                               transpose, c->op_tx, c->op_cz, c->general ? c->kdh : nullptr,
-                              c->general ? c->dch : nullptr, za, st);
+                              c->general ? c->dch : nullptr, st);
+}
+
+// the folded form of w = A z for z = P^-1 of the folded vector F, y its
+// electrode-level rows
+static void apply_op_fold(p4d_ctx *c, int transpose, const FoldVec &F, const double *y, double *w, hipStream_t st)
+{
+    const Geom &g = c->g;
+    ProfScope ps(c->prof, P4D_K_OPERATOR, 16.0 * g.Nm + 16.0 * g.nelem + 80.0 * g.ne, st);
+    launch_operator_fold(g, c->tabs, c->sigh, c->kaph, c->gg, c->ss, c->ee, c->mm, c->omega, F, y, w, transpose,
+                         c->op_tx, c->op_cz, c->general ? c->kdh : nullptr, c->general ? c->dch : nullptr, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -612,6 +620,7 @@ ChebCoef cheb_coef(double lmax, int deg)
 template <typename T>
 struct VState {
     int xcur[4][kMaxLevels];   // 0: xa, 1: xb holds the current iterate
+    TailBatch<T> tb;           // boxes whose tail kernel is still to be launched
 };
 
 static double *lvx(Level &L, int which) { return (double *)(which ? L.xb : L.xa); }
@@ -763,48 +772,65 @@ static void vcycle_level(p4d_ctx *c, VState<T> &vs, int l, hipStream_t st)
     if (!na) return;
     const int deg = c->pc.cheb_degree;
     if (l >= 1 && !c->rec) {
-        // boxes whose level l is their last smoothed level and fits the
-        // LDS of one workgroup run the rest of their cycle in the tail kernel
-        TailBatch<T> tb{};
+        // boxes whose levels from l down are one or two smoothed levels that
+        // fit the LDS of one workgroup run the rest of their cycle in the tail
+        // kernel
+        TailBatch<T> &tb = vs.tb;
         tb.deg = deg;
         int rest[4], nr = 0, tmask = 0;
         for (int q = 0; q < na; q++) {
             Box &B = c->box[act[q]];
-            const Level &F = B.lev[l], &Cl = B.lev[l + 1];
-            if (B.nlev - 2 != l || tail_lds_bytes<T>(F.n, Cl.n) > kTailLds) {
+            Level &E = B.lev[l];
+            const int below = B.nlev - 2 - l;   // smoothed levels below l
+            Level *F = below == 1 ? &B.lev[l + 1] : nullptr;
+            const Level &Cl = B.lev[B.nlev - 1];
+            if (below > 1 || !tail_fits(E.nx, E.ny, E.nz, F ? F->nx : 0, F ? F->ny : 0, F ? F->nz : 0, Cl.n)) {
                 rest[nr++] = act[q];
                 continue;
             }
             TailArgs<T> &A = tb.a[tb.nbox++];
-            A.nx = F.nx; A.ny = F.ny; A.nz = F.nz; A.n = F.n;
+            A = TailArgs<T>{};
+            auto level = [&](TailLevel<T> &t, const Level &L) {
+                t.nx = L.nx; t.ny = L.ny; t.nz = L.nz; t.n = L.n;
+                t.S = (const T *)L.S;
+                t.invd = (const T *)L.invd;
+                t.b = (const T *)L.b;
+                const ChebCoef C = cheb_coef(L.lmax, deg);
+                for (int s = 0; s < 5; s++) {
+                    t.c1[s] = C.c1[s];
+                    t.c2[s] = C.c2[s];
+                }
+            };
+            level(A.top, E);
+            if (F) level(A.sub, *F);
             A.cx = Cl.nx; A.cy = Cl.ny; A.cz = Cl.nz; A.nc = Cl.n;
-            A.S = (const T *)F.S;
-            A.invd = (const T *)F.invd;
-            A.b = (const T *)F.b;
-            A.x1 = lvx(const_cast<Level &>(F), vs.xcur[act[q]][l]);
+            A.x1 = lvx(E, vs.xcur[act[q]][l]);
             // the per-stage schedule flips the iterate buffer once per
             // smoothing step: deg - 1 before and deg after the correction
             const int fin = (vs.xcur[act[q]][l] + 2 * deg - 1) & 1;
-            A.xout = lvx(const_cast<Level &>(F), fin);
+            A.xout = lvx(E, fin);
             vs.xcur[act[q]][l] = fin;
             A.Ainv = Cl.Ainv;
-            const ChebCoef C = cheb_coef(F.lmax, deg);
-            for (int t = 0; t < 5; t++) {
-                A.c1[t] = C.c1[t];
-                A.c2[t] = C.c2[t];
-            }
             tmask |= 1 << act[q];
         }
-        if (tb.nbox) launch_tail<T>(tb, st);
-        if (!nr) return;
-        // the other boxes continue level by level; the tail's boxes sit out
-        // the coarser levels
+        // the other boxes continue level by level, the tail's boxes sit out the
+        // coarser levels; one launch runs the tails of all boxes, also of
+        // those that enter it at different levels, once no box descends
+        auto flush = [&]() {
+            if (tb.nbox) launch_tail<T>(tb, st);
+            tb.nbox = 0;
+        };
+        if (!nr) {
+            flush();
+            return;
+        }
         for (int q = 0; q < nr; q++) act[q] = rest[q];
         na = nr;
         const int keep = c->box_mask;
         c->box_mask &= ~tmask;
         vcycle_rest<T>(c, vs, l, act, na, st);
         c->box_mask = keep;
+        flush();
         return;
     }
     vcycle_rest<T>(c, vs, l, act, na, st);
@@ -981,22 +1007,21 @@ static RadArgs rad_args(const p4d_ctx *c)
 }
 
 // z = P^-1 (s r), or P^-T, with the scale s read from device memory (rscale;
-// null: 1).  alpha given: r is a folded vector (its electrode-level rows and
-// alpha) and z its electrode-level part.
+// null: 1).  F given: r is that folded vector and z its direction's
+// electrode-level part.
 template <typename T, typename TZ>
 static void apply_pc_t(p4d_ctx *c, int transpose, const double *r, const double *rscale, TZ *z,
-                       hipStream_t st, const double *alpha = nullptr)
+                       hipStream_t st, const FoldVec *F = nullptr)
 {
     const Geom &g = c->g;
     const int schur = c->pc.pc == P4D_PC_SCHUR;
     const int nb = (int)((g.nnode + kBlock - 1) / kBlock);
     RadArgs R = rad_args(c);
-    R.zeta = c->qbuf;
     if (c->rec) {
         rec_stage<T>(c, SK_RADF, nb);
-    } else if (alpha) {
-        ProfScope ps(c->prof, P4D_K_COUPLING, 24.0 * g.ne + (8.0 + sizeof(T) * 2 + 8.0) * g.Nm, st);
-        launch_rad_fwd_zeta<T>(g, R, r, rscale, alpha, transpose, st);
+    } else if (F) {
+        ProfScope ps(c->prof, P4D_K_COUPLING, 48.0 * g.ne + (8.0 + sizeof(T) * 2 + 8.0) * g.Nm, st);
+        launch_rad_fwd_fold<T>(g, R, *F, r, transpose, st);
     } else {
         ProfScope ps(c->prof, P4D_K_RADIAL, 8.0 * g.N + 32.0 * g.ne + (sizeof(T) * 2 + 8.0) * g.Nm, st);
         launch_rad_fwd<T>(g, R, r, rscale, transpose, schur, st);
@@ -1012,7 +1037,7 @@ static void apply_pc_t(p4d_ctx *c, int transpose, const double *r, const double 
         c->rec_R = R;
         return;
     }
-    if (alpha) {
+    if (F) {
         BgsArgs B{};
         B.R = R;
         ProfScope ps(c->prof, P4D_K_COUPLING, (8.0 + sizeof(TZ)) * g.Nm, st);
@@ -1099,12 +1124,11 @@ static void apply_pc_schur(p4d_ctx *c, const double *r, const double *rscale, TZ
     else apply_pc_schur_t<double, TZ>(c, r, rscale, z, st);
 }
 
-// z = P^-1 (rscale r) for a folded vector (pc SCHUR)
-static void apply_pc_fold(p4d_ctx *c, int transpose, const double *r, const double *rscale, const double *alpha,
-                          double *z, hipStream_t st)
+// z = P^-1 of the folded vector F (pc SCHUR), r its electrode-level rows
+static void apply_pc_fold(p4d_ctx *c, int transpose, const FoldVec &F, const double *r, double *z, hipStream_t st)
 {
-    if (c->prec == 1) apply_pc_t<float, double>(c, transpose, r, rscale, z, st, alpha);
-    else apply_pc_t<double, double>(c, transpose, r, rscale, z, st, alpha);
+    if (c->prec == 1) apply_pc_t<float, double>(c, transpose, r, F.scale, z, st, &F);
+    else apply_pc_t<double, double>(c, transpose, r, F.scale, z, st, &F);
 }
 
 template <typename TZ>
@@ -1291,26 +1315,28 @@ static p4d_status finish_setup(p4d_ctx *c)
 // preconditioner solves the particle rows exactly, so the particle rows of
 // A P^-1 v are those of v; every vector of a cycle is a combination of the
 // cycle's first one and such products, and its particle rows are a multiple
-// alpha of the first vector's, r_s.  The basis then holds the
-// electrode-level rows and one alpha per vector (a seventh of the unknowns
-// of the cube with N_r = 20), every inner product adds alpha_i alpha_j
-// ||r_s||^2, the preconditioner and the operator need the particles only
-// through zeta_j = (A_ss,j^-1 r_s,j)_N, formed once per cycle, and the
-// particle part of the update is one back-substitution of sum_k y_k alpha_k
-// / beta_k times r_s.  The iterates, the Hessenberg matrix and the residual
-// norms are those of the whole vectors up to rounding.  (With Z in FP32 the
-// stored direction is not the exact one, so A z differs from v in the
-// particle rows: those solves keep whole vectors.)  Measured, setup and solve:
-// 15.3 M unknowns with N_r = 20 7.58 -> 4.57 ms (8 steps), 68 M with N_r = 16
-// 86.6 -> 33.1 ms (19 steps), 17 thousand (launch-bound) 1.08 -> 1.02 ms; the
-// solutions agree to 1e-15 .. 1e-11.
+// alpha of the first vector's.  The basis holds the electrode-level rows, the
+// surface rows (which carry the reaction's rounding, a thousand times that of
+// the rows below; kept, they are treated as in whole vectors) and one alpha
+// for the rest: a fifth of the unknowns at N_r = 20.  Every inner product adds
+// alpha_i alpha_j sig2, the preconditioner and the operator need the particles
+// only through the last two rows of A_ss^-1 times the first vector's, formed
+// once per cycle, and the particle part of the update is formed at its end
+// from the directions' electrode-level rows.  The iterates, the Hessenberg
+// matrix and the residual norms are those of the whole vectors up to rounding.
+// (With Z in FP32 the stored direction is not the exact one, so A z differs
+// from v in the particle rows: those solves keep whole vectors.)  Measured,
+// setup and solve: 15.3 M unknowns with N_r = 20 7.3 -> 4.7 ms (8 steps), 68 M
+// with N_r = 16 83 -> 35 ms (18 steps).  The true residuals, whose rounding is a
+// third of them at these sizes, agree with whole vectors' to 3 digits, so that
+// solves stop at the same step.
 static bool fold_rows(const p4d_solve_opts &o)
 {
     return o.krylov == P4D_KRYLOV_FULL && o.pc == P4D_PC_SCHUR && !o.z_fp32;
 }
-// values of a step handed to the host: h of both passes, the norm, the
-// alphas (kept in c->hdev, as is sig2)
-constexpr int kHAlpha = 129, kHSig2 = kHAlpha + kMaxRestart + 1, kHPub = kHAlpha + kMaxRestart + 1;
+// places in c->hdev (and a batched cell's): the alphas and sig2, after the 129
+// values of a step that are handed to the host
+constexpr int kHAlpha = 129, kHSig2 = kHAlpha + kMaxRestart + 1;
 
 template <typename TZ>
 static p4d_status fgmres(p4d_ctx *c, int transpose, const double *b, double *x,
@@ -1319,19 +1345,20 @@ static p4d_status fgmres(p4d_ctx *c, int transpose, const double *b, double *x,
     const Geom &g = c->g;
     const bool schur = o.krylov == P4D_KRYLOV_SCHUR;
     const bool fold = fold_rows(o);
-    const long long N = schur || fold ? g.Nm : g.N;   // Krylov vector length
+    // lengths of the Krylov vectors and of the directions
+    const long long N = schur ? g.Nm : (fold ? g.Nm + g.ne : g.N), Nz = schur || fold ? g.Nm : g.N;
     const int m = o.restart;
     double *V = (double *)c->scratch;
     // basis vector q at Vq + q N.  Folded: a whole vector at V (a cycle's
-    // residual), the others' electrode-level rows after it; that and Z take
-    // no more than whole vectors do.
+    // residual, its vector 0), the other vectors after it; those, Z and u1 take
+    // no more than whole vectors do (N_r >= 3).
     double *Vq = fold ? V + g.N - N : V;
     TZ *Z = (TZ *)(c->scratch + align_up(8 * (size_t)((fold ? g.N : N) + m * N)));
-    double *alpha = c->hdev + kHAlpha, *sig2 = c->hdev + kHSig2, *zeta = c->qbuf;
-    std::vector<double> al(m + 1, 1.0);
+    double *alpha = c->hdev + kHAlpha, *sig2 = c->hdev + kHSig2, *u0 = c->qbuf, *u1 = (double *)Z + m * g.Nm;
+    const FoldMap M = fold ? fold_map(g) : FoldMap{};
     // the Krylov right-hand side: b, or bhat (after Z; the region is sized
     // for the full space, which leaves room)
-    double *bk = schur ? (double *)((char *)Z + align_up(sizeof(TZ) * (size_t)m * N)) : (double *)b;
+    double *bk = schur ? (double *)((char *)Z + align_up(sizeof(TZ) * (size_t)m * Nz)) : (double *)b;
     double *red = c->red;
     const int sb = stream_blocks(N);
     const int sbf = stream_blocks(g.N);
@@ -1365,10 +1392,10 @@ static p4d_status fgmres(p4d_ctx *c, int transpose, const double *b, double *x,
         return P4D_OK;
     };
 
-    // a folded cycle's first vector r: zeta, sig2, alpha_0 and the norm
+    // a folded cycle's first vector r: u0, u1, sig2, alpha_0 and the norm
     auto fold_start = [&](const double *r, double *norm, double *invbeta) {
-        ProfScope ps(c->prof, P4D_K_RADIAL, 8.0 * g.N + 16.0 * g.ne, st);
-        launch_fold_start(g, c->tabs, c->ss, r, zeta, red, transpose, st);
+        ProfScope ps(c->prof, P4D_K_RADIAL, 8.0 * g.N + 24.0 * g.ne, st);
+        launch_fold_start(g, c->tabs, c->ss, r, u0, u1, red, transpose, st);
         launch_fold_final(red, fold_blocks(g), norm, sig2, alpha, invbeta, st);
     };
 
@@ -1449,14 +1476,14 @@ static p4d_status fgmres(p4d_ctx *c, int transpose, const double *b, double *x,
         unsigned long long step_seq[2] = {0, 0};
         auto enqueue_step = [&](int k) {
             const double *vk = k == 0 ? v0 : Vq + (long long)k * N;
-            TZ *zk = Z + (long long)k * N;
+            TZ *zk = Z + (long long)k * Nz;
             double *w = Vq + (long long)(k + 1) * N;
             Fold F{};
             if (fold) {
                 F = Fold{alpha, sig2, c->invbeta, k, 0};
-                apply_pc_fold(c, transpose, vk, c->invbeta + k, alpha + k, (double *)zk, st);
-                apply_op_schur<double>(c, transpose, (const double *)zk, w, st,
-                                       ZetaArgs{zeta, c->invbeta + k, alpha + k});
+                const FoldVec fv{c->invbeta + k, alpha + k, k > 0 ? vk + g.Nm : nullptr, v0, u0, u1};
+                apply_pc_fold(c, transpose, fv, vk, (double *)zk, st);
+                apply_op_fold(c, transpose, fv, (const double *)zk, w, st);
             } else if (schur) {
                 apply_pc_schur<TZ>(c, vk, c->invbeta + k, zk, st);
                 apply_op_schur<TZ>(c, transpose, zk, w, st);
@@ -1470,16 +1497,16 @@ static p4d_status fgmres(p4d_ctx *c, int transpose, const double *b, double *x,
                 F.pass = p;
                 {
                     ProfScope ps(c->prof, P4D_K_MDOT, 8.0 * (nv + 1) * N, st);
-                    launch_mdot(N, w, Vq, v0, N, nv, red, sb, st);
+                    launch_mdot(N, w, Vq, v0, M, N, nv, red, sb, st);
                 }
                 launch_mdot_final(nv, red, sb, c->invbeta, c->hdev + 64 * p, c->cdev, F, st);
                 {
                     ProfScope ps(c->prof, P4D_K_ORTH, 8.0 * (nv + 2) * N, st);
-                    launch_orth(N, w, Vq, v0, N, nv, c->cdev, red, sb, F, st);
+                    launch_orth(N, w, Vq, v0, M, N, nv, c->cdev, red, sb, F, st);
                 }
             }
             launch_norm_final(red, sb, c->hdev + 128, c->invbeta + k + 1, F, st);
-            step_seq[k & 1] = publish(c, c->hdev, fold ? kHAlpha + k + 2 : 129, k & 1, st);
+            step_seq[k & 1] = publish(c, c->hdev, 129, k & 1, st);
         };
         // The next step is enqueued before the host reads this step's column
         // when the residual estimate is expected to stay above the tolerance
@@ -1511,7 +1538,6 @@ static p4d_status fgmres(p4d_ctx *c, int transpose, const double *b, double *x,
             for (int i = 0; i <= k; i++) hc[i] = hh[i] + (o.cgs2 ? hh[64 + i] : 0.0);
             const double hn = hh[128];
             hc[k + 1] = hn;
-            if (fold) al[k + 1] = hh[kHAlpha + k + 1];
             double colnorm = 0.0;
             for (int i = 0; i <= k + 1; i++) colnorm += hc[i] * hc[i];
             colnorm = std::sqrt(colnorm);
@@ -1548,21 +1574,17 @@ static p4d_status fgmres(p4d_ctx *c, int transpose, const double *b, double *x,
         HIPCHK(c, hipMemcpyAsync(c->ydev, hout, 8 * kused, hipMemcpyHostToDevice, st));
         {
             // x written, and read unless this update assigns it
-            ProfScope ps(c->prof, P4D_K_ZY, ((x_zero ? 8.0 : 16.0) + sizeof(TZ) * kused) * N, st);
-            if (fold && !x_zero) {
-                // the update's electrode-level part by itself (in V_1, which
-                // is done with): the particle part follows from it
-                launch_zy<TZ>(N, Vq + N, Z, N, kused, c->ydev, 1, st);
-            }
-            launch_zy<TZ>(N, x, Z, N, kused, c->ydev, x_zero ? 1 : 0, st);
-        }
-        if (fold && kused > 0) {
-            double gamma = 0.0;   // the update's multiple of the first vector's particle rows
-            for (int i = 0; i < kused; i++) gamma += yv[i] * al[i] / beta[i];
-            ProfScope ps(c->prof, P4D_K_RADIAL,
-                         (x_zero ? 16.0 : 24.0) * (g.N - g.Nm) + 8.0 * g.Nm + 32.0 * g.ne, st);
-            launch_red_back(g, c->tabs, c->gg, c->ss, c->ee, c->mm, gamma, v0, x_zero ? x : Vq + N, x,
-                            x_zero ? 0 : 1, transpose, st);
+            const double xb = x_zero ? 8.0 : 16.0;
+            ProfScope ps(c->prof, P4D_K_ZY,
+                         (xb + sizeof(TZ) * kused) * Nz +
+                             (fold ? (xb + 8.0) * (g.N - g.Nm) + (40.0 + 8.0 * kused) * g.ne : 0.0), st);
+            if (fold)
+                launch_fold_update(g,
+                                   FoldUpdate{c->tabs, c->gg, c->ss, c->ee, c->mm, c->omega, v0, Vq, (const double *)Z,
+                                              c->ydev, alpha, c->invbeta, x, kused, x_zero ? 0 : 1},
+                                   transpose, st);
+            else
+                launch_zy<TZ>(Nz, x, Z, Nz, kused, c->ydev, x_zero ? 1 : 0, st);
         }
         if (kused > 0) x_zero = false;
         inf.restarts++;
@@ -1584,7 +1606,7 @@ static p4d_status fgmres(p4d_ctx *c, int transpose, const double *b, double *x,
         // residual of the whole system (V has room for one full vector)
         {
             ProfScope ps(c->prof, P4D_K_RADIAL, 16.0 * (g.N - g.Nm) + 8.0 * g.Nm + 32.0 * g.ne, st);
-            launch_red_back(g, c->tabs, c->gg, c->ss, c->ee, c->mm, 1.0, b, x, x, 0, transpose, st);
+            launch_red_back(g, c->tabs, c->gg, c->ss, c->ee, c->mm, b, x, transpose, st);
         }
         apply_op<double>(c, transpose, x, V, b, red, st);
         launch_norm_final(red, ob, c->hdev + 200, nullptr, Fold{}, st);
@@ -2657,7 +2679,7 @@ static size_t batch_carve(p4d_batch *B, const p4d_solve_opts &o, char *base, p4d
     B->ustart = (int *)take(4 * maxst);
     B->dstart = (int *)take(4 * (maxst + 1));
     B->hb = (double *)take(8 * 256 * (size_t)B->n);
-    B->yb = (double *)take(8 * kYStride * (size_t)B->n);
+    B->yb = (double *)take(8 * 64 * (size_t)B->n);
     B->kused = (int *)take(4 * (size_t)B->n);
     return off;
 }
@@ -2668,7 +2690,7 @@ static double stage_bytes(const PStage<T> &S, const Geom &g, bool fold)
     double bytes = 0.0;
     switch (S.kind) {
     case SK_RADF:
-        if (fold) return 24.0 * g.ne + (8.0 + sizeof(T) * 2 + 8.0) * g.Nm;
+        if (fold) return 48.0 * g.ne + (8.0 + sizeof(T) * 2 + 8.0) * g.Nm;
         return 8.0 * g.N + 32.0 * g.ne + (sizeof(T) * 2 + 8.0) * g.Nm;
     case SK_RADB:
         if (fold) return 16.0 * g.Nm;
@@ -2819,7 +2841,7 @@ static p4d_status batch_record(p4d_batch *B, bool fold)
 
 namespace {
 struct CellRun {
-    std::vector<double> H, cs, sn, gv, yv, hc, beta, al;
+    std::vector<double> H, cs, sn, gv, yv, hc, beta;
     double bnorm = 0.0;
     int total = 0, kused = 0;
     bool done = false, first = true, in_cycle = false, breakdown = false, nonfinite = false;
@@ -2864,7 +2886,7 @@ static p4d_status batch_tables(p4d_batch *B, int m, bool fold, const double *con
         C.g = g;
         C.op = OpArgs{c->tabs, c->sigh, c->kaph, c->gg, c->ss, c->ee, c->mm, nullptr, nullptr, nullptr, c->oms};
         C.fold = fold;
-        C.nk = fold ? g.Nm : g.N;
+        C.nk = fold ? g.Nm + g.ne : g.N;
         C.op_blk0 = G.op;
         C.op_nblk = operator_blocks(g);
         G.op += C.op_nblk;
@@ -2883,9 +2905,10 @@ static p4d_status batch_tables(p4d_batch *B, int m, bool fold, const double *con
         C.fs_n = fold_blocks(g);
         G.fs += C.fs_n;
         C.qbuf = c->qbuf;
-        C.zeta = c->qbuf;
         C.V = (double *)c->scratch;
         C.Z = c->scratch + align_up(8 * (size_t)(g.N + m * C.nk));
+        C.u0 = c->qbuf;
+        C.u1 = (double *)C.Z + m * g.Nm;
         C.x = xv ? xv[i] : nullptr;
         C.b = bv ? bv[i] : nullptr;
         C.red = c->red;
@@ -2894,8 +2917,8 @@ static p4d_status batch_tables(p4d_batch *B, int m, bool fold, const double *con
         C.invbeta = c->invbeta;
         C.alpha = C.h + kHAlpha;
         C.sig2 = C.h + kHSig2;
-        C.y = B->yb + kYStride * (size_t)i;
-        C.gamma = C.y + 64;
+        C.omega = c->omega;
+        C.y = B->yb + 64 * (size_t)i;
         C.kused = B->kused + i;
         PCell &P = pcl[i];
         std::memset((void *)&P, 0, sizeof(P));
@@ -2907,6 +2930,8 @@ static p4d_status batch_tables(p4d_batch *B, int m, bool fold, const double *con
         P.schur = c->pc.pc == P4D_PC_SCHUR;
         P.b = C.b;
         P.alpha = C.alpha;
+        P.u0 = C.u0;
+        P.u1 = C.u1;
     }
     BHIPCHK(B, hipStreamSynchronize(st));
     BHIPCHK(B, hipMemcpy(B->bcell, bc.data(), sizeof(BCell) * n, hipMemcpyHostToDevice));
@@ -3025,7 +3050,7 @@ static p4d_status batch_fgmres(p4d_batch *B, int transpose, const double *const 
     for (auto &R : S) {
         R.H.assign((size_t)(m + 1) * m, 0.0);
         R.cs.assign(m, 0.0); R.sn.assign(m, 0.0); R.gv.assign(m + 1, 0.0);
-        R.yv.assign(m, 0.0); R.hc.assign(m + 2, 0.0); R.beta.assign(m + 1, 0.0); R.al.assign(m + 1, 1.0);
+        R.yv.assign(m, 0.0); R.hc.assign(m + 2, 0.0); R.beta.assign(m + 1, 0.0);
     }
     const size_t hcopy = 8 * 256 * (size_t)n;
     if (B->pc_mode == 2 && B->pgrid < 1)
@@ -3118,10 +3143,11 @@ static p4d_status batch_fgmres(p4d_batch *B, int transpose, const double *const 
                     for (int i = 0; i < n; i++)
                         if ((act >> i) & 1ULL) {
                             p4d_ctx *c = B->cell[i];
-                            const double *v = k > 0 ? bc[i].V + c->g.N + (long long)(k - 1) * c->g.Nm
-                                                    : ((zero >> i) & 1ULL ? bc[i].b : bc[i].V);
-                            apply_pc_fold(c, transpose, v, bc[i].invbeta + k, bc[i].alpha + k,
-                                          (double *)bc[i].Z + (long long)k * c->g.Nm, st);
+                            const double *v0 = (zero >> i) & 1ULL ? bc[i].b : bc[i].V;
+                            const double *v = k > 0 ? bc[i].V + c->g.N + (long long)(k - 1) * bc[i].nk : v0;
+                            const FoldVec fv{bc[i].invbeta + k, bc[i].alpha + k, k > 0 ? v + c->g.Nm : nullptr, v0,
+                                             bc[i].u0, bc[i].u1};
+                            apply_pc_fold(c, transpose, fv, v, (double *)bc[i].Z + (long long)k * c->g.Nm, st);
                         }
                 } else {
                     for (int i = 0; i < n; i++)
@@ -3138,10 +3164,10 @@ static p4d_status batch_fgmres(p4d_batch *B, int transpose, const double *const 
                 for (int i = 0; i < n; i++)
                     if ((act >> i) & 1ULL) {
                         const Geom &g = B->cell[i]->g;
-                        bytes += (sizeof(TZ) + 8.0) * bc[i].nk + 16.0 * g.nelem + (fold ? 48.0 : 32.0) * g.ne;
+                        bytes += (sizeof(TZ) + 8.0) * (fold ? g.Nm : g.N) + 16.0 * g.nelem + (fold ? 80.0 : 32.0) * g.ne;
                     }
                 ProfScope pr(B->prof, P4D_K_OPERATOR, bytes, st);
-                if (fold) launch_bop_fold(B->bcell, n, act, k, transpose, G.tile, st);
+                if (fold) launch_bop_fold(B->bcell, n, act, zero, k, transpose, G.tile, st);
                 else launch_bop<TZ>(B->bcell, n, act, k, 0, transpose, opb, G.tile, G.rad, B->nrmax, st);
             }
             const int nv = k + 1;
@@ -3187,7 +3213,6 @@ static p4d_status batch_fgmres(p4d_batch *B, int transpose, const double *const 
                 R.total++;
                 R.kused = k + 1;
                 R.beta[k + 1] = hn;
-                R.al[k + 1] = hh[kHAlpha + k + 1];
                 R.inf.relres_est = std::fabs(R.gv[k + 1]) / R.bnorm;
                 if (hn <= 1e-14 * colnorm) {
                     R.breakdown = true;
@@ -3215,10 +3240,7 @@ static p4d_status batch_fgmres(p4d_batch *B, int transpose, const double *const 
                 for (int j = q + 1; j < ku; j++) v -= R.H[(size_t)q * m + j] * R.yv[j];
                 R.yv[q] = v / R.H[(size_t)q * m + q];
             }
-            for (int q = 0; q < 64; q++) B->yb_h[kYStride * i + q] = q < ku ? R.yv[q] : 0.0;
-            double gamma = 0.0;
-            for (int q = 0; fold && q < ku; q++) gamma += R.yv[q] * R.al[q] / R.beta[q];
-            B->yb_h[kYStride * i + 64] = gamma;
+            for (int q = 0; q < 64; q++) B->yb_h[64 * i + q] = q < ku ? R.yv[q] : 0.0;
             B->kused_h[i] = ku;
             kmax = ku > kmax ? ku : kmax;
             R.inf.restarts++;
@@ -3227,25 +3249,22 @@ static p4d_status batch_fgmres(p4d_batch *B, int transpose, const double *const 
         if (zmask) {
             // the previous copies from these staging buffers have completed:
             // every step synchronizes the stream
-            BHIPCHK(B, hipMemcpyAsync(B->yb, B->yb_h, 8 * kYStride * (size_t)n, hipMemcpyHostToDevice, st));
+            BHIPCHK(B, hipMemcpyAsync(B->yb, B->yb_h, 8 * 64 * (size_t)n, hipMemcpyHostToDevice, st));
             BHIPCHK(B, hipMemcpyAsync(B->kused, B->kused_h, 4 * (size_t)n, hipMemcpyHostToDevice, st));
             double bytes = 0.0;
             for (int i = 0; i < n; i++)
-                if ((zmask >> i) & 1ULL) bytes += (16.0 + sizeof(TZ) * S[i].kused) * bc[i].nk;
-            {
-                ProfScope pr(B->prof, P4D_K_ZY, bytes, st);
-                launch_bzy<TZ>(B->bcell, n, zmask, zero, kmax, stb, st);
-            }
+                if ((zmask >> i) & 1ULL) {
+                    const Geom &g = B->cell[i]->g;
+                    const double xb = (zero >> i) & 1ULL ? 8.0 : 16.0;
+                    bytes += (xb + sizeof(TZ) * S[i].kused) * (fold ? g.Nm : g.N);
+                    if (fold) bytes += (xb + 8.0) * (g.N - g.Nm) + (40.0 + 8.0 * S[i].kused) * g.ne;
+                }
+            ProfScope pr(B->prof, P4D_K_ZY, bytes, st);
             if (fold) {
-                double rb = 0.0;
-                for (int i = 0; i < n; i++)
-                    if ((zmask >> i) & 1ULL) {
-                        const Geom &g = B->cell[i]->g;
-                        rb += ((zero >> i) & 1ULL ? 16.0 : 24.0) * (g.N - g.Nm) + 8.0 * g.Nm + 32.0 * g.ne;
-                    }
-                ProfScope pr(B->prof, P4D_K_RADIAL, rb, st);
-                launch_bred_back(B->bcell, n, zmask, zero, transpose, opb, B->nrmax, st);
+                launch_bfold_update(B->bcell, n, zmask, zero, transpose, opb, B->nrmax, st);
                 zero &= ~zmask;
+            } else {
+                launch_bzy<TZ>(B->bcell, n, zmask, kmax, stb, st);
             }
         }
     }
@@ -3302,7 +3321,7 @@ p4d_status p4d_batch_create(const p4d_problem_desc *descs, int32_t ncells, p4d_b
         B->cell.push_back(c);
     }
     if (hipHostMalloc((void **)&B->hb_h, 8 * (256 * (size_t)ncells + 1), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void **)&B->yb_h, 8 * kYStride * (size_t)ncells, hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc((void **)&B->yb_h, 8 * 64 * (size_t)ncells, hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void **)&B->kused_h, 4 * (size_t)ncells, hipHostMallocDefault) != hipSuccess) {
         if (B->hb_h) hipHostFree(B->hb_h);
         if (B->yb_h) hipHostFree(B->yb_h);

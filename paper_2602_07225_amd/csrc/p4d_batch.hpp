@@ -47,7 +47,7 @@ struct PCell {
     void *Z;                 // preconditioned directions, [m][N]
     const double *invbeta;   // 1 / ||V_k||
     int schur;
-    const double *b, *alpha; // folded vectors: the first cycle's vector 0, alpha per vector
+    const double *b, *alpha, *u0, *u1;   // folded: the first cycle's vector 0, alpha per vector (see FoldVec)
 };
 
 // One launch: the work list of one stage depth (queue positions
@@ -116,7 +116,7 @@ struct BCell {
     int rad_blk0, rad_n;     // particle-row workgroups
     int fs_blk0, fs_n;       // workgroups of the pass over a folded cycle's first vector
     int fold;                // folded particle rows (see fgmres)
-    long long nk;            // length of the basis vectors (g.N, folded g.Nm)
+    long long nk;            // length of the basis vectors (g.N, folded g.Nm + g.ne)
     int op_tx, op_cz;        // operator tile shape
     double *qbuf;            // reaction q per electrode node
     double *V;
@@ -129,20 +129,19 @@ struct BCell {
     double *invbeta;
     const double *y;         // least-squares coefficients of the finished cycle
     const int *kused;        // their number
-    double *zeta, *alpha, *sig2;   // folded: as in the single-cell solve
-    const double *gamma;     // folded: the update's multiple of the particle rows
+    double *u0, *u1, *alpha, *sig2;   // folded: as in the single-cell solve
+    const double *omega;
 };
-constexpr int kYStride = 72;         // least-squares coefficients per cell, then gamma at 64
 
 // the first vectors of folded cycles: b (first) or the residual at V
 void launch_bfold_start(const BCell *cells, int ncells, unsigned long long active, unsigned long long first,
                         int transpose, int nblk, int nrmax, hipStream_t st);
-// folded: x_s from the update of the finished cycle (added unless first)
-void launch_bred_back(const BCell *cells, int ncells, unsigned long long active, unsigned long long first,
+// folded: the update of the finished cycle (assigned if first, else added)
+void launch_bfold_update(const BCell *cells, int ncells, unsigned long long active, unsigned long long first,
                       int transpose, int nblk_op, int nrmax, hipStream_t st);
-// folded: V_{k+1} = the electrode-level rows of A Z_k
-void launch_bop_fold(const BCell *cells, int ncells, unsigned long long active, int k, int transpose,
-                     int nblk_tile, hipStream_t st);
+// folded: V_{k+1} = A Z_k
+void launch_bop_fold(const BCell *cells, int ncells, unsigned long long active, unsigned long long first, int k,
+                     int transpose, int nblk_tile, hipStream_t st);
 void launch_bstart(const BCell *cells, int ncells, int nblk_st, hipStream_t st);
 // resid: V_0 = b - A x (one thread per node, with partial sums); else
 // V_{k+1} = A Z_k (tiled macro rows, then the particle rows)
@@ -157,7 +156,7 @@ void launch_borth(const BCell *cells, int ncells, unsigned long long active, uns
 void launch_bnorm_final(const BCell *cells, int ncells, unsigned long long active, int slot, int op,
                         hipStream_t st);
 template <typename TZ>
-void launch_bzy(const BCell *cells, int ncells, unsigned long long active, unsigned long long first, int kmax,
-                int nblk_st, hipStream_t st);
+void launch_bzy(const BCell *cells, int ncells, unsigned long long active, int kmax, int nblk_st,
+                hipStream_t st);
 
 }  // namespace p4d

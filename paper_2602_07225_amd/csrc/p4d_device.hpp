@@ -54,10 +54,21 @@ __device__ inline double block_max(double v, double *lds)
 
 // ---------------------------------------------------------------------------
 // Krylov vectors with the particle part folded (see fgmres in p4d_api.hip):
-// the particle rows of every vector of a cycle are a multiple alpha of those
-// of the cycle's first vector, whose sum of squares is sig2.  A vector is
-// then its electrode-level rows and alpha.
+// below the surface, the particle rows of every vector of a cycle are a
+// multiple alpha of those of the cycle's first vector, whose sum of squares is
+// sig2.  A vector is then its electrode-level rows, its surface rows (one per
+// electrode node, phi_s order) and alpha.  The first vector is whole; FoldMap
+// finds entry i of a folded vector in it (nm beyond every i: not folded).
 // ---------------------------------------------------------------------------
+__host__ __device__ inline FoldMap fold_map(const Geom &g)
+{
+    return FoldMap{g.Nm, g.Nm + g.nea, g.off_cs[0] + (long long)(g.nr[0] - 1) * g.nea - g.Nm,
+                   g.off_cs[1] + (long long)(g.nr[1] - 1) * g.nec - g.Nm - g.nea};
+}
+__device__ inline long long fold_at(const FoldMap &M, long long i)
+{
+    return i < M.nm ? i : i + (i < M.na ? M.d0 : M.d1);
+}
 // alpha of w = A P^-1 v_k before Gram-Schmidt (v_k's, normalized), or after
 // its first pass
 __device__ inline double fold_alpha(const double *alpha, const double *invbeta, int k, int pass)
@@ -80,6 +91,7 @@ __host__ __device__ inline int fold_nblk(const Geom &g)
     return (int)(b < 4096 ? b : 4096);
 }
 // its final sums by one workgroup: the norm, sig2, alpha_0 = 1 and 1 / norm
+// (partial: the squares of the folded vector's rows and of the others)
 __device__ inline void fold_final_block(const double *partial, int nblk, double *norm, double *sig2, double *alpha,
                                         double *invbeta, double *lds)
 {

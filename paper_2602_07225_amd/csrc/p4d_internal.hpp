@@ -127,34 +127,42 @@ struct CoarseBatch {
     CoarseArgs<T> a[4];
 };
 
-// The last two levels of a box's V-cycle in one workgroup: the last smoothed
-// level F (from the first iterate the restriction left there: smoothing
-// steps 2..deg, residual, restriction to the coarsest level, dense coarse
-// solve, prolongation, smoothing steps 1..deg) with F's stencil and vectors
-// held in LDS.  The arithmetic is that of the per-stage kernels (the same
-// device functions), so the results are identical.
+// The end of a box's V-cycle in one workgroup: a smoothed level (from the
+// first iterate the restriction left there), a second smoothed level below it
+// if there is one (sub.n > 0), and the dense solve of the coarsest level.  The
+// arithmetic is that of the per-stage kernels (the same device functions), so
+// the results are identical.
+template <typename T>
+struct TailLevel {
+    int nx, ny, nz, n;
+    const T *S, *invd, *b;           // stencil (upper half, [14][n]), inverse diagonal, rhs (top only)
+    double c1[5], c2[5];             // Chebyshev steps 1..deg
+};
 template <typename T>
 struct TailArgs {
-    int nx, ny, nz, n;               // level F
+    TailLevel<T> top, sub;
     int cx, cy, cz, nc;              // coarsest level
-    const T *S, *invd, *b;           // level F stencil (upper half, [14][n]), inverse diagonal, rhs
-    const double *x1;                // level F first iterate
-    double *xout;                    // level F final iterate
+    const double *x1;                // top: first iterate
+    double *xout;                    // top: final iterate
     const double *Ainv;              // coarsest level: dense inverse, column-major
-    double c1[5], c2[5];             // level F Chebyshev steps 1..deg
 };
 template <typename T>
 struct TailBatch {
     int nbox, deg;
     TailArgs<T> a[4];
 };
-constexpr int kTailLds = 96 * 1024;  // LDS of the tail kernel
-constexpr int kTailThreads = 1024;
-// LDS bytes the tail needs for a level of n nodes above a coarsest level of nc
-template <typename T>
-__host__ __device__ constexpr long long tail_lds_bytes(long long n, long long nc)
+constexpr int kTailLds = 152 * 1024; // LDS of the tail kernel
+constexpr int kTailThreads = 512;
+constexpr int kTailNodes = 2;        // nodes of its upper level per thread
+// LDS doubles: both iterates with a one-node halo, the residuals, the
+// coarsest level's right-hand side, solution, partial sums and inverse
+__host__ __device__ inline long long tail_pad(int nx, int ny, int nz) { return (nx + 2LL) * (ny + 2) * (nz + 2); }
+__host__ __device__ inline bool tail_fits(int nx, int ny, int nz, int sx, int sy, int sz, int nc)
 {
-    return 8 * (2 * n + 5 * nc + nc * nc) + (long long)sizeof(T) * (18 * n + nc) + 64;
+    const long long n = (long long)nx * ny * nz, m = (long long)sx * sy * sz;
+    return n <= (long long)kTailNodes * kTailThreads && m <= kTailThreads && nc <= kTailThreads &&
+           8 * (tail_pad(nx, ny, nz) + (m > 0 ? tail_pad(sx, sy, sz) : 0) + n + m + 6LL * nc + (long long)nc * nc) <=
+               kTailLds;
 }
 
 // ---- launchers (each defined beside its kernels) ---------------------------
@@ -174,15 +182,24 @@ void launch_grad(const Geom &g, const RadialTab *tabs, const double *x, const do
                  double *dsigma, double *partial, hipStream_t st);
 void launch_grad_final(const double *partial, int nblk, double *dDs, hipStream_t st);
 
+// A folded vector as the preconditioner and the operator see it: scale = 1 /
+// its norm (device), alpha, its surface rows vs (null: the cycle's first
+// vector, whose surface rows are its own), the cycle's first vector v0 (whole)
+// and the last two rows of A_ss,j^-1 times the particle rows of v0
+struct FoldVec {
+    const double *scale = nullptr, *alpha = nullptr, *vs = nullptr, *v0 = nullptr;
+    const double *u0 = nullptr, *u1 = nullptr;   // surface row, the row below
+};
+
 // radial.hip (RadArgs in p4d_kernels.hpp)
 struct RadArgs;
 template <typename T>
 void launch_rad_fwd(const Geom &g, const RadArgs &R, const double *r, const double *rscale, int transpose,
                     int schur, hipStream_t st);
-// the same with zeta_j = zeta[j] *rscale *alpha given (folded basis vectors)
+// the same for a folded vector
 template <typename T>
-void launch_rad_fwd_zeta(const Geom &g, const RadArgs &R, const double *r, const double *rscale,
-                         const double *alpha, int transpose, hipStream_t st);
+void launch_rad_fwd_fold(const Geom &g, const RadArgs &R, const FoldVec &F, const double *r, int transpose,
+                         hipStream_t st);
 template <typename T, typename TZ>
 void launch_rad_back(const Geom &g, const RadArgs &R, const double *r, const double *rscale, TZ *z,
                      int transpose, int schur, hipStream_t st);
@@ -338,42 +355,49 @@ template <typename T>
 void launch_cast(long long n, const double *src, T *dst, hipStream_t st);
 
 // operator.hip: the Schur complement of the particle blocks (electrode-level
-// vectors of length Nm); with zeta the electrode-level rows of A z for a
-// folded vector: w = S y + a_y s_j zeta_j (transposed Gamma b_y zeta_j),
-// zeta_j = zeta[j] *scale *alpha
-struct ZetaArgs {
-    const double *zeta = nullptr, *scale = nullptr, *alpha = nullptr;
-};
+// vectors of length Nm)
 template <typename TX>
 void launch_operator_schur(const Geom &g, const RadialTab *tabs, const double *sigh,
                            const double *kaph, const double *gg, const double *ss, const double *ee,
                            const double *mm, const double *om, const TX *y, double *w, int transpose,
-                           int tile_tx, int tile_cz, const double *kdh, const double *dch,
-                           const ZetaArgs &za, hipStream_t st);
+                           int tile_tx, int tile_cz, const double *kdh, const double *dch, hipStream_t st);
+// the folded form of w = A z (the electrode-level and surface rows) for z =
+// P^-1 of the folded vector F, y its electrode-level rows
+void launch_operator_fold(const Geom &g, const RadialTab *tabs, const double *sigh, const double *kaph,
+                          const double *gg, const double *ss, const double *ee, const double *mm, const double *om,
+                          const FoldVec &F, const double *y, double *w, int transpose, int tile_tx, int tile_cz,
+                          const double *kdh, const double *dch, hipStream_t st);
 // reduced.hip
 void launch_red_rhs(const Geom &g, const RadialTab *tabs, const double *gg, const double *ss,
                     const double *ee, const double *mm, const double *b, double *bhat, int transpose,
                     hipStream_t st);
-// x_s = (add: x_s +) A_ss^-1 (gamma b_s - delta(y) e_N), y electrode-level
 void launch_red_back(const Geom &g, const RadialTab *tabs, const double *gg, const double *ss,
-                     const double *ee, const double *mm, double gamma, const double *b, const double *y, double *x,
-                     int add, int transpose, hipStream_t st);
-// the first vector r of a folded cycle: zeta_j = (A_ss,j^-1 r_s,j)_N, the
-// norm of r, sig2 = ||r_s||^2, alpha_0 = 1 and (invbeta given) 1 / ||r||
+                     const double *ee, const double *mm, const double *b, double *x, int transpose,
+                     hipStream_t st);
+// the update of a folded cycle
+struct FoldUpdate;
+void launch_fold_update(const Geom &g, const FoldUpdate &U, int transpose, hipStream_t st);
+// the first vector r of a folded cycle: the last two rows u0, u1 of A_ss,j^-1
+// r_s,j, the norm of r, sig2, alpha_0 = 1 and (invbeta given) 1 / ||r||
 int fold_blocks(const Geom &g);
-void launch_fold_start(const Geom &g, const RadialTab *tabs, const double *ss, const double *r, double *zeta,
-                       double *partial, int transpose, hipStream_t st);
+void launch_fold_start(const Geom &g, const RadialTab *tabs, const double *ss, const double *r, double *u0,
+                       double *u1, double *partial, int transpose, hipStream_t st);
 void launch_fold_final(const double *partial, int nblk, double *norm, double *sig2, double *alpha,
                        double *invbeta, hipStream_t st);
 void launch_red_resid(long long n, const double *bhat, double *w, double *partial, int nblk,
                       hipStream_t st);
 
+// where the entries of a folded vector lie in a whole one (p4d_device.hpp)
+struct FoldMap {
+    long long nm = 1LL << 62, na = 1LL << 62, d0 = 0, d1 = 0;
+};
+
 // krylov.hip
 int stream_blocks(long long n);
 // basis vector q at V + q ldv, except vector 0 at v0 (the first cycle's
-// right-hand side, read in place)
-void launch_mdot(long long n, const double *w, const double *V, const double *v0, long long ldv, int nv,
-                 double *partial, int nblk, hipStream_t st);
+// right-hand side, read in place) with its entries found by M
+void launch_mdot(long long n, const double *w, const double *V, const double *v0, const FoldMap &M, long long ldv,
+                 int nv, double *partial, int nblk, hipStream_t st);
 // Folded particle rows of the basis (p4d_device.hpp): alpha per vector,
 // sig2; alpha null: whole vectors
 struct Fold {
@@ -384,7 +408,7 @@ struct Fold {
 };
 void launch_mdot_final(int nv, const double *partial, int nblk, const double *invbeta,
                        double *h, double *c, const Fold &F, hipStream_t st);
-void launch_orth(long long n, double *w, const double *V, const double *v0, long long ldv, int nv,
+void launch_orth(long long n, double *w, const double *V, const double *v0, const FoldMap &M, long long ldv, int nv,
                  const double *c, double *partial, int nblk, const Fold &F, hipStream_t st);
 // (with F: the norm of w = V_{F.k + 1}, its alpha included)
 void launch_norm_final(const double *partial, int nblk, double *beta_out, double *invbeta_out, const Fold &F,

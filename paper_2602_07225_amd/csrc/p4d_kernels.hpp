@@ -273,66 +273,83 @@ __device__ inline void smooth0_tile(const Geom &g, const LevelArgs<T> &A, int ti
 // a lower offset o is that neighbour's coupling at offset 26 - o.
 //   S x = rowsum x_i + sum_{j != i} s_ij (x_j - x_i)
 // ---------------------------------------------------------------------------
+// S x at a node from its 27 couplings (zero to a missing neighbour, whose x
+// may then be any finite value) and neighbourhood
+template <typename T>
+__device__ inline double stencil_row(const T sv[27], const double xv[27])
+{
+    const double xc = xv[13];
+    double Sx = (double)sv[13] * xc;
+#pragma unroll
+    for (int o = 0; o < 27; o++) {
+        if (o == 13) continue;
+        Sx += (double)sv[o] * (xv[o] - xc);
+    }
+    return Sx;
+}
+// which neighbours of node (i, j, k) lie on an nx x ny x nz grid: bit d + 1
+// per axis and offset d, and the answer for stencil offset o (0 or 1), formed
+// without branches
+struct NbMask {
+    unsigned x, y, z;
+    __device__ NbMask(int i, int j, int k, int nx, int ny, int nz)
+        : x((i > 0 ? 1u : 0u) | 2u | (i < nx - 1 ? 4u : 0u)), y((j > 0 ? 1u : 0u) | 2u | (j < ny - 1 ? 4u : 0u)),
+          z((k > 0 ? 1u : 0u) | 2u | (k < nz - 1 ? 4u : 0u))
+    {
+    }
+    __device__ int has(int o) const { return (x >> (o % 3)) & (y >> (o / 3 % 3)) & (z >> (o / 9)) & 1u; }
+};
+// one Chebyshev step from the residual r: the direction (dprev: the previous
+// one, used if c1 != 0)
+__device__ inline double cheb_dir(double c1, double c2, double invd, double r, double dprev)
+{
+    double d = c2 * invd * r;
+    if (c1 != 0.0) d += c1 * dprev;
+    return d;
+}
+
 template <typename T, bool RESID_ONLY>
 __device__ inline void smooth_block(const LevelArgs<T> &A, int blk)
 {
     const int n = blk * kBlock + threadIdx.x;
     if (n >= A.n) return;
     const int i = n % A.nx, t = n / A.nx;
-    const int j = t % A.ny, kl = t / A.ny;
+    const NbMask M(i, t % A.ny, t / A.ny, A.nx, A.ny, A.nz);
     // all coefficients and neighbours are loaded before any arithmetic (a
-    // missing neighbour's index is clamped to the node, its term skipped),
+    // missing neighbour's index is clamped to the node, its coupling dropped),
     // so the loads are in flight together
     T sv[27];
     double xv[27];
-    bool okv[27];
 #pragma unroll
     for (int o = 0; o < 27; o++) {
-        const int dx = o % 3 - 1, dy = (o / 3) % 3 - 1, dz = o / 9 - 1;
-        okv[o] = (i + dx >= 0) && (i + dx < A.nx) && (j + dy >= 0) && (j + dy < A.ny) &&
-                 (kl + dz >= 0) && (kl + dz < A.nz);
-        const int nbr = okv[o] ? n + dx + A.nx * (dy + A.ny * dz) : n;
+        const int h = M.has(o), nbr = n + (((o % 3 - 1) + A.nx * ((o / 3) % 3 - 1 + A.ny * (o / 9 - 1))) & -h);
         xv[o] = A.xin[nbr];
-        if (o > 13) sv[o] = A.S[(long long)(o - 13) * A.n + n];
-        else if (o < 13) sv[o] = A.S[(long long)(13 - o) * A.n + nbr];
-        else sv[o] = A.S[n];
+        const T v = o >= 13 ? A.S[(long long)(o - 13) * A.n + n] : A.S[(long long)(13 - o) * A.n + nbr];
+        sv[o] = h ? v : T(0);
     }
     const double xc = xv[13];
-    double Sx = (double)sv[13] * xc;
-#pragma unroll
-    for (int o = 0; o < 27; o++) {
-        if (o == 13) continue;
-        if (okv[o]) Sx += (double)sv[o] * (xv[o] - xc);
-    }
-    const double r = (double)A.b[n] - Sx;
+    const double r = (double)A.b[n] - stencil_row(sv, xv);
     if (RESID_ONLY) {
         A.rout[n] = (T)r;
         return;
     }
-    double d = A.c2 * (double)A.invd[n] * r;
-    if (A.c1 != 0.0) d += A.c1 * (A.din_x ? xc : (double)A.din[n]);
+    const double d = cheb_dir(A.c1, A.c2, (double)A.invd[n], r,
+                              A.c1 != 0.0 ? (A.din_x ? xc : (double)A.din[n]) : 0.0);
     A.xout[n] = xc + d;
     if (A.dout) A.dout[n] = (T)d;
 }
 
-// b_c = P^T r_f; also the first Chebyshev iterate x_c1 = c2 D_c^-1 b_c
-template <typename T>
-__device__ inline void restrict_block(const TransferArgs<T> &A, int blk)
+// (P^T r_f) at coarse node n
+template <typename Ptr>
+__device__ inline double restrict_value(int fx, int fy, int fz, int cx, int cy, int cz, int n, Ptr rf)
 {
-    const int nc = A.cx * A.cy * A.cz;
-    const int n = blk * kBlock + threadIdx.x;
-    if (n >= nc) return;
-    const int I = n % A.cx, t = n / A.cx;
-    const int J = t % A.cy, K = t / A.cy;
+    const int I = n % cx, t = n / cx;
+    const int J = t % cy, K = t / cy;
     int fi[3], fj[3], fk[3];
     double wi[3], wj[3], wk[3];
-    const int ni = fine_of(A.fx, I, fi, wi);
-    const int nj = fine_of(A.fy, J, fj, wj);
-    const int nk = fine_of(A.cz == A.fz ? 1 : A.fz, K, fk, wk);   // (z kept: identity)
-    (void)ni; (void)nj; (void)nk;
-    // issued with the residual loads (after the store below it would wait
-    // for them first)
-    const double idc = A.xc1 ? (double)A.invdc[n] : 0.0;
+    fine_of(fx, I, fi, wi);
+    fine_of(fy, J, fj, wj);
+    fine_of(cz == fz ? 1 : fz, K, fk, wk);   // (z kept: identity)
     // all 27 slots, without tests: an unused slot reads a point that a used
     // slot reads too and adds an exact zero to a sum that starts at +0 (and
     // so never holds -0), leaving it as it is bit for bit; unguarded, the
@@ -342,16 +359,55 @@ __device__ inline void restrict_block(const TransferArgs<T> &A, int blk)
     for (int c = 0; c < 3; c++) {
 #pragma unroll
         for (int bq = 0; bq < 3; bq++) {
-            const long long row = (long long)A.fx * (fj[bq] + (long long)A.fy * fk[c]);
+            const int row = fx * (fj[bq] + fy * fk[c]);
             double part = 0.0;
 #pragma unroll
-            for (int a = 0; a < 3; a++) part += wi[a] * (double)A.rf[row + fi[a]];
+            for (int a = 0; a < 3; a++) part += wi[a] * (double)rf[row + fi[a]];
             acc += wj[bq] * wk[c] * part;
         }
     }
-    const T bc = (T)acc;
+    return acc;
+}
+
+// b_c = P^T r_f; also the first Chebyshev iterate x_c1 = c2 D_c^-1 b_c
+template <typename T>
+__device__ inline void restrict_block(const TransferArgs<T> &A, int blk)
+{
+    const int nc = A.cx * A.cy * A.cz;
+    const int n = blk * kBlock + threadIdx.x;
+    if (n >= nc) return;
+    // issued with the residual loads (after the store below it would wait
+    // for them first)
+    const double idc = A.xc1 ? (double)A.invdc[n] : 0.0;
+    const T bc = (T)restrict_value(A.fx, A.fy, A.fz, A.cx, A.cy, A.cz, n, A.rf);
     A.bc[n] = bc;
     if (A.xc1) A.xc1[n] = A.c2c * idc * (double)bc;
+}
+
+// (P x_c) at fine node (i, j, k); coarse node (I, J, K) at xc[I + sy J + sz K]
+template <typename Ptr>
+__device__ inline double prolong_value(int fx, int fy, int fz, bool keepz, int i, int j, int k, Ptr xc, int sy, int sz)
+{
+    int Ci[2], Cj[2], Ck[2];
+    double wi[2], wj[2], wk[2];
+    coarse_of(fx, i, Ci, wi);
+    coarse_of(fy, j, Cj, wj);
+    coarse_of(keepz ? 1 : fz, k, Ck, wk);
+    // all 8 slots, without tests (an unused slot adds an exact zero; see
+    // restrict_block)
+    double acc = 0.0;
+#pragma unroll
+    for (int c = 0; c < 2; c++) {
+#pragma unroll
+        for (int bq = 0; bq < 2; bq++) {
+            const int row = sy * Cj[bq] + sz * Ck[c];
+            double part = 0.0;
+#pragma unroll
+            for (int a = 0; a < 2; a++) part += wi[a] * xc[row + Ci[a]];
+            acc += wj[bq] * wk[c] * part;
+        }
+    }
+    return acc;
 }
 
 // x_f += P x_c
@@ -363,27 +419,7 @@ __device__ inline void prolong_block(const TransferArgs<T> &A, int blk)
     if (n >= nf) return;
     const int i = n % A.fx, t = n / A.fx;
     const int j = t % A.fy, k = t / A.fy;
-    int Ci[2], Cj[2], Ck[2];
-    double wi[2], wj[2], wk[2];
-    const int ni = coarse_of(A.fx, i, Ci, wi);
-    const int nj = coarse_of(A.fy, j, Cj, wj);
-    const int nk = coarse_of(A.cz == A.fz ? 1 : A.fz, k, Ck, wk);
-    (void)ni; (void)nj; (void)nk;
-    // all 8 slots, without tests (an unused slot adds an exact zero; see
-    // restrict_block)
-    double acc = 0.0;
-#pragma unroll
-    for (int c = 0; c < 2; c++) {
-#pragma unroll
-        for (int bq = 0; bq < 2; bq++) {
-            const long long row = (long long)A.cx * (Cj[bq] + (long long)A.cy * Ck[c]);
-            double part = 0.0;
-#pragma unroll
-            for (int a = 0; a < 2; a++) part += wi[a] * A.xc[row + Ci[a]];
-            acc += wj[bq] * wk[c] * part;
-        }
-    }
-    A.xf[n] += acc;
+    A.xf[n] += prolong_value(A.fx, A.fy, A.fz, A.cz == A.fz, i, j, k, A.xc, A.cx, A.cx * A.cy);
 }
 
 // Coarsest level, 64 rows of x = A^-1 b per workgroup (FP64); the 4 waves
@@ -430,16 +466,44 @@ struct RadArgs {
     const void *invd0;   // T
     double c2box[4];
     const double *x0[4]; // final level-0 iterates per box (rad_back)
-    const double *zeta;  // folded vectors: (A_ss,j^-1 s_j)_N of the cycle's particle rows s
 };
+
+// The surface rows of a folded vector at one electrode node, scaled: ap the
+// scaled alpha, e what the surface row has beyond ap times the first vector's
+// (rounding, as long as P solves the particle rows exactly)
+struct FoldNode {
+    double ap, e;
+};
+__device__ inline FoldNode fold_node(const Geom &g, const FoldVec &F, long long je)
+{
+    const double sc = *F.scale;
+    FoldNode n{*F.alpha * sc, 0.0};
+    if (F.vs) n.e = F.vs[je] * sc - n.ap * F.v0[fold_at(fold_map(g), g.Nm + je)];
+    return n;
+}
+// row q of z_s,j = A_ss,j^-1 (r_s,j - delta_j e_N) for a folded r: u is row q
+// of A_ss,j^-1 s_j, t that of T0^-1 e_N, eo = e omega_j, dw = delta_j omega_j
+__device__ inline double fold_row(double ap, double u, double eo, double dw, double t)
+{
+    const double zn = ap * u + eo * t;
+    return zn - dw * t;
+}
+// delta_j of A_sy z (transposed A_ys^T z)
+template <bool TRANS, typename Tab>
+__device__ inline double fold_delta(const Geom &g, const Tab &T, bool dir, double m, double gj, double sj, double ej,
+                                    double zps, double zpe, double zce)
+{
+    if (!TRANS) return T.Gamma * ((dir ? 0.0 : gj) * zps - gj * zpe + ej * zce);
+    return sj * ((dir ? 0.0 : m) * zps - m * zpe - g.tc * m * zce);
+}
 
 // zeta_j = (A_ss,j^-1 r_s,j)_N; r~_y = r_y - a_y s_j zeta_j (transposed:
 // r_y - Gamma b_y zeta_j); written in precision T with the first Chebyshev
 // iterate of each box.  SCHUR 0: r~_y = r_y; 1: zeta_j by elimination; 2: a
-// folded vector, zeta_j = R.zeta[j] zscale.
+// folded vector F.
 template <typename T, int NRMAX, bool TRANS, int SCHUR>
 __device__ inline void rad_fwd_block(const Geom &g, const RadArgs &R, const double *r, double rscale,
-                                     int blk, double zscale = 0.0)
+                                     int blk, const FoldVec &F = FoldVec{})
 {
     const long long n = (long long)blk * kBlock + threadIdx.x;
     if (n >= g.nnode) return;
@@ -476,7 +540,10 @@ __device__ inline void rad_fwd_block(const Geom &g, const RadArgs &R, const doub
             }
         };
         if (SCHUR == 2) {
-            couple(R.zeta[je] * zscale, el == 0 ? R.tabs[0].Gamma : R.tabs[1].Gamma, R.ss[je]);
+            const double tN = el == 0 ? R.tabs[0].tau0 : R.tabs[1].tau0;
+            const FoldNode fn = fold_node(g, F, je);
+            couple(fold_row(fn.ap, F.u0[je], fn.e * R.om[je], 0.0, tN), el == 0 ? R.tabs[0].Gamma : R.tabs[1].Gamma,
+                   R.ss[je]);
         } else if (SCHUR) {
             auto elim = [&](const auto &Tb) {
                 const int N = Tb.N;
@@ -617,11 +684,12 @@ __device__ inline void macro_out_block(const Geom &g, const RadArgs &R, const do
     z[je] = (TZ)(k == 0 ? r[je] * rscale : (el == 0 ? R.x0[0] : R.x0[1])[je]);
 }
 
-// The first vector r of a folded cycle at one node: zeta_j = (A_ss,j^-1
-// r_s,j)_N (FP64) and the squares of its electrode-level and particle rows
+// The first vector r of a folded cycle at one node: the last two rows of
+// A_ss,j^-1 r_s,j (FP64) and the squares of its folded (electrode-level and
+// surface) and of its other particle rows
 template <int NRMAX, bool TRANS>
 __device__ inline void fold_start_node(const Geom &g, const RadialTab *tabs, const double *ss, const double *r,
-                                       double *zeta, long long n, double &sqy, double &sqs)
+                                       double *u0, double *u1, long long n, double &sqy, double &sqs)
 {
     const int k = (int)(n / ((long long)g.nx * g.ny));
     const double rpe = r[g.off_pe + n], rce = r[g.off_ce + n];
@@ -640,90 +708,126 @@ __device__ inline void fold_start_node(const Geom &g, const RadialTab *tabs, con
         double rv[NRMAX];
 #pragma unroll
         for (int q = 0; q < NRMAX; q++) rv[q] = rs[(long long)(q < N ? q : N - 1) * nn];
-        double y = rv[0];
-        double sq = rv[0] * rv[0];
+        double y = rv[0], ym = 0.0;
+        double sq = rv[0] * rv[0], rl = rv[0];
 #pragma unroll
         for (int q = 1; q < NRMAX; q++) {
             if (q < N) {
+                ym = y;
                 y = rv[q] - (TRANS ? Tb.lT[q] : Tb.l[q]) * y;
-                sq += rv[q] * rv[q];
+                rl = rv[q];
+                if (q < N - 1) sq += rv[q] * rv[q];
             }
         }
         sqs += sq;
-        zeta[je] = y / (Tb.piv[N - 1] + Tb.Gamma * ss[je]);
+        sqy += rl * rl;
+        const double zn = y / (Tb.piv[N - 1] + Tb.Gamma * ss[je]);
+        u0[je] = zn;
+        u1[je] = (ym - (TRANS ? Tb.tsub[N - 1] : Tb.tsup[N - 2]) * zn) * Tb.ipiv[N - 2];
     };
     const int elw = __builtin_amdgcn_readfirstlane(el);
     if (__builtin_amdgcn_ballot_w64(el != elw) == 0) elim(*(const ConstTab *)(tabs + elw));
     else elim(tabs[el]);
 }
 
-// x_s,j = (ADD: x_s,j +) A_ss,j^-1 (gamma b_s,j - delta_j e_N), delta_j =
-// Gamma b_y . y (transposed s_j a_y . y), all in FP64
-template <int NRMAX, bool TRANS, bool ADD>
-__device__ inline void red_back_block(const Geom &g, const RadialTab *tabs, const double *gg, const double *ss,
-                                      const double *ee, const double *mm, double gamma, const double *b,
-                                      const double *y, double *x, int blk)
+// The update x (+)= sum_k y_k z_k of a folded cycle at one node: the
+// electrode-level rows from the stored directions; the particle rows of each
+// direction from those and A_ss^-1 s (s: the particle rows of the cycle's first
+// vector, solved once), rounded and added up one direction after the other
+// like stored ones.  (Summed before the solve, the particle surface rows carry
+// a third of the rounding, which is the largest part of the true residual: such
+// solves stop now and then a cycle earlier than those with whole vectors.)
+struct FoldUpdate {
+    const RadialTab *tabs;
+    const double *gg, *ss, *ee, *mm, *om;
+    const double *v0, *V, *Z, *y, *alpha, *invbeta;   // V_q (q >= 1) at V + q (Nm + ne)
+    double *x;
+    int nv, add;
+};
+template <int NRMAX, bool TRANS>
+__device__ inline void fold_update_node(const Geom &g, const FoldUpdate &U, long long n)
 {
-    const long long n = (long long)blk * kBlock + threadIdx.x;
-    if (n >= g.nnode) return;
     const int k = (int)(n / ((long long)g.nx * g.ny));
     const int el = node_mat(g, k);
-    if (el < 0) return;
     const long long base = el == 0 ? 0 : g.nea;
     const long long klo = el == 0 ? 0 : g.na + g.ns;
-    const long long je = base + n - klo * g.nx * g.ny;
+    const long long je = base + n - klo * g.nx * g.ny;   // (electrode nodes)
+    const long long pe = g.off_pe + n, ce = g.off_ce + n, ld = g.Nm;
+    double xpe = U.add ? U.x[pe] : 0.0, xce = U.add ? U.x[ce] : 0.0;
+    if (el < 0) {
+        for (int q = 0; q < U.nv; q++) {
+            xpe += U.y[q] * U.Z[q * ld + pe];
+            xce += U.y[q] * U.Z[q * ld + ce];
+        }
+        U.x[pe] = xpe;
+        U.x[ce] = xce;
+        return;
+    }
     const bool dir = (k == 0);
     auto solve = [&](const auto &Tb) {
         const int N = Tb.N;
         const long long nn = el == 0 ? g.nea : g.nec;
-        const long long offs = el == 0 ? g.off_cs[0] : g.off_cs[1];
-        const double *bs = b + offs + (je - base);
-        double *xs = x + offs + (je - base);
-        const double yps = dir ? 0.0 : y[je], ype = y[g.off_pe + n], yce = y[g.off_ce + n];
-        const double sj = ss[je], m = mm[je], gj = gg[je];
-        const double delta = TRANS ? sj * (m * yps - m * ype - g.tc * m * yce)
-                                   : Tb.Gamma * (gj * yps - gj * ype + ee[je] * yce);
-        double rv[NRMAX], xo[NRMAX];
+        const long long offs = (el == 0 ? g.off_cs[0] : g.off_cs[1]) + (je - base);
+        const double *rs = U.v0 + offs;
+        double *xs = U.x + offs;
+        const double sj = U.ss[je], m = U.mm[je], gj = U.gg[je], ej = U.ee[je], om = U.om[je];
+        // u = A_ss^-1 s, in place over the column
+        double u[NRMAX], xv[NRMAX];
 #pragma unroll
-        for (int q = 0; q < NRMAX; q++) rv[q] = bs[(long long)(q < N ? q : N - 1) * nn];
-        if (ADD) {
+        for (int q = 0; q < NRMAX; q++) u[q] = rs[(long long)(q < N ? q : N - 1) * nn];
+        if (U.add) {
 #pragma unroll
-            for (int q = 0; q < NRMAX; q++) xo[q] = xs[(long long)(q < N ? q : N - 1) * nn];
+            for (int q = 0; q < NRMAX; q++) xv[q] = xs[(long long)(q < N ? q : N - 1) * nn];
+        } else {
+#pragma unroll
+            for (int q = 0; q < NRMAX; q++) xv[q] = 0.0;
         }
-        // forward elimination with the shared unit-lower factor; the surface
-        // entry carries -delta
-        double yv[NRMAX];
-        yv[0] = gamma * rv[0];   // N >= 3: the surface entry is not the first
-        double ylast = yv[0];
+        double xps = U.add ? U.x[je] : 0.0;
+        const double sN = U.v0[fold_at(fold_map(g), g.Nm + je)];
+        double ul = u[0];
 #pragma unroll
         for (int q = 1; q < NRMAX; q++) {
             if (q < N) {
-                const double rq = q == N - 1 ? gamma * rv[q] - delta : gamma * rv[q];
-                yv[q] = rq - (TRANS ? Tb.lT[q] : Tb.l[q]) * yv[q - 1];
-                ylast = yv[q];
+                u[q] -= (TRANS ? Tb.lT[q] : Tb.l[q]) * u[q - 1];
+                ul = u[q];
             }
         }
-        double zn = ylast / (Tb.piv[N - 1] + Tb.Gamma * sj);
-        double xlast = 0.0;
-        if (ADD) {
+        double zn = ul / (Tb.piv[N - 1] + Tb.Gamma * sj);
 #pragma unroll
-            for (int q = 0; q < NRMAX; q++)
-                if (q == N - 1) xlast = xo[q];
-        }
-        xs[(long long)(N - 1) * nn] = ADD ? xlast + zn : zn;
-#pragma unroll
-        for (int q = NRMAX - 2; q >= 0; q--) {
+        for (int q = NRMAX - 1; q >= 0; q--) {
+            if (q == N - 1) u[q] = zn;
             if (q < N - 1) {
-                zn = (yv[q] - (TRANS ? Tb.tsub[q + 1] : Tb.tsup[q]) * zn) * Tb.ipiv[q];
-                xs[(long long)q * nn] = ADD ? xo[q] + zn : zn;
+                zn = (u[q] - (TRANS ? Tb.tsub[q + 1 < kMaxNr ? q + 1 : q] : Tb.tsup[q]) * zn) * Tb.ipiv[q];
+                u[q] = zn;
             }
         }
+        for (int p = 0; p < U.nv; p++) {
+            const double zps = U.Z[p * ld + je], zpe = U.Z[p * ld + pe], zce = U.Z[p * ld + ce];
+            const double sc = U.invbeta[p], yp = U.y[p], ap = U.alpha[p] * sc;
+            const double e = p > 0 ? U.V[p * (ld + g.ne) + ld + je] * sc - ap * sN : 0.0;
+            const double dw = fold_delta<TRANS>(g, Tb, dir, m, gj, sj, ej, zps, zpe, zce) * om, eo = e * om;
+            xps += yp * zps;
+            xpe += yp * zpe;
+            xce += yp * zce;
+#pragma unroll
+            for (int q = 0; q < NRMAX; q++) {
+                if (q < N) {
+                    xv[q] += yp * fold_row(ap, u[q], eo, dw, TRANS ? Tb.tNT[q] : Tb.tN[q]);
+                }
+            }
+        }
+        U.x[je] = xps;
+        U.x[pe] = xpe;
+        U.x[ce] = xce;
+#pragma unroll
+        for (int q = 0; q < NRMAX; q++)
+            if (q < N) xs[(long long)q * nn] = xv[q];
     };
     // the electrode's table through a wave-uniform pointer (scalar loads) when
     // the whole wave lies in one electrode, per lane otherwise
     const int elw = __builtin_amdgcn_readfirstlane(el);
-    if (__builtin_amdgcn_ballot_w64(el != elw) == 0) solve(*(const ConstTab *)(tabs + elw));
-    else solve(tabs[el]);
+    if (__builtin_amdgcn_ballot_w64(el != elw) == 0) solve(*(const ConstTab *)(U.tabs + elw));
+    else solve(U.tabs[el]);
 }
 
 // ---------------------------------------------------------------------------
@@ -740,20 +844,29 @@ struct OpArgs {
     const double *om;    // omega per electrode node (Schur complement operator)
     const double *kdh;   // h * diffusion-potential coefficient per element (GEN)
     const double *dch;   // h * c_e diffusion coefficient per element (GEN)
-    ZetaArgs za;         // RED: the folded particle rows' part (zeta null: none)
+    FoldVec fv;          // OP_FOLD
 };
 
-// q of the RED forms: omega_j times the electrode-level reaction, plus s_j
-// (transposed Gamma) times the surface value zeta_j of the folded particle
-// rows, the two adding up to the reaction with the particle solved for
-template <bool TRANS>
-__device__ inline double red_reaction(const OpArgs &O, double q, long long je, double Gam, double sj, double zsc)
+// Forms of the operator: A on whole vectors; the Schur complement of the
+// particle blocks on electrode-level vectors (the reaction scaled by omega_j,
+// no particle column); A on the direction of a folded vector, of which x holds
+// the electrode-level rows (the surface rows of y after its electrode-level
+// ones)
+enum OpMode { OP_FULL = 0, OP_RED = 1, OP_FOLD = 2 };
+
+// the last two rows of the particle column of a folded vector's direction
+template <bool TRANS, typename Tab>
+__device__ inline void fold_surface(const Geom &g, const OpArgs &O, const Tab &T, long long je, bool dir, double m,
+                                    double gj, double sj, double ej, double zps, double zpe, double zce, double &xsN,
+                                    double &xsM)
 {
-    q *= O.om[je];
-    if (O.za.zeta) q += (TRANS ? Gam : sj) * (O.za.zeta[je] * zsc);
-    return q;
+    const int N = T.N;
+    const FoldNode fn = fold_node(g, O.fv, je);
+    const double om = O.om[je];
+    const double dw = fold_delta<TRANS>(g, T, dir, m, gj, sj, ej, zps, zpe, zce) * om, eo = fn.e * om;
+    xsN = fold_row(fn.ap, O.fv.u0[je], eo, dw, TRANS ? T.tNT[N - 1] : T.tN[N - 1]);
+    xsM = fold_row(fn.ap, O.fv.u1[je], eo, dw, TRANS ? T.tNT[N - 2] : T.tN[N - 2]);
 }
-__device__ inline double zeta_scale(const OpArgs &O) { return O.za.zeta ? *O.za.scale * *O.za.alpha : 0.0; }
 
 template <typename TX>
 __device__ inline double ldx(const TX *p) { return (double)*p; }
@@ -878,10 +991,8 @@ __device__ inline double op_radial_row(const Tab &T, bool trans, int r, int N, d
 // the output (y, or b - A x when RESID); returns the sum of squares written.
 // GEN: separate element coefficients for the diffusion-potential block
 // (P.Kx) and the c_e diffusion (P.Kce), instead of chi * kappa and kappa.
-// RED: the Schur complement of the particle blocks (see operator_tile): the
-// reaction enters scaled by omega_j, no particle column (x, y hold the
-// electrode-level unknowns only)
-template <typename TX, int NRMAX, bool TRANS, bool RESID, bool GEN = false, bool RED = false>
+// MODE: see OpMode
+template <typename TX, int NRMAX, bool TRANS, bool RESID, bool GEN = false, int MODE = OP_FULL>
 __device__ inline double operator_finish(const Geom &g, const OpArgs &O, long long n, int i, int j,
                                          int k, const OpStencil &P)
 {
@@ -926,8 +1037,9 @@ __device__ inline double operator_finish(const Geom &g, const OpArgs &O, long lo
             const double m = O.mm[je], gj = O.gg[je], sj = O.ss[je], ej = O.ee[je];
             // the particle column, loaded at once (indices clamped to the last point)
             double xr[NRMAX], bv[NRMAX];
-            double xsN = 0.0, bps = 0.0;
-            if (!RED) {
+            double xsN = 0.0, xsM = 0.0, bps = 0.0;
+            if (MODE == OP_FOLD) fold_surface<TRANS>(g, O, T, je, dir, m, gj, sj, ej, P.xpsc, xpe, xce, xsN, xsM);
+            if (MODE == OP_FULL) {
 #pragma unroll
                 for (int r = 0; r < NRMAX; r++) xr[r] = ldx(xs + (long long)(r < N ? r : N - 1) * nn);
                 if (RESID) {
@@ -941,17 +1053,17 @@ __device__ inline double operator_finish(const Geom &g, const OpArgs &O, long lo
             }
             if (RESID) bps = b[je];
             const OpCoupling cp = op_coupling<TRANS>(g, T, dir, m, gj, sj, ej, P.xpsc, xpe, xce, xsN);
-            const double q = RED ? red_reaction<TRANS>(O, cp.q, je, T.Gamma, sj, zeta_scale(O)) : cp.q;
-            const double r3 = cp.r3;
+            const double q = MODE == OP_RED ? cp.q * O.om[je] : cp.q, r3 = cp.r3;
             double yps = dir ? xps : P.Kps + cp.r0 * q;
             ype += cp.r1 * q;
             yce += cp.r2 * q;
             if (RESID) yps = bps - yps;
             y[je] = yps;
             sq += yps * yps;
+            if (MODE == OP_FOLD) y[g.Nm + je] = op_radial_row(T, TRANS, N - 1, N, xsM, xsN, 0.0) + r3 * q;
 #pragma unroll
             for (int r = 0; r < NRMAX; r++) {
-                if (RED) break;
+                if (MODE != OP_FULL) break;
                 if (r < N) {
                     const double xm = r > 0 ? xr[r > 0 ? r - 1 : 0] : 0.0;
                     const double x0 = xr[r];
@@ -982,7 +1094,7 @@ __device__ inline double operator_finish(const Geom &g, const OpArgs &O, long lo
 
 // The operator y = A x (or A^T x, or b - A x) at one node, every stencil
 // value read from memory (paper Sec. 4.1, eq. blocks; see operator.hip).
-template <typename TX, int NRMAX, bool TRANS, bool RESID, bool GEN = false, bool RED = false>
+template <typename TX, int NRMAX, bool TRANS, bool RESID, bool GEN = false, int MODE = OP_FULL>
 __device__ inline double operator_node(const Geom &g, const OpArgs &O, long long n)
 {
     const TX *x = (const TX *)O.x;
@@ -1074,7 +1186,7 @@ __device__ inline double operator_node(const Geom &g, const OpArgs &O, long long
         P.Kps = stiff_of<GEN>(g, cs, X);
         P.xpsc = X[13];
     }
-    return operator_finish<TX, NRMAX, TRANS, RESID, GEN, RED>(g, O, n, i, j, k, P);
+    return operator_finish<TX, NRMAX, TRANS, RESID, GEN, MODE>(g, O, n, i, j, k, P);
 }
 
 // ---------------------------------------------------------------------------
@@ -1095,16 +1207,13 @@ __host__ __device__ inline int op_tiles(int nx, int ny, int nz, int TX, int CZ)
     return smooth0_box_tiles(nx, ny, nz, TX, CZ);
 }
 
-// RED: the Schur complement S = A_yy - A_ys A_ss^-1 A_sy of the particle
-// blocks instead of A, over the electrode-level unknowns only: the reaction
-// coupling of each electrode node enters scaled by omega_j (Sherman-Morrison:
-// 1 - Gamma s_j (A_ss,j^-1)_NN = omega_j) and there is no particle column.
-template <typename TX_T, bool TRANS, bool RED = false>
+// MODE: see OpMode (OP_RED: 1 - Gamma s_j (A_ss,j^-1)_NN = omega_j by
+// Sherman-Morrison)
+template <typename TX_T, bool TRANS, int MODE = OP_FULL>
 __device__ inline void operator_tile(const Geom &g, const OpArgs &O, double *qout, int tile, int TX,
                                      int CZ, OpLds &L)
 {
     const TX_T *x = (const TX_T *)O.x;
-    const double zsc = RED ? zeta_scale(O) : 0.0;
     const int TY = kBlock / TX;
     const int PX = TX + 2, PY = TY + 2;
     const int EX = TX + 1, EY = TY + 1;
@@ -1270,20 +1379,23 @@ __device__ inline void operator_tile(const Geom &g, const OpArgs &O, double *qou
                 // the tile's layer lies in one electrode: its table through a
                 // wave-uniform pointer (scalar loads)
                 const ConstTab &T = *(const ConstTab *)(O.tabs + __builtin_amdgcn_readfirstlane(el));
-                double xsN = 0.0;
-                if (!RED) {
+                double xsN = 0.0, xsM = 0.0;
+                const double m = O.mm[je], gj = O.gg[je], sj = O.ss[je], ej = O.ee[je];
+                if (MODE == OP_FULL) {
                     const long long nn = el == 0 ? g.nea : g.nec;
                     const long long offs = el == 0 ? g.off_cs[0] : g.off_cs[1];
                     xsN = ldx(x + offs + (je - base) + (long long)(T.N - 1) * nn);
                 }
-                const double sj = O.ss[je];
-                const OpCoupling cp = op_coupling<TRANS>(g, T, dir, O.mm[je], O.gg[je], sj,
-                                                         O.ee[je], P.xpsc, P.xpe, P.xce, xsN);
-                const double q = RED ? red_reaction<TRANS>(O, cp.q, je, T.Gamma, sj, zsc) : cp.q;
+                if (MODE == OP_FOLD)
+                    fold_surface<TRANS>(g, O, T, je, dir, m, gj, sj, ej, P.xpsc, P.xpe, P.xce, xsN, xsM);
+                const OpCoupling cp = op_coupling<TRANS>(g, T, dir, m, gj, sj, ej, P.xpsc, P.xpe, P.xce, xsN);
+                const double q = MODE == OP_RED ? cp.q * O.om[je] : cp.q;
                 O.y[je] = dir ? ldx(x + je) : P.Kps + cp.r0 * q;
                 ype += cp.r1 * q;
                 yce += cp.r2 * q;
-                if (!RED) qout[je] = q;
+                if (MODE == OP_FULL) qout[je] = q;
+                if (MODE == OP_FOLD)
+                    O.y[g.Nm + je] = op_radial_row(T, TRANS, T.N - 1, T.N, xsM, xsN, 0.0) + cp.r3 * q;
             }
             O.y[g.off_pe + n] = ype;
             O.y[g.off_ce + n] = yce;

@@ -49,25 +49,23 @@ template void launch_rad_fwd<float>(const Geom &, const RadArgs &, const double 
                                     hipStream_t);
 
 template <typename T, bool TRANS>
-__global__ __launch_bounds__(kBlock) void k_rad_fwd_zeta(Geom g, RadArgs R, const double *r, const double *rscale,
-                                                         const double *alpha)
+__global__ __launch_bounds__(kBlock) void k_rad_fwd_fold(Geom g, RadArgs R, FoldVec F, const double *r)
 {
-    const double rs = *rscale;
-    rad_fwd_block<T, 1, TRANS, 2>(g, R, r, rs, blockIdx.x, *alpha * rs);
+    rad_fwd_block<T, 1, TRANS, 2>(g, R, r, *F.scale, blockIdx.x, F);
 }
 
 template <typename T>
-void launch_rad_fwd_zeta(const Geom &g, const RadArgs &R, const double *r, const double *rscale,
-                         const double *alpha, int transpose, hipStream_t st)
+void launch_rad_fwd_fold(const Geom &g, const RadArgs &R, const FoldVec &F, const double *r, int transpose,
+                         hipStream_t st)
 {
     const int nb = (int)((g.nnode + kBlock - 1) / kBlock);
-    if (transpose) hipLaunchKernelGGL((k_rad_fwd_zeta<T, true>), dim3(nb), dim3(kBlock), 0, st, g, R, r, rscale, alpha);
-    else hipLaunchKernelGGL((k_rad_fwd_zeta<T, false>), dim3(nb), dim3(kBlock), 0, st, g, R, r, rscale, alpha);
+    if (transpose) hipLaunchKernelGGL((k_rad_fwd_fold<T, true>), dim3(nb), dim3(kBlock), 0, st, g, R, F, r);
+    else hipLaunchKernelGGL((k_rad_fwd_fold<T, false>), dim3(nb), dim3(kBlock), 0, st, g, R, F, r);
 }
-template void launch_rad_fwd_zeta<double>(const Geom &, const RadArgs &, const double *, const double *,
-                                          const double *, int, hipStream_t);
-template void launch_rad_fwd_zeta<float>(const Geom &, const RadArgs &, const double *, const double *,
-                                         const double *, int, hipStream_t);
+template void launch_rad_fwd_fold<double>(const Geom &, const RadArgs &, const FoldVec &, const double *, int,
+                                          hipStream_t);
+template void launch_rad_fwd_fold<float>(const Geom &, const RadArgs &, const FoldVec &, const double *, int,
+                                         hipStream_t);
 
 template <typename T, typename TZ, int NRMAX, bool TRANS, bool SCHUR>
 __global__ __launch_bounds__(kBlock) void k_rad_back(Geom g, RadArgs R, const double *r,

@@ -68,25 +68,75 @@ __global__ __launch_bounds__(kBlock) void k_red_rhs(Geom g, RedArgs R, const dou
     bhat[g.off_ce + n] = bce;
 }
 
-template <int NRMAX, bool TRANS, bool ADD>
-__global__ __launch_bounds__(kBlock) void k_red_back(Geom g, RedArgs R, double gamma, const double *b, const double *y,
-                                                     double *x)
+template <int NRMAX, bool TRANS>
+__global__ __launch_bounds__(kBlock) void k_red_back(Geom g, RedArgs R, const double *__restrict__ b,
+                                                     double *__restrict__ x)
 {
-    red_back_block<NRMAX, TRANS, ADD>(g, R.tabs, R.gg, R.ss, R.ee, R.mm, gamma, b, y, x, blockIdx.x);
+    const long long n = (long long)blockIdx.x * kBlock + threadIdx.x;
+    if (n >= g.nnode) return;
+    const int k = (int)(n / ((long long)g.nx * g.ny));
+    const int el = node_mat(g, k);
+    if (el < 0) return;
+    const long long base = el == 0 ? 0 : g.nea;
+    const long long klo = el == 0 ? 0 : g.na + g.ns;
+    const long long je = base + n - klo * g.nx * g.ny;
+    const bool dir = (k == 0);
+    const RadialTab &Tb = R.tabs[el];
+    const int N = Tb.N;
+    const long long nn = el == 0 ? g.nea : g.nec;
+    const long long offs = el == 0 ? g.off_cs[0] : g.off_cs[1];
+    const double *bs = b + offs + (je - base);
+    double *xs = x + offs + (je - base);
+    const double yps = dir ? 0.0 : x[je], ype = x[g.off_pe + n], yce = x[g.off_ce + n];
+    const double sj = R.ss[je], m = R.mm[je], gj = R.gg[je];
+    const double delta = TRANS ? sj * (m * yps - m * ype - g.tc * m * yce)
+                               : Tb.Gamma * (gj * yps - gj * ype + R.ee[je] * yce);
+    double rv[NRMAX];
+#pragma unroll
+    for (int q = 0; q < NRMAX; q++) rv[q] = bs[(long long)(q < N ? q : N - 1) * nn];
+    // forward elimination with the shared unit-lower factor; the surface
+    // entry carries -delta
+    double yv[NRMAX];
+    yv[0] = rv[0];   // N >= 3: the surface entry is not the first
+    double ylast = yv[0];
+#pragma unroll
+    for (int q = 1; q < NRMAX; q++) {
+        if (q < N) {
+            const double rq = q == N - 1 ? rv[q] - delta : rv[q];
+            yv[q] = rq - (TRANS ? Tb.lT[q] : Tb.l[q]) * yv[q - 1];
+            ylast = yv[q];
+        }
+    }
+    double zn = ylast / (Tb.piv[N - 1] + Tb.Gamma * sj);
+    xs[(long long)(N - 1) * nn] = zn;
+#pragma unroll
+    for (int q = NRMAX - 2; q >= 0; q--) {
+        if (q < N - 1) {
+            zn = (yv[q] - (TRANS ? Tb.tsub[q + 1] : Tb.tsup[q]) * zn) * Tb.ipiv[q];
+            xs[(long long)q * nn] = zn;
+        }
+    }
+}
+
+template <int NRMAX, bool TRANS>
+__global__ __launch_bounds__(kBlock) void k_fold_update(Geom g, FoldUpdate U)
+{
+    const long long n = (long long)blockIdx.x * kBlock + threadIdx.x;
+    if (n < g.nnode) fold_update_node<NRMAX, TRANS>(g, U, n);
 }
 
 // the first vector of a folded cycle (see fold_start_node); workgroups stride
-// over the nodes, with the partial sums of the electrode-level and particle
-// squares at 2 b and 2 b + 1
+// over the nodes, with the partial sums of its two groups of squares at 2 b
+// and 2 b + 1
 template <int NRMAX, bool TRANS>
 __global__ __launch_bounds__(kBlock) void k_fold_start(Geom g, const RadialTab *tabs, const double *__restrict__ ss,
-                                                       const double *__restrict__ r, double *__restrict__ zeta,
-                                                       double *__restrict__ partial)
+                                                       const double *__restrict__ r, double *__restrict__ u0,
+                                                       double *__restrict__ u1, double *__restrict__ partial)
 {
     __shared__ double lds[4];
     double sqy = 0.0, sqs = 0.0;
     for (long long n = (long long)blockIdx.x * kBlock + threadIdx.x; n < g.nnode; n += (long long)gridDim.x * kBlock)
-        fold_start_node<NRMAX, TRANS>(g, tabs, ss, r, zeta, n, sqy, sqs);
+        fold_start_node<NRMAX, TRANS>(g, tabs, ss, r, u0, u1, n, sqy, sqs);
     sqy = block_sum(sqy, lds);
     sqs = block_sum(sqs, lds);
     if (threadIdx.x == 0) {
@@ -144,40 +194,48 @@ void launch_red_rhs(const Geom &g, const RadialTab *tabs, const double *gg, cons
 }
 
 void launch_red_back(const Geom &g, const RadialTab *tabs, const double *gg, const double *ss,
-                     const double *ee, const double *mm, double gamma, const double *b, const double *y, double *x,
-                     int add, int transpose, hipStream_t st)
+                     const double *ee, const double *mm, const double *b, double *x, int transpose,
+                     hipStream_t st)
 {
     const RedArgs R = red_args(tabs, gg, ss, ee, mm);
     const int nb = (int)((g.nnode + kBlock - 1) / kBlock);
-#define P4D_RB1(NR, TR, AD) \
-    hipLaunchKernelGGL((k_red_back<NR, TR, AD>), dim3(nb), dim3(kBlock), 0, st, g, R, gamma, b, y, x)
-#define P4D_RB(NR)                              \
-    do {                                        \
-        if (transpose) {                        \
-            if (add) P4D_RB1(NR, true, true);   \
-            else P4D_RB1(NR, true, false);      \
-        } else {                                \
-            if (add) P4D_RB1(NR, false, true);  \
-            else P4D_RB1(NR, false, false);     \
-        }                                       \
+#define P4D_RB(NR)                                                                                \
+    do {                                                                                          \
+        if (transpose)                                                                            \
+            hipLaunchKernelGGL((k_red_back<NR, true>), dim3(nb), dim3(kBlock), 0, st, g, R, b, x);  \
+        else                                                                                      \
+            hipLaunchKernelGGL((k_red_back<NR, false>), dim3(nb), dim3(kBlock), 0, st, g, R, b, x); \
     } while (0)
     P4D_NR_SWITCH(rad_nrmax(g), P4D_RB)
 #undef P4D_RB
-#undef P4D_RB1
+}
+
+void launch_fold_update(const Geom &g, const FoldUpdate &U, int transpose, hipStream_t st)
+{
+    const int nb = (int)((g.nnode + kBlock - 1) / kBlock);
+#define P4D_FU(NR)                                                                                    \
+    do {                                                                                              \
+        if (transpose) hipLaunchKernelGGL((k_fold_update<NR, true>), dim3(nb), dim3(kBlock), 0, st, g, U); \
+        else hipLaunchKernelGGL((k_fold_update<NR, false>), dim3(nb), dim3(kBlock), 0, st, g, U);          \
+    } while (0)
+    P4D_NR_SWITCH(rad_nrmax(g), P4D_FU)
+#undef P4D_FU
 }
 
 int fold_blocks(const Geom &g) { return fold_nblk(g); }
 
-void launch_fold_start(const Geom &g, const RadialTab *tabs, const double *ss, const double *r, double *zeta,
-                       double *partial, int transpose, hipStream_t st)
+void launch_fold_start(const Geom &g, const RadialTab *tabs, const double *ss, const double *r, double *u0,
+                       double *u1, double *partial, int transpose, hipStream_t st)
 {
     const int nb = fold_nblk(g);
 #define P4D_FS(NR)                                                                                             \
     do {                                                                                                       \
         if (transpose)                                                                                         \
-            hipLaunchKernelGGL((k_fold_start<NR, true>), dim3(nb), dim3(kBlock), 0, st, g, tabs, ss, r, zeta, partial); \
+            hipLaunchKernelGGL((k_fold_start<NR, true>), dim3(nb), dim3(kBlock), 0, st, g, tabs, ss, r, u0, u1, \
+                               partial);                                                                      \
         else                                                                                                   \
-            hipLaunchKernelGGL((k_fold_start<NR, false>), dim3(nb), dim3(kBlock), 0, st, g, tabs, ss, r, zeta, partial); \
+            hipLaunchKernelGGL((k_fold_start<NR, false>), dim3(nb), dim3(kBlock), 0, st, g, tabs, ss, r, u0, u1, \
+                               partial);                                                                      \
     } while (0)
     P4D_NR_SWITCH(rad_nrmax(g), P4D_FS)
 #undef P4D_FS
