@@ -750,7 +750,7 @@ __global__ __launch_bounds__(kBlock) void k_zline(LineBatch lb, int colour)
                 }
                 const int q = k * LT + l;
                 Llo[q] = Zr[4 * w];    // offset (0,0,-1), +0 in the bottom layer
-                Lup[q] = Zr[22 * w];   // offset (0,0,+1), +0 in the top layer
+                Lup[q] = Zr[22 * w];   // the line's factors (k_zline_factor)
                 Ldg[q] = Zr[13 * w];
                 Lrh[q] = rhs;
             }
@@ -759,21 +759,19 @@ __global__ __launch_bounds__(kBlock) void k_zline(LineBatch lb, int colour)
     }
     if (threadIdx.x < w) {
         // the next row's values are read one step ahead (ahead of this
-        // step's stores), so that the LDS latency leaves the chain of
-        // dependent divisions
+        // step's stores), so that the LDS latency leaves the chain; with the
+        // pivots' reciprocals stored, a step of it is a multiply-add and a
+        // product (two dependent divisions before: 300 of its ~330 cycles)
         const int ll = threadIdx.x;
-        double cprev = 0.0, dprev = 0.0;
-        double lo = Llo[ll], dg = Ldg[ll], up = Lup[ll], rh = Lrh[ll];
+        double dprev = 0.0;
+        double lo = Llo[ll], id = Ldg[ll], rh = Lrh[ll];
         for (int k = 0; k < nz; k++) {
             const int q = k * LT + ll;
             const int qn = k + 1 < nz ? q + LT : q;
-            const double lo1 = Llo[qn], dg1 = Ldg[qn], up1 = Lup[qn], rh1 = Lrh[qn];
-            const double den = dg - lo * cprev;
-            cprev = up / den;
-            dprev = (rh - lo * dprev) / den;
-            Lup[q] = cprev;
+            const double lo1 = Llo[qn], id1 = Ldg[qn], rh1 = Lrh[qn];
+            dprev = (rh - lo * dprev) * id;
             Lrh[q] = dprev;
-            lo = lo1; dg = dg1; up = up1; rh = rh1;
+            lo = lo1; id = id1; rh = rh1;
         }
         double nxt = 0.0;
         double c = Lup[(nz - 1) * LT + ll], d = Lrh[(nz - 1) * LT + ll];
@@ -835,6 +833,40 @@ __global__ __launch_bounds__(kBlock) void k_zline_order(int nx, int ny, int nz, 
     }
 }
 
+// The tridiagonal block of each line factored in place in Sz, one thread per
+// line: the pivots' reciprocals over the diagonal (offset 13), the
+// superdiagonal over the pivots at offset 22 (the subdiagonal, offset 4, stays).
+// A line's rows are read eight ahead of the chain of divisions.
+__global__ __launch_bounds__(64) void k_zline_factor(int nx, int ny, int nz, int LT, double *__restrict__ Sz)
+{
+    const int line = blockIdx.x * 64 + threadIdx.x;
+    if (line >= nx * ny) return;
+    const int i = line % nx, j = line / nx;
+    const int colour = (i & 1) | ((j & 1) << 1);
+    const long long base = 27 * zline_rows_below(nx, ny, nz, colour);
+    const int ncx = (nx - (i & 1) + 1) / 2;
+    constexpr int kU = 8;
+    double cprev = 0.0;
+    for (int k0 = 0; k0 < nz; k0 += kU) {
+        double lo[kU], dg[kU], up[kU];
+#pragma unroll
+        for (int u = 0; u < kU; u++) {
+            const int k = k0 + u < nz ? k0 + u : nz - 1;
+            lo[u] = Sz[zline_index(base, ncx, nz, LT, i >> 1, j >> 1, k, 4)];
+            dg[u] = Sz[zline_index(base, ncx, nz, LT, i >> 1, j >> 1, k, 13)];
+            up[u] = Sz[zline_index(base, ncx, nz, LT, i >> 1, j >> 1, k, 22)];
+        }
+#pragma unroll
+        for (int u = 0; u < kU; u++) {
+            if (k0 + u >= nz) break;
+            const double id = 1.0 / (dg[u] - lo[u] * cprev);
+            cprev = up[u] * id;
+            Sz[zline_index(base, ncx, nz, LT, i >> 1, j >> 1, k0 + u, 13)] = id;
+            Sz[zline_index(base, ncx, nz, LT, i >> 1, j >> 1, k0 + u, 22)] = cprev;
+        }
+    }
+}
+
 // Tile width LT (lines along x, a power of two) and chunk depth KC (layers,
 // a power of two, KC * LT <= kBlock) of an nx x ny x nz box: 8-line tiles on
 // boxes with many lines (HBM-bound sweeps), 2-line tiles on boxes with few
@@ -864,6 +896,7 @@ void launch_zline_order(int nx, int ny, int nz, const double *S, double *Sz, hip
     const long long N = (long long)nx * ny * nz;
     hipLaunchKernelGGL(k_zline_order, dim3((unsigned)((N + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, nx,
                        ny, nz, LT, S, Sz);
+    hipLaunchKernelGGL(k_zline_factor, dim3((nx * ny + 63) / 64), dim3(64), 0, st, nx, ny, nz, LT, Sz);
 }
 
 void launch_zline(LineBatch lb, int colour, hipStream_t st)
@@ -1015,52 +1048,17 @@ __global__ __launch_bounds__(kBlock) void k_dense(int nx, int ny, int nz,
     A[t] = 0.5 * (entry(r, c) + entry(c, r));
 }
 
-// In-place Gauss-Jordan inversion of SPD matrices (no pivoting), one
-// workgroup per matrix; each wave sweeps rows, its lanes the columns.  The
-// result is written column-major (equal to row-major for the symmetric
-// inverse).
-__global__ __launch_bounds__(1024) void k_invert(InvBatch ib)
-{
-    __shared__ double rowp[1024];
-    __shared__ double colp[1024];
-    const int box = blockIdx.x;
-    const int n = ib.n[box];
-    double *A = ib.A[box];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
-    for (int p = 0; p < n; p++) {
-        __syncthreads();
-        const double d = 1.0 / A[(long long)p * n + p];
-        for (int q = threadIdx.x; q < n; q += blockDim.x) {
-            rowp[q] = A[(long long)p * n + q] * d;
-            colp[q] = A[(long long)q * n + p];
-        }
-        __syncthreads();
-        for (int i = wave; i < n; i += nw) {
-            const double ci = colp[i];
-            double *Ai = A + (long long)i * n;
-            for (int j = lane; j < n; j += 64) {
-                double v;
-                if (i == p) v = j == p ? d : rowp[j];
-                else v = j == p ? -ci * d : Ai[j] - ci * rowp[j];
-                Ai[j] = v;
-            }
-        }
-    }
-    __syncthreads();
-    double *out = ib.Ainv[box];
-    for (long long t = threadIdx.x; t < (long long)n * n; t += blockDim.x) out[t] = A[t];
-}
-
 void launch_dense_from_stencil(int nx, int ny, int nz, const double *S, double *A, hipStream_t st)
 {
     const long long n = (long long)nx * ny * nz;
     hipLaunchKernelGGL(k_dense, dim3((int)((n * n + kBlock - 1) / kBlock)), dim3(kBlock), 0, st, nx,
                        ny, nz, S, A);
 }
-// Same elimination for n <= kInvLds with the matrix held in registers, at
-// most kInvE entries per thread at fixed positions: per pivot only the pivot
-// row and column pass through LDS.  Each entry is updated by the same
-// expressions as above, so the inverse is the same.
+// In-place Gauss-Jordan inversion of SPD matrices (no pivoting), one workgroup
+// per matrix, for n <= kInvLds: the matrix held in registers, at most kInvE
+// entries per thread at fixed positions, per pivot only the pivot row and
+// column pass through LDS.  The result is written column-major (equal to
+// row-major for the symmetric inverse).
 constexpr int kInvLds = 80;
 constexpr int kInvE = (kInvLds * kInvLds + 1023) / 1024;
 __global__ __launch_bounds__(1024) void k_invert_lds(InvBatch ib)
@@ -1104,7 +1102,7 @@ __global__ __launch_bounds__(1024) void k_invert_lds(InvBatch ib)
     }
 }
 
-// The same elimination for n <= 64, laid out so that publishing a pivot row
+// The same for n <= 64, laid out so that publishing a pivot row
 // and column needs no search: thread t holds column j = t % 64 in rows
 // t / 64 + 16 s (s = 0..3).  Row and column p + 1 and the reciprocal of
 // their diagonal entry are stored, into the other of two buffers, by their
@@ -1165,18 +1163,180 @@ __global__ __launch_bounds__(1024) void k_invert_w64(InvBatch ib)
     }
 }
 
-void launch_invert(const InvBatch &ib, hipStream_t st)
+// Blocked form of the same inversion for larger matrices: 32 pivots at a time.
+//   k_inv_diag:  D = A_pp^-1 (one workgroup per matrix, an entry per thread)
+//   k_inv_panel: C_i = A_ip kept, A_pj <- D A_pj
+//   k_inv_rank:  A_ij -= C_i A_pj, A_ip = -C_i D, A_pp = D
+// One workgroup that passed the whole matrix through memory for every pivot
+// took 3.68 ms for four matrices of 100 to 244 unknowns; here the matrix is
+// passed once for 32 pivots, by a workgroup per 32 x 32 tile: 0.19 ms.  C and D
+// lie in the result's memory, which is written last (32 n + 1024 values, fewer
+// than n^2 from n = 49 on).
+constexpr int kInvB = 32;
+static_assert(kInvLds * kInvB + kInvB * kInvB <= kInvLds * kInvLds, "room for C and D");
+__global__ __launch_bounds__(1024) void k_inv_diag(InvBatch ib, int p0)
 {
-    int nmax = 0;
-    for (int b = 0; b < ib.nbox; b++) nmax = ib.n[b] > nmax ? ib.n[b] : nmax;
-    if (nmax <= kInvW)
-        hipLaunchKernelGGL(k_invert_w64, dim3(ib.nbox), dim3(1024), 0, st, ib);
-    else if (nmax <= kInvLds)
-        hipLaunchKernelGGL(k_invert_lds, dim3(ib.nbox), dim3(1024), 0, st, ib);
-    else
-        hipLaunchKernelGGL(k_invert, dim3(ib.nbox), dim3(1024), 0, st, ib);
+    __shared__ double rowp[2][kInvB], colp[2][kInvB], dp[2];
+    const int box = blockIdx.x, n = ib.n[box];
+    if (p0 >= n) return;
+    const int nb = n - p0 < kInvB ? n - p0 : kInvB;
+    double *D = ib.Ainv[box] + (long long)n * kInvB;
+    const int j = threadIdx.x % kInvB, i = threadIdx.x / kInvB;
+    const bool own = i < nb && j < nb;
+    double v = own ? ib.A[box][(long long)(p0 + i) * n + p0 + j] : 0.0;
+    // row, column and diagonal reciprocal of pivot q into buffer q & 1
+    auto publish = [&](int q) {
+        const int b = q & 1;
+        if (i == q && own) {
+            rowp[b][j] = v;
+            if (j == q) dp[b] = 1.0 / v;
+        }
+        if (j == q && own) colp[b][i] = v;
+    };
+    publish(0);
+    __syncthreads();
+    for (int p = 0; p < nb; p++) {
+        const int b = p & 1;
+        if (own) {
+            const double d = dp[b], rp = rowp[b][j] * d;
+            if (i == p) v = j == p ? d : rp;
+            else v = j == p ? -colp[b][i] * d : v - colp[b][i] * rp;
+        }
+        if (p + 1 < nb) publish(p + 1);
+        __syncthreads();
+    }
+    D[i * kInvB + j] = v;   // rows and columns past the end are zero
 }
 
+// 32 x 32 tile product by 256 threads, 2 x 2 entries each: acc = X Y, X and Y
+// (row-major, zero past the ends) in LDS
+__device__ inline void inv_product(const double (*X)[kInvB + 1], const double (*Y)[kInvB], double acc[2][2])
+{
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+#pragma unroll
+    for (int a = 0; a < 2; a++)
+#pragma unroll
+        for (int b = 0; b < 2; b++) acc[a][b] = 0.0;
+#pragma unroll 8
+    for (int k = 0; k < kInvB; k++)
+#pragma unroll
+        for (int a = 0; a < 2; a++)
+#pragma unroll
+            for (int b = 0; b < 2; b++) acc[a][b] += X[ty + 16 * a][k] * Y[k][tx + 16 * b];
+}
+
+// tile t of the pivot's panels: A_pj <- D A_pj (t < nt) or C_i = A_ip
+__global__ __launch_bounds__(256) void k_inv_panel(InvBatch ib, int p0)
+{
+    __shared__ double X[kInvB][kInvB + 1], Y[kInvB][kInvB];
+    const int box = blockIdx.y, n = ib.n[box];
+    if (p0 >= n) return;
+    const int nt = (n + kInvB - 1) / kInvB, t = blockIdx.x % nt;
+    if ((int)blockIdx.x >= 2 * nt || t == p0 / kInvB) return;
+    const int q0 = t * kInvB, nb = n - p0 < kInvB ? n - p0 : kInvB, nq = n - q0 < kInvB ? n - q0 : kInvB;
+    double *A = ib.A[box], *C = ib.Ainv[box];
+    const double *D = C + (long long)n * kInvB;
+    if ((int)blockIdx.x >= nt) {
+        for (int e = threadIdx.x; e < nq * kInvB; e += 256) {
+            const int i = e / kInvB, k = e % kInvB;
+            C[(long long)(q0 + i) * kInvB + k] = k < nb ? A[(long long)(q0 + i) * n + p0 + k] : 0.0;
+        }
+        return;
+    }
+    for (int e = threadIdx.x; e < kInvB * kInvB; e += 256) {
+        const int i = e / kInvB, k = e % kInvB;
+        X[i][k] = D[e];
+        Y[i][k] = i < nb && k < nq ? A[(long long)(p0 + i) * n + q0 + k] : 0.0;
+    }
+    __syncthreads();
+    double acc[2][2];
+    inv_product(X, Y, acc);
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+    for (int a = 0; a < 2; a++)
+        for (int b = 0; b < 2; b++)
+            if (ty + 16 * a < nb && tx + 16 * b < nq)
+                A[(long long)(p0 + ty + 16 * a) * n + q0 + tx + 16 * b] = acc[a][b];
+}
+
+// tile (i, j) of the rest
+__global__ __launch_bounds__(256) void k_inv_rank(InvBatch ib, int p0)
+{
+    __shared__ double X[kInvB][kInvB + 1], Y[kInvB][kInvB];
+    const int box = blockIdx.z, n = ib.n[box];
+    if (p0 >= n) return;
+    const int nt = (n + kInvB - 1) / kInvB, ti = blockIdx.y, tj = blockIdx.x, tp = p0 / kInvB;
+    if (ti >= nt || tj >= nt || (ti == tp && tj != tp)) return;
+    const int i0 = ti * kInvB, j0 = tj * kInvB, nb = n - p0 < kInvB ? n - p0 : kInvB;
+    const int ni = n - i0 < kInvB ? n - i0 : kInvB, nj = n - j0 < kInvB ? n - j0 : kInvB;
+    double *A = ib.A[box];
+    const double *C = ib.Ainv[box], *D = C + (long long)n * kInvB;
+    if (ti == tp) {   // (the pivot block)
+        for (int e = threadIdx.x; e < nb * nb; e += 256)
+            A[(long long)(p0 + e / nb) * n + p0 + e % nb] = D[(e / nb) * kInvB + e % nb];
+        return;
+    }
+    for (int e = threadIdx.x; e < kInvB * kInvB; e += 256) {
+        const int i = e / kInvB, k = e % kInvB;
+        X[i][k] = i < ni ? C[(long long)(i0 + i) * kInvB + k] : 0.0;
+        Y[i][k] = tj == tp ? D[e] : (i < nb && k < nj ? A[(long long)(p0 + i) * n + j0 + k] : 0.0);
+    }
+    __syncthreads();
+    double acc[2][2];
+    inv_product(X, Y, acc);
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+    for (int a = 0; a < 2; a++)
+        for (int b = 0; b < 2; b++) {
+            const int i = ty + 16 * a, j = tx + 16 * b;
+            if (i >= ni || j >= nj) continue;
+            double *at = A + (long long)(i0 + i) * n + j0 + j;
+            *at = tj == tp ? -acc[a][b] : *at - acc[a][b];
+        }
+}
+
+__global__ __launch_bounds__(kBlock) void k_inv_store(InvBatch ib)
+{
+    const int box = blockIdx.y;
+    const long long t = (long long)blockIdx.x * kBlock + threadIdx.x;
+    if (t < (long long)ib.n[box] * ib.n[box]) ib.Ainv[box][t] = ib.A[box][t];
+}
+
+void launch_invert(const InvBatch &ib, hipStream_t st)
+{
+    int nmax = 0, nmin = 1 << 30;
+    for (int b = 0; b < ib.nbox; b++) {
+        nmax = ib.n[b] > nmax ? ib.n[b] : nmax;
+        nmin = ib.n[b] < nmin ? ib.n[b] : nmin;
+    }
+    if (nmax <= kInvW) {
+        hipLaunchKernelGGL(k_invert_w64, dim3(ib.nbox), dim3(1024), 0, st, ib);
+        return;
+    }
+    if (nmax <= kInvLds) {
+        hipLaunchKernelGGL(k_invert_lds, dim3(ib.nbox), dim3(1024), 0, st, ib);
+        return;
+    }
+    if (nmin <= kInvLds) {
+        // the boxes on either side of the limit by themselves
+        InvBatch part[2] = {};
+        for (int b = 0; b < ib.nbox; b++) {
+            InvBatch &q = part[ib.n[b] > kInvLds];
+            q.n[q.nbox] = ib.n[b];
+            q.A[q.nbox] = ib.A[b];
+            q.Ainv[q.nbox++] = ib.Ainv[b];
+        }
+        launch_invert(part[0], st);
+        launch_invert(part[1], st);
+        return;
+    }
+    const int nt = (nmax + kInvB - 1) / kInvB;
+    for (int p0 = 0; p0 < nmax; p0 += kInvB) {
+        hipLaunchKernelGGL(k_inv_diag, dim3(ib.nbox), dim3(1024), 0, st, ib, p0);
+        hipLaunchKernelGGL(k_inv_panel, dim3(2 * nt, ib.nbox), dim3(256), 0, st, ib, p0);
+        hipLaunchKernelGGL(k_inv_rank, dim3(nt, nt, ib.nbox), dim3(256), 0, st, ib, p0);
+    }
+    hipLaunchKernelGGL(k_inv_store, dim3((int)(((long long)nmax * nmax + kBlock - 1) / kBlock), ib.nbox), dim3(kBlock), 0,
+                       st, ib);
+}
 
 // A coarse level's smoother data in one pass over its stored Galerkin
 // stencil: the difference form in T (slot 0 the row sum formed in FP64,

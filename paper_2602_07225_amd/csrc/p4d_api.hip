@@ -900,7 +900,8 @@ static void vcycle_rest(p4d_ctx *c, VState<T> &vs, int l, int *act, int na, hipS
 }
 
 // One V-cycle at level l with z-line smoothing (FP64; levels keep their z
-// extent): x = 0, cheb_degree passes of colours 0..3, residual, restriction,
+// extent): from x = 0 (left by the restriction, at level 0 by the right-hand
+// side's kernel), cheb_degree passes of colours 0..3, residual, restriction,
 // the coarser level, prolongation, cheb_degree passes of colours 3..0.  The
 // iterate of every level stays in its xa buffer.
 static void vcycle_line(p4d_ctx *c, int l, hipStream_t st)
@@ -937,7 +938,6 @@ static void vcycle_line(p4d_ctx *c, int l, hipStream_t st)
         A.b = (const double *)L.b;
         A.x = (double *)L.xa;
         A.r = (double *)L.r;
-        hipMemsetAsync(A.x, 0, 8 * (size_t)L.n, st);
         // stencil, b, x read and written
         bytes += (27.0 * 8 + 8 + 16) * L.n;
     }
@@ -966,8 +966,9 @@ static void vcycle_line(p4d_ctx *c, int l, hipStream_t st)
             blk += (Cl.n + kBlock - 1) / kBlock;
             A.rf = (const double *)F.r;
             A.bc = (double *)Cl.b;
-            A.xc1 = nullptr;
-            A.invdc = nullptr;
+            // the coarse iterate starts from x = 0 (the coarsest solve assigns it)
+            A.xc1 = l + 1 == B.nlev - 1 ? nullptr : (double *)Cl.xa;
+            A.invdc = (const double *)Cl.invd;
             A.c2c = 0.0;
         }
         launch_restrict<double>(tb, blk, st);
@@ -1002,7 +1003,10 @@ static RadArgs rad_args(const p4d_ctx *c)
     R.b0 = c->b0;
     R.x1 = (double *)c->x0a;
     R.invd0 = c->invd0;
-    for (int b = 0; b < 4; b++) R.c2box[b] = cheb_coef(c->box[b].lev[0].lmax, c->pc.cheb_degree).c2[1];
+    // (z-line sweeps start from x = 0)
+    for (int b = 0; b < 4; b++)
+        R.c2box[b] = c->pc.smoother == P4D_SMOOTH_ZLINE ? 0.0
+                                                        : cheb_coef(c->box[b].lev[0].lmax, c->pc.cheb_degree).c2[1];
     return R;
 }
 
