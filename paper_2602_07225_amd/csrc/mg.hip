@@ -680,10 +680,14 @@ void launch_rap(const Geom &g, const RapJob *jobs, int njobs, int zc, hipStream_
 // planes around the tile (2 LT + 1 by 3 nodes, layers k0 - 1 .. k0 + KC) in
 // LDS; its threads form, one (line, layer) each, the right-hand side with
 // the couplings to other lines moved over (lines of one colour do not
-// couple) and copy the line's tridiagonal block (offsets (0,0,-1), centre,
-// (0,0,1)).  Then one thread per line eliminates down the line and
-// substitutes back up in LDS, and all threads write x.  LDS [k][line] keeps
-// the threads of the elimination on consecutive banks.
+// couple), scale it with the pivot's reciprocal and copy the line's two other
+// factors.  Then 32 lanes per line substitute down and back up in LDS, and
+// all threads write x.  One thread per line cost ~100 cycles a row: a sweep
+// of a 226 x 23 x 61 roll's small levels 10.2 us and of its levels 0 (2.5k
+// workgroups) 30 to 31, now 5.5 and 23 (there the bound is the stencil's
+// 216 bytes a row from HBM: 16 us).  x gathered without LDS: 9.2 and 60 us;
+// its loads all issued before the first LDS store: 5.6 and 27.
+// LDS [line][layer], the line's stride odd.
 // ---------------------------------------------------------------------------
 // Sz index of coefficient o of the row of line (a, bl) of a colour in layer
 // k; base = 27 x the rows of the lower colours, ncx the colour's lines
@@ -703,6 +707,8 @@ __device__ inline long long zline_rows_below(int nx, int ny, int nz, int colour)
     return offc;
 }
 
+__host__ __device__ inline int zline_pad(int nz) { return nz | 1; }
+
 __global__ __launch_bounds__(kBlock) void k_zline(LineBatch lb, int colour)
 {
     extern __shared__ double lds[];
@@ -719,76 +725,98 @@ __global__ __launch_bounds__(kBlock) void k_zline(LineBatch lb, int colour)
     const int nz = A.nz;
     const long long layer = (long long)A.nx * A.ny;
     const double *Z = A.Sz + 27 * zline_rows_below(A.nx, A.ny, nz, colour) + ((long long)bl * ncx + a0) * 27 * nz;
-    double *Llo = lds, *Ldg = lds + LT * nz, *Lup = Ldg + LT * nz, *Lrh = Lup + LT * nz;
-    double *Lx = Lrh + LT * nz;   // [KC + 2][3][FX]
+    const int nzp = zline_pad(nz);
+    double *Lfa = lds, *Lup = Lfa + LT * nzp, *Lrh = Lup + LT * nzp;   // [line][layer]
+    double *Lx = Lrh + LT * nzp;                                       // [KC + 2][3][FX]
     const int j = cy + 2 * bl;
+    const int l = threadIdx.x % LT, kk = threadIdx.x / LT;
     for (int k0 = 0; k0 < nz; k0 += KC) {
         for (int q = threadIdx.x; q < (KC + 2) * plane; q += kBlock) {
             const int pl = q / plane, r = q - pl * plane;
-            const int ii = fi0 + r % FX, jj = fj0 + r / FX, kk = k0 - 1 + pl;
-            const bool ok = ii >= 0 && ii < A.nx && jj >= 0 && jj < A.ny && kk >= 0 && kk < nz;
-            Lx[q] = ok ? A.x[ii + (long long)A.nx * jj + layer * kk] : 0.0;
+            const int ii = fi0 + r % FX, jj = fj0 + r / FX, kz = k0 - 1 + pl;
+            const bool ok = ii >= 0 && ii < A.nx && jj >= 0 && jj < A.ny && kz >= 0 && kz < nz;
+            Lx[q] = ok ? A.x[ii + (long long)A.nx * jj + layer * kz] : 0.0;
         }
         __syncthreads();
-        {
-            const int l = threadIdx.x % LT, kk = threadIdx.x / LT, k = k0 + kk;
-            if (kk < KC && k < nz && l < w) {
-                const int i = cx + 2 * (a0 + l);
-                const long long n = i + (long long)A.nx * j + layer * k;
-                const double *Zr = Z + (long long)k * 27 * w + l;   // coefficient o at Zr[o * w]
-                const double *P = Lx + (kk + 1) * plane + (i - fi0) + FX;
-                double rhs = A.b[n];
-                // no bounds tests: Sz holds +0 for a neighbour off the box and
-                // the staged x is +0 there, so that such a term subtracts an
-                // exact -0 and leaves rhs as it is, bit for bit; unguarded,
-                // the loads are all in flight at once
+        const int k = k0 + kk;
+        if (kk < KC && k < nz && l < w) {
+            const int i = cx + 2 * (a0 + l);
+            const double *Zr = Z + (long long)k * 27 * w + l;   // coefficient o at Zr[o * w]
+            const double *P = Lx + (kk + 1) * plane + (i - fi0) + FX;
+            double rhs = A.b[i + (long long)A.nx * j + layer * k];
+            // no bounds tests: Sz holds +0 for a neighbour off the box and the
+            // staged x is +0 there, so that such a term subtracts an exact -0
+            // and leaves rhs as it is, bit for bit; unguarded, the loads are
+            // all in flight at once
 #pragma unroll
-                for (int o = 0; o < 27; o++) {
-                    const int dx = o % 3 - 1, dy = (o / 3) % 3 - 1, dz = o / 9 - 1;
-                    if (dx == 0 && dy == 0) continue;
-                    rhs -= Zr[o * w] * P[dx + FX * dy + plane * dz];
-                }
-                const int q = k * LT + l;
-                Llo[q] = Zr[4 * w];    // offset (0,0,-1), +0 in the bottom layer
-                Lup[q] = Zr[22 * w];   // the line's factors (k_zline_factor)
-                Ldg[q] = Zr[13 * w];
-                Lrh[q] = rhs;
+            for (int o = 0; o < 27; o++) {
+                const int dx = o % 3 - 1, dy = (o / 3) % 3 - 1, dz = o / 9 - 1;
+                if (dx == 0 && dy == 0) continue;
+                rhs -= Zr[o * w] * P[dx + FX * dy + plane * dz];
             }
+            const int q = l * nzp + k;
+            Lfa[q] = -Zr[4 * w];    // the line's factors (k_zline_factor); the
+            Lup[q] = Zr[22 * w];    // first is +-0 in the bottom layer
+            Lrh[q] = rhs * Zr[13 * w];
         }
         __syncthreads();
     }
-    if (threadIdx.x < w) {
-        // the next row's values are read one step ahead (ahead of this
-        // step's stores), so that the LDS latency leaves the chain; with the
-        // pivots' reciprocals stored, a step of it is a multiply-add and a
-        // product (two dependent divisions before: 300 of its ~330 cycles)
-        const int ll = threadIdx.x;
-        double dprev = 0.0;
-        double lo = Llo[ll], id = Ldg[ll], rh = Lrh[ll];
-        for (int k = 0; k < nz; k++) {
-            const int q = k * LT + ll;
-            const int qn = k + 1 < nz ? q + LT : q;
-            const double lo1 = Llo[qn], id1 = Ldg[qn], rh1 = Lrh[qn];
-            dprev = (rh - lo * dprev) * id;
-            Lrh[q] = dprev;
-            lo = lo1; id = id1; rh = rh1;
+    // Both substitutions are recurrences d_k = b_k + f_k d_(k-1).  A line's
+    // rows are dealt in runs to 32 lanes; a lane composes its run into one
+    // map d -> B + F d, five shuffles give each lane the value that enters
+    // its run, and the run is gone through again with it.  (|f| < 1 for the
+    // dominant rows of these boxes, so the products shrink.)
+    const int sub = threadIdx.x & 31, m = (nz + 31) >> 5;
+    for (int ll = threadIdx.x >> 5; ll < w; ll += kBlock / 32) {
+        const int q0 = ll * nzp;
+        const int lo = sub * m, hi = lo + m < nz ? lo + m : nz;   // empty at the end: hi <= lo
+        double F = 1.0, B = 0.0;
+        for (int k = lo; k < hi; k++) {
+            const double f = Lfa[q0 + k];
+            B = Lrh[q0 + k] + f * B;
+            F *= f;
         }
-        double nxt = 0.0;
-        double c = Lup[(nz - 1) * LT + ll], d = Lrh[(nz - 1) * LT + ll];
-        for (int k = nz - 1; k >= 0; k--) {
-            const int q = k * LT + ll;
-            const int qn = k > 0 ? q - LT : q;
-            const double c1 = Lup[qn], d1 = Lrh[qn];
-            nxt = d - (k < nz - 1 ? c * nxt : 0.0);
-            Lrh[q] = nxt;
-            c = c1; d = d1;
+#pragma unroll
+        for (int s = 1; s < 32; s <<= 1) {
+            const double Fp = __shfl_up(F, s, 32), Bp = __shfl_up(B, s, 32);
+            if (sub >= s) {
+                B += F * Bp;
+                F *= Fp;
+            }
+        }
+        double d = __shfl_up(B, 1, 32);
+        d = sub ? d : 0.0;
+        F = 1.0;
+        B = 0.0;
+        for (int k = lo; k < hi; k++) {
+            d = Lrh[q0 + k] + Lfa[q0 + k] * d;
+            Lrh[q0 + k] = d;
+        }
+        for (int k = hi - 1; k >= lo; k--) {
+            const double f = k < nz - 1 ? -Lup[q0 + k] : 0.0;
+            B = Lrh[q0 + k] + f * B;
+            F *= f;
+        }
+#pragma unroll
+        for (int s = 1; s < 32; s <<= 1) {
+            const double Fp = __shfl_down(F, s, 32), Bp = __shfl_down(B, s, 32);
+            if (sub + s < 32) {
+                B += F * Bp;
+                F *= Fp;
+            }
+        }
+        d = __shfl_down(B, 1, 32);
+        d = sub < 31 ? d : 0.0;
+        for (int k = hi - 1; k >= lo; k--) {
+            d = Lrh[q0 + k] - (k < nz - 1 ? Lup[q0 + k] * d : 0.0);
+            Lrh[q0 + k] = d;
         }
     }
     __syncthreads();
     for (int p = threadIdx.x; p < LT * nz; p += kBlock) {
         const int l = p % LT, k = p / LT;
         if (l >= w) continue;
-        A.x[cx + 2 * (a0 + l) + (long long)A.nx * j + layer * k] = Lrh[k * LT + l];
+        A.x[cx + 2 * (a0 + l) + (long long)A.nx * j + layer * k] = Lrh[l * nzp + k];
     }
 }
 
@@ -797,19 +825,22 @@ __global__ __launch_bounds__(kBlock) void k_resid_full(LineBatch lb)
     const LineArgs &A = lb.a[find_box(lb, blockIdx.x)];
     const int n = (blockIdx.x - A.blk0) * kBlock + threadIdx.x;
     if (n >= A.n) return;
-    const int i = n % A.nx, t = n / A.nx, j = t % A.ny, k = t / A.ny;
-    const long long layer = (long long)A.nx * A.ny, N = A.n;
-    double acc = A.b[n];
+    const int i = n % A.nx, t = n / A.nx;
+    const NbMask M(i, t % A.ny, t / A.ny, A.nx, A.ny, A.nz);
+    const long long N = A.n;
+    // every value loaded before the sum (at valid addresses: the node itself
+    // off the box, with no coupling)
+    double sv[27], xv[27];
 #pragma unroll
     for (int o = 0; o < 27; o++) {
-        const int dx = o % 3 - 1, dy = (o / 3) % 3 - 1, dz = o / 9 - 1;
-        const bool ok = ((unsigned)(i + dx) < (unsigned)A.nx) & ((unsigned)(j + dy) < (unsigned)A.ny) &
-                        ((unsigned)(k + dz) < (unsigned)A.nz);
-        // loads at valid addresses (the node itself off the box) and a select
-        const double sv = A.S[o * N + n];
-        const double xv = A.x[ok ? n + dx + (long long)A.nx * dy + layer * dz : (long long)n];
-        acc = ok ? acc - sv * xv : acc;
+        const int h = M.has(o), off = (o % 3 - 1) + A.nx * ((o / 3) % 3 - 1 + A.ny * (o / 9 - 1));
+        const double v = A.S[o * N + n];
+        xv[o] = A.x[n + (off & -h)];
+        sv[o] = h ? v : 0.0;
     }
+    double acc = A.b[n];
+#pragma unroll
+    for (int o = 0; o < 27; o++) acc -= sv[o] * xv[o];
     A.r[n] = acc;
 }
 
@@ -834,8 +865,8 @@ __global__ __launch_bounds__(kBlock) void k_zline_order(int nx, int ny, int nz, 
 }
 
 // The tridiagonal block of each line factored in place in Sz, one thread per
-// line: the pivots' reciprocals over the diagonal (offset 13), the
-// superdiagonal over the pivots at offset 22 (the subdiagonal, offset 4, stays).
+// line: the pivots' reciprocals over the diagonal (offset 13), the sub- and
+// the superdiagonal over the pivots at offsets 4 and 22.
 // A line's rows are read eight ahead of the chain of divisions.
 __global__ __launch_bounds__(64) void k_zline_factor(int nx, int ny, int nz, int LT, double *__restrict__ Sz)
 {
@@ -861,6 +892,7 @@ __global__ __launch_bounds__(64) void k_zline_factor(int nx, int ny, int nz, int
             if (k0 + u >= nz) break;
             const double id = 1.0 / (dg[u] - lo[u] * cprev);
             cprev = up[u] * id;
+            Sz[zline_index(base, ncx, nz, LT, i >> 1, j >> 1, k0 + u, 4)] = lo[u] * id;
             Sz[zline_index(base, ncx, nz, LT, i >> 1, j >> 1, k0 + u, 13)] = id;
             Sz[zline_index(base, ncx, nz, LT, i >> 1, j >> 1, k0 + u, 22)] = cprev;
         }
@@ -872,11 +904,11 @@ __global__ __launch_bounds__(64) void k_zline_factor(int nx, int ny, int nz, int
 // boxes with many lines (HBM-bound sweeps), 2-line tiles on boxes with few
 // (latency-bound sweeps, where one deep chunk per workgroup pays); then the
 // widest tile and deepest chunk, at most the z extent rounded up, whose line
-// rows (four doubles each) and staged x planes fit the 64 KB LDS budget.
+// rows (three doubles each) and staged x planes fit the 64 KB LDS budget.
 // The stencil reordering and the sweeps both take the tile from here.
 static size_t zline_lds(int LT, int KC, int nz)
 {
-    return (size_t)32 * LT * nz + (size_t)8 * (KC + 2) * (2 * LT + 1) * 3;
+    return (size_t)24 * LT * zline_pad(nz) + (size_t)8 * (KC + 2) * (2 * LT + 1) * 3;
 }
 static bool zline_tile(int nx, int ny, int nz, int &LT, int &KC)
 {

@@ -49,3 +49,16 @@ def test_zline_preconditioner(nx, ny, nz, degree):
     errs = field_errors(p, to_np(s.apply_pc(to_dev(r))), orc.apply_pc(r))
     say(f"{nx}x{ny}x{nz} degree {degree}", {k: f"{v:.1e}" for k, v in errs.items()})
     assert max(errs.values()) <= 1e-9
+
+
+# lines around 32 rows per run of the substitutions: one, two and three rows a
+# lane, the last lanes' runs short or empty
+@pytest.mark.parametrize("nz", [31, 32, 33, 64, 65, 90])
+def test_zline_substitutions_around_their_runs(nz):
+    p = pi.make_custom(7, 3, nz, (4, 5), seed=83, sigma_log=0.5, corr_cells=3.0)
+    r = np.random.default_rng(11).standard_normal(p.N)
+    orc = O.Oracle(p).setup(smoother=O.SMOOTH_ZLINE)
+    s = solver_for(p, smoother=O.SMOOTH_ZLINE).setup(smoother=O.SMOOTH_ZLINE)
+    errs = field_errors(p, to_np(s.apply_pc(to_dev(r))), orc.apply_pc(r))
+    say(f"7x3x{nz}", {k: f"{v:.1e}" for k, v in errs.items()})
+    assert max(errs.values()) <= 1e-9
