@@ -57,15 +57,8 @@ __global__ __launch_bounds__(kBlock) void k_bgs_rhs(Geom g, BgsArgs B, const dou
                              : (f == BF_PHIE && (done & (1 << BF_CE)));
     if (kterm) {
         double ck[8], X[27];
-#pragma unroll
-        for (int e = 0; e < 8; e++) {
-            const int ei = i - 1 + (e & 1), ej2 = j - 1 + ((e >> 1) & 1), ek = k - 1 + ((e >> 2) & 1);
-            const bool ok = ei >= 0 && ej2 >= 0 && ek >= 0 && ei < g.nx - 1 && ej2 < g.ny - 1 &&
-                            ek < g.nz - 1;
-            const long long id = ei + (long long)(g.nx - 1) * (ej2 + (long long)(g.ny - 1) * ek);
-            ck[e] = ok ? B.kx[id] : 0.0;
-        }
-        load_nb(g, TRANS ? R.x0[2] + g.off_pe : R.x0[3] + g.off_ce, n, i, j, k, X);
+        NodeElems(g, i, j, k).load(B.kx, ck);
+        load_nb(g, TRANS ? R.x0[2] + g.off_pe : R.x0[3] + g.off_ce, n, NbMask(i, j, k, g.nx, g.ny, g.nz), X);
         t -= B.kx_scale * q1_stiff(ck, X);
     }
     const T bt = (T)t;

@@ -871,18 +871,47 @@ __device__ inline void fold_surface(const Geom &g, const OpArgs &O, const Tab &T
 template <typename TX>
 __device__ inline double ldx(const TX *p) { return (double)*p; }
 
+// The node's neighbourhood in f, absent neighbours as zeros.  An absent
+// neighbour's index is clamped to the node and its value dropped by a select,
+// so that the loads are in flight together (bounds tests around them became
+// branches, with one wait per load).
 template <typename TX>
-__device__ inline void load_nb(const Geom &g, const TX *f, long long n, int i, int j, int k,
-                               double X[27])
+__device__ inline void load_nb(const Geom &g, const TX *f, long long n, const NbMask &M, double X[27])
 {
+    const TX *fn = f + n;
 #pragma unroll
-    for (int o = 0; o < 27; o++) {
-        const int dx = o % 3 - 1, dy = (o / 3) % 3 - 1, dz = o / 9 - 1;
-        const bool ok = (i + dx >= 0) && (i + dx < g.nx) && (j + dy >= 0) && (j + dy < g.ny) &&
-                        (k + dz >= 0) && (k + dz < g.nz);
-        X[o] = ok ? ldx(f + n + dx + (long long)g.nx * (dy + (long long)g.ny * dz)) : 0.0;
-    }
+    for (int o = 0; o < 27; o++)
+        X[o] = ldx(fn + (((o % 3 - 1) + g.nx * ((o / 3) % 3 - 1 + g.ny * (o / 9 - 1))) & -M.has(o)));
+#pragma unroll
+    for (int o = 0; o < 27; o++) X[o] = M.has(o) ? X[o] : 0.0;
 }
+
+// The eight elements of a node (e = ex + 2 ey + 4 ez, ex: the upper one along
+// x), absent ones clamped to one that is there
+struct NodeElems {
+    unsigned x, y, z;
+    int ix[2], iy[2], iz[2];
+    __device__ NodeElems(const Geom &g, int i, int j, int k)
+        : x((i > 0 ? 1u : 0u) | (i < g.nx - 1 ? 2u : 0u)), y((j > 0 ? 1u : 0u) | (j < g.ny - 1 ? 2u : 0u)),
+          z((k > 0 ? 1u : 0u) | (k < g.nz - 1 ? 2u : 0u))
+    {
+        ix[0] = i > 0 ? i - 1 : 0;
+        ix[1] = i < g.nx - 1 ? i : i - 1;
+        iy[0] = (g.nx - 1) * (j > 0 ? j - 1 : 0);
+        iy[1] = (g.nx - 1) * (j < g.ny - 1 ? j : j - 1);
+        iz[0] = (g.nx - 1) * (g.ny - 1) * (k > 0 ? k - 1 : 0);
+        iz[1] = (g.nx - 1) * (g.ny - 1) * (k < g.nz - 1 ? k : k - 1);
+    }
+    __device__ int has(int e) const { return (x >> (e & 1)) & (y >> ((e >> 1) & 1)) & (z >> (e >> 2)) & 1u; }
+    __device__ int id(int e) const { return ix[e & 1] + iy[(e >> 1) & 1] + iz[e >> 2]; }
+    __device__ void load(const double *C, double c[8]) const
+    {
+#pragma unroll
+        for (int e = 0; e < 8; e++) c[e] = C[id(e)];
+#pragma unroll
+        for (int e = 0; e < 8; e++) c[e] = has(e) ? c[e] : 0.0;
+    }
+};
 
 // Stencil parts of the operator at one node, gathered either per node from
 // memory or from an LDS tile: K_kappa phi_e, K_kappa c_e, M_eps c_e and, on
@@ -903,37 +932,66 @@ struct OpStencil {
 // phi_e and c_e on the element's corners.  Xc: the input's c_e around the
 // node (the forward form).  (K_e u)_a = sum_{b != a} kw[a^b] (u_a - u_b).
 template <typename TX, bool TRANS>
-__device__ inline void newton_terms(const Geom &g, const TX *x, long long n, int i, int j, int k,
-                                    const double Xc[27], OpStencil &P)
+__device__ inline void newton_terms(const Geom &g, const TX *x, long long n, int i, int j, int k, const NbMask &M,
+                                    const NodeElems &E, const double Xc[27], OpStencil &P)
 {
     const double *up = g.nwu + g.off_pe, *uc = g.nwu + g.off_ce;
-    const long long layer = (long long)g.nx * g.ny;
     double npe = 0.0, nce = 0.0;
-    for (int e = 0; e < 8; e++) {
-        const int ex = e & 1, ey = (e >> 1) & 1, ez = (e >> 2) & 1;
-        const int ei = i - 1 + ex, ej = j - 1 + ey, ek = k - 1 + ez;
-        if (ei < 0 || ej < 0 || ek < 0 || ei >= g.nx - 1 || ej >= g.ny - 1 || ek >= g.nz - 1) continue;
-        const long long id = ei + (long long)(g.nx - 1) * (ej + (long long)(g.ny - 1) * ek);
-        // corner b of the element is node n + off(b); this node is corner a
-        const long long c0 = ei + (long long)g.nx * ej + layer * ek;
-        auto node = [&](int b) { return c0 + (b & 1) + (long long)g.nx * ((b >> 1) & 1) + layer * ((b >> 2) & 1); };
-        const double A = g.nwa[id], B = g.nwb[id], C = g.nwc[id];
-        if (!TRANS) {
-            const int a = (1 - ex) | ((1 - ey) << 1) | ((1 - ez) << 2);
-            double sp = 0.0, sc = 0.0, xm = 0.0;
-            const double upa = up[n], uca = uc[n];
-            for (int b = 0; b < 8; b++) {
-                xm += Xc[nb_index(ex - 1 + (b & 1), ey - 1 + ((b >> 1) & 1), ez - 1 + ((b >> 2) & 1))];
-                if (b == a) continue;
-                const long long nb = node(b);
-                const double w = g.kw[a ^ b];
-                sp += w * (upa - up[nb]);
-                sc += w * (uca - uc[nb]);
+    if (!TRANS) {
+        // one 27-value neighbourhood at a time: the means of x_ce, then the
+        // sums over the state's phi_e, then those over its c_e.  An absent
+        // element's coefficients are zeros, and so are its terms.
+        double xm[8], sp[8], sc[8], U[27];
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+            xm[e] = 0.0;
+#pragma unroll
+            for (int b = 0; b < 8; b++)
+                xm[e] += Xc[nb_index((e & 1) - 1 + (b & 1), ((e >> 1) & 1) - 1 + ((b >> 1) & 1), (e >> 2) - 1 + (b >> 2))];
+            xm[e] *= 0.125;
+        }
+        auto sums = [&](double s[8]) {
+#pragma unroll
+            for (int e = 0; e < 8; e++) {
+                const int a = e ^ 7;   // this node's corner of the element
+                s[e] = 0.0;
+#pragma unroll
+                for (int b = 0; b < 8; b++)
+                    if (b != a)
+                        s[e] += g.kw[a ^ b] * (U[13] - U[nb_index((e & 1) - 1 + (b & 1), ((e >> 1) & 1) - 1 + ((b >> 1) & 1),
+                                                                  (e >> 2) - 1 + (b >> 2))]);
             }
-            xm *= 0.125;
-            npe += (A * sp + B * sc) * xm;
-            nce += C * sc * xm;
-        } else {
+        };
+        // (finished before the next loads, as in operator_node)
+        auto done = [](double v[8]) {
+            __asm__ volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]),
+                             "+v"(v[7]) : : "memory");
+        };
+        done(xm);
+        load_nb(g, up, n, M, U);
+        sums(sp);
+        done(sp);
+        load_nb(g, uc, n, M, U);
+        sums(sc);
+        done(sc);
+        double A[8], B[8], C[8];
+        E.load(g.nwa, A);
+        E.load(g.nwb, B);
+        E.load(g.nwc, C);
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+            npe += (A[e] * sp[e] + B[e] * sc[e]) * xm[e];
+            nce += C[e] * sc[e] * xm[e];
+        }
+    } else {
+        const long long layer = (long long)g.nx * g.ny;
+        for (int e = 0; e < 8; e++) {
+            if (!E.has(e)) continue;
+            const int id = E.id(e);
+            const double A = g.nwa[id], B = g.nwb[id], C = g.nwc[id];
+            // corner b of the element
+            const long long c0 = (i - 1 + (e & 1)) + (long long)g.nx * (j - 1 + ((e >> 1) & 1)) + layer * (k - 1 + (e >> 2));
+            auto node = [&](int b) { return c0 + (b & 1) + (long long)g.nx * ((b >> 1) & 1) + layer * ((b >> 2) & 1); };
             double t = 0.0;
             for (int a = 0; a < 8; a++) {
                 const long long na = node(a);
@@ -1101,88 +1159,65 @@ __device__ inline double operator_node(const Geom &g, const OpArgs &O, long long
     const int i = (int)(n % g.nx);
     const long long t = n / g.nx;
     const int j = (int)(t % g.ny), k = (int)(t / g.ny);
+    const NbMask M(i, j, k, g.nx, g.ny, g.nz);
+    const NodeElems E(g, i, j, k);
     // element coefficients of the node's eight elements; each set is read
     // beside the neighbourhood that uses it, so only one set is live at a time
-    auto elem_of = [&](const double *C, double c[8]) {
-#pragma unroll
-        for (int e = 0; e < 8; e++) {
-            const int ei = i - 1 + (e & 1), ej = j - 1 + ((e >> 1) & 1), ek = k - 1 + ((e >> 2) & 1);
-            const bool ok = ei >= 0 && ej >= 0 && ek >= 0 && ei < g.nx - 1 && ej < g.ny - 1 &&
-                            ek < g.nz - 1;
-            c[e] = ok ? C[ei + (long long)(g.nx - 1) * (ej + (long long)(g.ny - 1) * ek)] : 0.0;
-        }
-    };
     double ck[8], cs[8], cm[8];
-    elem_of(O.kaph, ck);
+    E.load(O.kaph, ck);
     OpStencil P;
     double X[27];
     P.Kx = 0.0;
-    load_nb(g, x + g.off_pe, n, i, j, k, X);
+    load_nb(g, x + g.off_pe, n, M, X);
     P.Kpe = stiff_of<GEN>(g, ck, X);
     P.xpe = X[13];
     if (GEN && TRANS) {
         double cx[8];
-#pragma unroll
-        for (int e = 0; e < 8; e++) {
-            const int ei = i - 1 + (e & 1), ej = j - 1 + ((e >> 1) & 1), ek = k - 1 + ((e >> 2) & 1);
-            const bool ok = ei >= 0 && ej >= 0 && ek >= 0 && ei < g.nx - 1 && ej < g.ny - 1 &&
-                            ek < g.nz - 1;
-            cx[e] = ok ? O.kdh[ei + (long long)(g.nx - 1) * (ej + (long long)(g.ny - 1) * ek)] : 0.0;
-        }
+        E.load(O.kdh, cx);
         P.Kx = stiff_of<GEN>(g, cx, X);
     }
     // an empty statement that takes the finished sums: they may not be
     // deferred past it nor the next neighbourhood's loads hoisted above it,
     // so one 27-value neighbourhood is live at a time (register use)
     __asm__ volatile("" : "+v"(P.Kpe), "+v"(P.Kx) : : "memory");
-    load_nb(g, x + g.off_ce, n, i, j, k, X);
+    load_nb(g, x + g.off_ce, n, M, X);
     if (GEN) {
         double cd[8], cx[8];
-#pragma unroll
-        for (int e = 0; e < 8; e++) {
-            const int ei = i - 1 + (e & 1), ej = j - 1 + ((e >> 1) & 1), ek = k - 1 + ((e >> 2) & 1);
-            const bool ok = ei >= 0 && ej >= 0 && ek >= 0 && ei < g.nx - 1 && ej < g.ny - 1 &&
-                            ek < g.nz - 1;
-            const long long id = ei + (long long)(g.nx - 1) * (ej + (long long)(g.ny - 1) * ek);
-            cd[e] = ok ? O.dch[id] : 0.0;
-            cx[e] = (ok && !TRANS) ? O.kdh[id] : 0.0;
-        }
+        E.load(O.dch, cd);
         P.Kce = stiff_of<GEN>(g, cd, X);
-        if (!TRANS) P.Kx = stiff_of<GEN>(g, cx, X);
+        if (!TRANS) {
+            E.load(O.kdh, cx);
+            P.Kx = stiff_of<GEN>(g, cx, X);
+        }
     } else {
         P.Kce = stiff_of<GEN>(g, ck, X);
     }
+    // per-element storage only with separate coefficients (GEN)
+    if (GEN && g.meh) {
+        E.load((const double *)(const __attribute__((address_space(1))) double *)g.meh, cm);
+    } else {
 #pragma unroll
-    for (int e = 0; e < 8; e++) {
-        const int ei = i - 1 + (e & 1), ej = j - 1 + ((e >> 1) & 1), ek = k - 1 + ((e >> 2) & 1);
-        const bool ok = ei >= 0 && ej >= 0 && ek >= 0 && ei < g.nx - 1 && ej < g.ny - 1 &&
-                        ek < g.nz - 1;
-        const long long id = ei + (long long)(g.nx - 1) * (ej + (long long)(g.ny - 1) * ek);
-        // per-element storage only with separate coefficients (GEN)
-        cm[e] = ok ? (GEN ? elem_storage(g, id, ek) : (elem_mat(g, ek) >= 0 ? g.mass_elec : g.mass_sep))
-                   : 0.0;
+        for (int e = 0; e < 8; e++)
+            cm[e] = E.has(e) ? (elem_mat(g, k - 1 + (e >> 2)) >= 0 ? g.mass_elec : g.mass_sep) : 0.0;
     }
     P.Mce = q1_mass(cm, X);
     P.xce = X[13];
-    if (GEN && g.nwu) newton_terms<TX, TRANS>(g, x, n, i, j, k, X, P);
+    if (GEN) __asm__ volatile("" : "+v"(P.Kce), "+v"(P.Mce), "+v"(P.Kx) : : "memory");
+    if (GEN && g.nwu) newton_terms<TX, TRANS>(g, x, n, i, j, k, M, E, X, P);
     __asm__ volatile("" : "+v"(P.Kce), "+v"(P.Mce), "+v"(P.Kx), "+v"(P.Npe), "+v"(P.Nce) : : "memory");
     P.Kps = 0.0;
     P.xpsc = 0.0;
     const int el = node_mat(g, k);
     if (el >= 0) {
-        elem_of(O.sigh, cs);
+        E.load(O.sigh, cs);
         const long long base = el == 0 ? 0 : g.nea;
         const int klo = el == 0 ? 0 : g.na + g.ns;
         const int khi = el == 0 ? g.na - 1 : g.nz - 1;
         const long long je = base + i + (long long)g.nx * (j + (long long)g.ny * (k - klo));
         // phi_s neighbours: same electrode, grounded layer as a zero column
-#pragma unroll
-        for (int o = 0; o < 27; o++) {
-            const int dx = o % 3 - 1, dy = (o / 3) % 3 - 1, dz = o / 9 - 1;
-            const bool ok = (i + dx >= 0) && (i + dx < g.nx) && (j + dy >= 0) && (j + dy < g.ny) &&
-                            (k + dz >= klo) && (k + dz <= khi) && (k + dz != 0);
-            X[o] = ok ? ldx(x + je + dx + (long long)g.nx * (dy + (long long)g.ny * dz)) : 0.0;
-        }
+        NbMask S = M;
+        S.z = (k > klo && k != 1 ? 1u : 0u) | (k != 0 ? 2u : 0u) | (k < khi ? 4u : 0u);
+        load_nb(g, x, je, S, X);
         P.Kps = stiff_of<GEN>(g, cs, X);
         P.xpsc = X[13];
     }
