@@ -613,10 +613,10 @@ __global__ __launch_bounds__(kBlock) void k_bmdot(const BCell *__restrict__ cell
     for (int q = 0; q < KMAX; q++) acc[q] = 0.0;
     for (long long i = (long long)lb * kBlock + threadIdx.x; i < N; i += (long long)nb * kBlock) {
         const double wi = w[i];
-        const double *p0 = v0 + fold_at(M, i);
+        double v[KMAX];
+        basis_row<KMAX>(v0, M, V, N, nv, i, v);
 #pragma unroll
-        for (int q = 0; q < KMAX; q++)
-            if (q < nv) acc[q] += wi * *(q == 0 ? p0 : V + (long long)q * N + i);
+        for (int q = 0; q < KMAX; q++) acc[q] += wi * v[q];
     }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
@@ -678,10 +678,10 @@ __global__ __launch_bounds__(kBlock) void k_borth(const BCell *__restrict__ cell
     double sq = 0.0;
     for (long long i = (long long)lb * kBlock + threadIdx.x; i < N; i += (long long)nb * kBlock) {
         double wi = w[i];
-        const double *p0 = v0 + fold_at(M, i);
+        double v[KMAX];
+        basis_row<KMAX>(v0, M, V, N, nv, i, v);
 #pragma unroll
-        for (int q = 0; q < KMAX; q++)
-            if (q < nv) wi -= cq[q] * *(q == 0 ? p0 : V + (long long)q * N + i);
+        for (int q = 0; q < KMAX; q++) wi -= cq[q] * v[q];
         w[i] = wi;
         sq += wi * wi;
     }

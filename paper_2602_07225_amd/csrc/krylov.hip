@@ -29,10 +29,10 @@ __global__ __launch_bounds__(kBlock) void k_mdot(long long n, const double *__re
     const long long stride = (long long)gridDim.x * kBlock;
     for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) {
         const double wi = w[i];
-        const double *p0 = v0 + fold_at(M, i);
+        double v[KMAX];
+        basis_row<KMAX>(v0, M, V, ldv, nv, i, v);
 #pragma unroll
-        for (int q = 0; q < KMAX; q++)
-            if (q < nv) acc[q] += wi * *(q == 0 ? p0 : V + (long long)q * ldv + i);
+        for (int q = 0; q < KMAX; q++) acc[q] += wi * v[q];
     }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
@@ -109,10 +109,10 @@ __global__ __launch_bounds__(kBlock) void k_orth(long long n, double *__restrict
     const long long stride = (long long)gridDim.x * kBlock;
     for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) {
         double wi = w[i];
-        const double *p0 = v0 + fold_at(M, i);
+        double v[KMAX];
+        basis_row<KMAX>(v0, M, V, ldv, nv, i, v);
 #pragma unroll
-        for (int q = 0; q < KMAX; q++)
-            if (q < nv) wi -= cq[q] * *(q == 0 ? p0 : V + (long long)q * ldv + i);
+        for (int q = 0; q < KMAX; q++) wi -= cq[q] * v[q];
         w[i] = wi;
         sq += wi * wi;
     }
