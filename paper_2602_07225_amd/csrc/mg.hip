@@ -92,6 +92,26 @@ __global__ __launch_bounds__(kBlock) void k_prolong(TransferBatch<T> tb)
     const int bx = find_box(tb, blockIdx.x);
     prolong_block<T>(tb.a[bx], blockIdx.x - tb.a[bx].blk0);
 }
+// (lb and tb hold the same boxes)
+template <typename T>
+__global__ __launch_bounds__(kFineThreads) void k_prolong_smooth(LevelBatch<T> lb, TransferBatch<T> tb)
+{
+    __shared__ double lds[kFineHalo];
+    const int bx = find_box(lb, blockIdx.x);
+    prolong_smooth_block<T>(lb.a[bx], tb.a[bx], blockIdx.x - lb.a[bx].blk0, lds);
+}
+template <typename T>
+void launch_prolong_smooth(LevelBatch<T> lb, const TransferBatch<T> &tb, hipStream_t st)
+{
+    int blk = 0;
+    for (int q = 0; q < lb.nbox; q++) {
+        lb.a[q].blk0 = blk;
+        blk += fine_tiles(lb.a[q].nx, lb.a[q].ny, lb.a[q].nz);
+    }
+    hipLaunchKernelGGL((k_prolong_smooth<T>), dim3(blk), dim3(kFineThreads), 0, st, lb, tb);
+}
+template void launch_prolong_smooth<double>(LevelBatch<double>, const TransferBatch<double> &, hipStream_t);
+template void launch_prolong_smooth<float>(LevelBatch<float>, const TransferBatch<float> &, hipStream_t);
 template <typename T>
 void launch_restrict(const TransferBatch<T> &tb, int nblk, hipStream_t st)
 {

@@ -641,10 +641,11 @@ static PStage<T> &rec_stage(p4d_ctx *c, int kind, int nunits)
 }
 
 // grp: the event pair of the level-0 steps it belongs to (or null: a pair
-// of its own)
+// of its own); corr (l >= 1): the coarse correction is added first
 template <typename T>
 static void smooth_step(p4d_ctx *c, VState<T> &vs, int l, const int *boxes, int nb, int step,
-                        int post, hipStream_t st, ProfScope *grp = nullptr)
+                        int post, hipStream_t st, ProfScope *grp = nullptr,
+                        const TransferBatch<T> *corr = nullptr)
 {
     // step index t (1-based); post-smoothing step 1 starts from a nonzero x
     LevelBatch<T> lb{};
@@ -700,6 +701,8 @@ static void smooth_step(p4d_ctx *c, VState<T> &vs, int l, const int *boxes, int 
             ProfScope ps(c->prof, P4D_K_SMOOTH0, bytes, st);
             launch_smooth0<T>(c->g, lb, blk, 0, c->tile_tx, c->tile_cz, st);
         }
+    } else if (corr) {
+        launch_prolong_smooth<T>(lb, *corr, st);
     } else {
         launch_smooth<T>(lb, blk, 0, st);
     }
@@ -875,6 +878,14 @@ static void vcycle_rest(p4d_ctx *c, VState<T> &vs, int l, int *act, int na, hipS
         else launch_restrict<T>(tb, blk, st);
     }
     vcycle_level<T>(c, vs, l + 1, st);
+    // on a small level the correction and the first smoothing step are one
+    // launch (the batched stages stay apart)
+    int tiles = 0;
+    for (int q = 0; q < na; q++) {
+        const Level &F = c->box[act[q]].lev[l];
+        tiles += fine_tiles(F.nx, F.ny, F.nz);
+    }
+    const bool fused = l >= 1 && !c->rec && tiles <= kFineTiles;
     {   // prolongation and correction
         TransferBatch<T> tb{};
         tb.nbox = na;
@@ -891,11 +902,12 @@ static void vcycle_rest(p4d_ctx *c, VState<T> &vs, int l, int *act, int na, hipS
             A.xf = lvx(F, vs.xcur[act[q]][l]);
         }
         if (c->rec) rec_stage<T>(c, SK_PROLONG, blk).u.tb = tb;
+        else if (fused) smooth_step<T>(c, vs, l, act, na, 1, 1, st, nullptr, &tb);
         else launch_prolong<T>(tb, blk, st);
     }
     {
         ProfScope grp(c->prof, P4D_K_SMOOTH0, 0.0, st, grouped ? deg : 0);
-        for (int t = 1; t <= deg; t++) smooth_step<T>(c, vs, l, act, na, t, 1, st, grouped ? &grp : nullptr);
+        for (int t = fused ? 2 : 1; t <= deg; t++) smooth_step<T>(c, vs, l, act, na, t, 1, st, grouped ? &grp : nullptr);
     }
 }
 

@@ -233,6 +233,10 @@ template <typename T>
 void launch_restrict(const TransferBatch<T> &tb, int nblk, hipStream_t st);
 template <typename T>
 void launch_prolong(const TransferBatch<T> &tb, int nblk, hipStream_t st);
+// levels >= 1: the smoothing step lb (c1 = 0) from x = lb's xin + P x_c (tb;
+// its xf is not used)
+template <typename T>
+void launch_prolong_smooth(LevelBatch<T> lb, const TransferBatch<T> &tb, hipStream_t st);
 template <typename T>
 void launch_coarse(const CoarseBatch<T> &cb, hipStream_t st);
 template <typename T>

@@ -422,6 +422,69 @@ __device__ inline void prolong_block(const TransferArgs<T> &A, int blk)
     A.xf[n] += prolong_value(A.fx, A.fy, A.fz, A.cz == A.fz, i, j, k, A.xc, A.cx, A.cx * A.cy);
 }
 
+// Prolongation and the first post-smoothing step of small levels >= 1 in one
+// pass: a workgroup forms x + P x_c on a tile of 8 x 8 x 4 nodes and the nodes
+// around it in LDS, a thread each, and smooths the tile; the arithmetic is
+// that of the two stages, bit for bit.  The two launches are bound by launch
+// and latency on small levels: 3.2 to 4.0 + 4.3 to 4.6 us up to 100
+// workgroups, 5.1 to 5.8 in one; with the two rounds of workgroups that the
+// chip takes (a workgroup a CU, 119 registers and ten waves) 4 + 4.8 and 7.7;
+// with three 5 + 6.5 and 14.0, since 344 of 600 nodes are formed once more by
+// each neighbour: kFineTiles ends at two.  (The residual with the restriction
+// in the same way took 6.9 to 9.4 us against 8: left apart.)
+constexpr int kFineTiles = 512;
+constexpr int kFineX = 8, kFineY = 8, kFineZ = 4;
+constexpr int kFineThreads = 640;     // a node with halo each, the first 256 smooth
+constexpr int kFineHalo = (kFineX + 2) * (kFineY + 2) * (kFineZ + 2);
+__host__ __device__ inline int fine_tiles(int nx, int ny, int nz)
+{
+    return ((nx + kFineX - 1) / kFineX) * ((ny + kFineY - 1) / kFineY) * ((nz + kFineZ - 1) / kFineZ);
+}
+template <typename T>
+__device__ inline void prolong_smooth_block(const LevelArgs<T> &A, const TransferArgs<T> &R, int tile, double *lds)
+{
+    const int tx = (A.nx + kFineX - 1) / kFineX, ty = (A.ny + kFineY - 1) / kFineY;
+    const int i0 = tile % tx * kFineX, j0 = tile / tx % ty * kFineY, k0 = tile / tx / ty * kFineZ;
+    const int i = i0 + threadIdx.x % kFineX, j = j0 + threadIdx.x / kFineX % kFineY,
+              k = k0 + threadIdx.x / (kFineX * kFineY);
+    const bool own = threadIdx.x < kFineX * kFineY * kFineZ && i < A.nx && j < A.ny && k < A.nz;
+    const int n = own ? i + A.nx * (j + A.ny * k) : 0;
+    const NbMask M(i, j, k, A.nx, A.ny, A.nz);
+    // the couplings are on their way while x is formed
+    T sv[27];
+    if (own) {
+#pragma unroll
+        for (int o = 0; o < 27; o++) {
+            const int h = M.has(o), nbr = n + (((o % 3 - 1) + A.nx * ((o / 3) % 3 - 1 + A.ny * (o / 9 - 1))) & -h);
+            sv[o] = o >= 13 ? A.S[(long long)(o - 13) * A.n + n] : A.S[(long long)(13 - o) * A.n + nbr];
+        }
+    }
+    const double bn = own ? (double)A.b[n] : 0.0, idn = own ? (double)A.invd[n] : 0.0;
+    constexpr int HX = kFineX + 2, HY = kFineY + 2;
+    const int q = threadIdx.x;
+    if (q < kFineHalo) {
+        const int ii = i0 - 1 + q % HX, jj = j0 - 1 + q / HX % HY, kk = k0 - 1 + q / (HX * HY);
+        double v = 0.0;
+        if (ii >= 0 && ii < A.nx && jj >= 0 && jj < A.ny && kk >= 0 && kk < A.nz) {
+            v = A.xin[ii + A.nx * (jj + A.ny * kk)];
+            v += prolong_value(A.nx, A.ny, A.nz, R.cz == A.nz, ii, jj, kk, R.xc, R.cx, R.cx * R.cy);
+        }
+        lds[q] = v;
+    }
+    __syncthreads();
+    if (!own) return;
+    double xv[27];
+    const double *P = lds + (i - i0 + 1) + HX * ((j - j0 + 1) + HY * (k - k0 + 1));
+#pragma unroll
+    for (int o = 0; o < 27; o++) {
+        xv[o] = P[(o % 3 - 1) + HX * ((o / 3) % 3 - 1 + HY * (o / 9 - 1))];
+        sv[o] = M.has(o) ? sv[o] : T(0);
+    }
+    const double d = cheb_dir(A.c1, A.c2, idn, bn - stencil_row(sv, xv), 0.0);   // c1 = 0 in the first step
+    A.xout[n] = xv[13] + d;
+    if (A.dout) A.dout[n] = (T)d;
+}
+
 // Coarsest level, 64 rows of x = A^-1 b per workgroup (FP64); the 4 waves
 // split the columns, then add up.
 struct CoarseLds {

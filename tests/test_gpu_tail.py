@@ -35,3 +35,12 @@ def test_equals_the_stages_one_by_one(dims, degree, pc_prec):
     assert ib.iters == i1.iters and ib.status == i1.status
     assert np.any(to_np(x1)) and np.array_equal(to_np(xb[:]), to_np(x1))
     B.close()
+
+
+# levels between the finest and the tail: the correction and the first
+# post-smoothing step in one launch, tiles of 8 x 8 x 4 nodes with remainders
+# of one node, of all but one, and none; a two-point axis
+@pytest.mark.parametrize("dims", [(33, 17, 66), (30, 31, 47), (2, 70, 90)])
+@pytest.mark.parametrize("degree,pc_prec", [(1, 0), (2, 0), (3, 1)])
+def test_corrected_and_smoothed_at_once_equals_the_stages(dims, degree, pc_prec):
+    test_equals_the_stages_one_by_one(dims, degree, pc_prec)
