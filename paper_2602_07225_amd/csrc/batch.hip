@@ -190,42 +190,40 @@ __global__ __launch_bounds__(kBlock) void k_bstage_sm0(StageRun run)
     else smooth0_tile<T, true>(g, A, u.unit - A.blk0, TX, CZ, lds);
 }
 
-template <typename T>
+// Stages of the coarse levels.  KINDS: the kinds in the list, one bit each (1
+// << kind); a list of one kind runs the kernel of that kind, whose registers
+// are its own: with the smoothing step's 136 only three workgroups fit a CU,
+// and the prolongation to the finest level, short workgroups that first look
+// up their unit, is bound by the workgroups in flight (16 cells, 25.6k of them:
+// 55 -> 38 us; the level above, 3.6k: 20 -> 8).
+constexpr int kAllKinds = ~0;
+template <typename T, int KINDS>
 __global__ __launch_bounds__(kBlock) void k_bstage_misc(StageRun run)
 {
-    __shared__ CoarseLds lds;
     const UnitRef u = unit_of(run);
     Ctab<PStage<T>> &S = ctab((const PStage<T> *)run.stages)[u.si];
     if (!((run.active >> S.cell) & 1ULL)) return;
-    const int unit = u.unit;
-    switch (S.kind) {
-    case SK_SM:
-    case SK_SMR: {
-        const LevelArgs<T> A = ld(S.u.lb.a[find_box(S.u.lb, unit)]);
-        if (S.kind == SK_SM) smooth_block<T, false>(A, unit - A.blk0);
-        else smooth_block<T, true>(A, unit - A.blk0);
-        break;
-    }
-    case SK_RESTRICT: {
-        const TransferArgs<T> A = ld(S.u.tb.a[find_box(S.u.tb, unit)]);
+    const int unit = u.unit, kind = S.kind;
+    auto is = [&](int q) { return KINDS == 1 << q || ((KINDS >> q) & 1 && kind == q); };
+    if (is(SK_SM)) {
+        const LevelArgs<T> A = ld(S.u.lb.a[__builtin_amdgcn_readfirstlane(find_box(S.u.lb, unit))]);
+        smooth_block<T, false>(A, unit - A.blk0);
+    } else if (is(SK_SMR)) {
+        const LevelArgs<T> A = ld(S.u.lb.a[__builtin_amdgcn_readfirstlane(find_box(S.u.lb, unit))]);
+        smooth_block<T, true>(A, unit - A.blk0);
+    } else if (is(SK_RESTRICT)) {
+        const TransferArgs<T> A = ld(S.u.tb.a[__builtin_amdgcn_readfirstlane(find_box(S.u.tb, unit))]);
         restrict_block<T>(A, unit - A.blk0);
-        break;
-    }
-    case SK_PROLONG: {
-        const TransferArgs<T> A = ld(S.u.tb.a[find_box(S.u.tb, unit)]);
+    } else if (is(SK_PROLONG)) {
+        const TransferArgs<T> A = ld(S.u.tb.a[__builtin_amdgcn_readfirstlane(find_box(S.u.tb, unit))]);
         prolong_block<T>(A, unit - A.blk0);
-        break;
-    }
-    case SK_COARSE: {
+    } else if (is(SK_COARSE)) {
+        __shared__ CoarseLds lds;
         const int box = unit / S.aux, rb = unit % S.aux;
         if (box < S.u.cb.nbox) {
             const CoarseArgs<T> A = ld(S.u.cb.a[box]);
             if (rb * 64 < A.n) coarse_block<T>(A, rb, lds);
         }
-        break;
-    }
-    default:
-        break;
     }
 }
 
@@ -259,7 +257,11 @@ void launch_batch_stage(const StageRun &run, int family, int nrmax, int kinds, h
         else hipLaunchKernelGGL((k_bstage_sm0<T, 3>), grid, block, 0, st, run);
         break;
     default:
-        hipLaunchKernelGGL((k_bstage_misc<T>), grid, block, 0, st, run);
+        if (kinds == 1 << SK_SM) hipLaunchKernelGGL((k_bstage_misc<T, 1 << SK_SM>), grid, block, 0, st, run);
+        else if (kinds == 1 << SK_SMR) hipLaunchKernelGGL((k_bstage_misc<T, 1 << SK_SMR>), grid, block, 0, st, run);
+        else if (kinds == 1 << SK_RESTRICT) hipLaunchKernelGGL((k_bstage_misc<T, 1 << SK_RESTRICT>), grid, block, 0, st, run);
+        else if (kinds == 1 << SK_PROLONG) hipLaunchKernelGGL((k_bstage_misc<T, 1 << SK_PROLONG>), grid, block, 0, st, run);
+        else hipLaunchKernelGGL((k_bstage_misc<T, kAllKinds>), grid, block, 0, st, run);
         break;
     }
 }

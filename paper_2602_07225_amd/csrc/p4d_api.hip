@@ -2629,7 +2629,8 @@ struct p4d_batch {
     int nstages = 0, nrmax = 8;
     struct WorkList {
         int family, nr;             // stage family, radial size class
-        int kinds = 0;              // level-0 smoothing lists: 1 steps, 2 residuals, 3 both
+        int kinds = 0;              // level-0 smoothing lists: 1 steps, 2 residuals, 3 both;
+                                    // coarse-level lists: a bit per kind (1 << kind)
         int pos0, npos;             // queue positions
         int item0, nitems;          // units
         int depth;                  // stage depth
@@ -2823,6 +2824,7 @@ static p4d_status batch_record(p4d_batch *B, bool fold)
                     if (j < 0 || stage_family(per[i][j].kind) != fam) continue;
                     if (radial && rad_nrmax(B->cell[i]->g) != kNrClass[ci]) continue;
                     if (fam == SF_SM0) W.kinds |= per[i][j].kind == SK_SM0 ? 1 : 2;
+                    else if (fam == SF_MISC) W.kinds |= 1 << per[i][j].kind;
                     order.push_back(base[i] + j);
                     ustart.push_back((int)items);
                     items += per[i][j].nunits;
