@@ -388,7 +388,8 @@ p4d_status p4d_batch_solve(p4d_batch *batch, const double *const *d_b, double *c
  * one cooperative launch per application: the whole grid walks the stage
  * depths with a grid barrier between depths (P4D_ERR_HIP where the device
  * cannot launch it cooperatively).  The three give the same results bit for
- * bit.                                                                      */
+ * bit.  Cells with z-line smoothing are preconditioned as in mode 1 whatever
+ * the mode.                                                                 */
 p4d_status p4d_batch_set_pc_mode(p4d_batch *batch, int32_t mode);
 /* Kernel timing of the batched launches, as p4d_profile / p4d_profile_read;
  * P4D_K_BATCH_PC times all preconditioner launches of one Arnoldi step

@@ -1044,8 +1044,9 @@ static void apply_pc_t(p4d_ctx *c, int transpose, const double *r, const double 
     }
     VState<T> vs{};
     for (int b = 0; b < 4; b++) vs.xcur[b][0] = 0;
-    if (c->pc.smoother == P4D_SMOOTH_ZLINE) vcycle_line(c, 0, st);   // (FP64 only)
-    else vcycle_level<T>(c, vs, 0, st);
+    // (z-line cycles: FP64 only, and launched, never recorded: see batch_fgmres)
+    if (c->pc.smoother != P4D_SMOOTH_ZLINE) vcycle_level<T>(c, vs, 0, st);
+    else if (!c->rec) vcycle_line(c, 0, st);
     // each box's final level-0 iterate (the two buffers alternate)
     for (int b = 0; b < 4; b++) R.x0[b] = (const double *)(vs.xcur[b][0] ? c->x0b : c->x0a);
     if (c->rec) {
@@ -3055,6 +3056,10 @@ static p4d_status batch_fgmres(p4d_batch *B, int transpose, const double *const 
 {
     const int n = B->n, m = o.restart;
     const bool fold = fold_rows(o);
+    // the stages of a z-line cycle are not recorded: such a batch applies its
+    // preconditioner cell after cell
+    bool stages = B->pc_mode != 1;
+    for (const p4d_ctx *c : B->cell) stages = stages && c->pc.smoother != P4D_SMOOTH_ZLINE;
     auto t0 = std::chrono::steady_clock::now();
     std::vector<BCell> bc;
     BatchGrid G;
@@ -3155,7 +3160,7 @@ static p4d_status batch_fgmres(p4d_batch *B, int transpose, const double *const 
                 for (int i = 0; i < n; i++)
                     if ((act >> i) & 1ULL) bytes += B->pc_bytes[i];
                 ProfScope pr(B->prof, P4D_K_BATCH_PC, bytes, st);
-                if (B->pc_mode != 1) {
+                if (stages) {
                     batch_apply_pc<T, TZ>(B, transpose, k, act, zero, st);
                 } else if (fold) {
                     for (int i = 0; i < n; i++)
