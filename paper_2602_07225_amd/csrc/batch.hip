@@ -594,7 +594,7 @@ __global__ __launch_bounds__(kBlock) void k_bfold_update(const BCell *__restrict
     if (n < g.nnode) fold_update_node<NRMAX, TRANS>(g, U, n);
 }
 
-template <int KMAX>
+template <int KMAX, int LOADS>
 __global__ __launch_bounds__(kBlock) void k_bmdot(const BCell *__restrict__ cells, int ncells,
                                                   unsigned long long active, unsigned long long first, int k)
 {
@@ -615,10 +615,7 @@ __global__ __launch_bounds__(kBlock) void k_bmdot(const BCell *__restrict__ cell
     for (int q = 0; q < KMAX; q++) acc[q] = 0.0;
     for (long long i = (long long)lb * kBlock + threadIdx.x; i < N; i += (long long)nb * kBlock) {
         const double wi = w[i];
-        double v[KMAX];
-        basis_row<KMAX>(v0, M, V, N, nv, i, v);
-#pragma unroll
-        for (int q = 0; q < KMAX; q++) acc[q] += wi * v[q];
+        basis_row<KMAX, LOADS>(v0, M, V, N, nv, i, [&](int q, double v) { acc[q] += wi * v; });
     }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
@@ -654,7 +651,7 @@ __global__ __launch_bounds__(kBlock) void k_bmdot_final(const BCell *__restrict_
     }
 }
 
-template <int KMAX>
+template <int KMAX, int LOADS>
 __global__ __launch_bounds__(kBlock) void k_borth(const BCell *__restrict__ cells, int ncells,
                                                   unsigned long long active, unsigned long long first, int k,
                                                   int pass)
@@ -666,10 +663,6 @@ __global__ __launch_bounds__(kBlock) void k_borth(const BCell *__restrict__ cell
     const int lb = blockIdx.x - C.st_blk0, nb = C.st_nblk;
     const long long N = C.nk;
     const int nv = k + 1;
-    if (C.fold && lb == 0 && threadIdx.x < 64) {
-        const double a = fold_update(fold_alpha(C.alpha, C.invbeta, k, pass), C.coef, C.alpha, nv);
-        if (threadIdx.x == 0) C.alpha[k + 1] = a;
-    }
     const double *__restrict__ V = C.V + (C.g.N - N);
     const double *__restrict__ v0 = C.fold && ((first >> c) & 1ULL) ? C.b : C.V;
     const FoldMap M = C.fold ? fold_map(C.g) : FoldMap{};
@@ -680,15 +673,19 @@ __global__ __launch_bounds__(kBlock) void k_borth(const BCell *__restrict__ cell
     double sq = 0.0;
     for (long long i = (long long)lb * kBlock + threadIdx.x; i < N; i += (long long)nb * kBlock) {
         double wi = w[i];
-        double v[KMAX];
-        basis_row<KMAX>(v0, M, V, N, nv, i, v);
-#pragma unroll
-        for (int q = 0; q < KMAX; q++) wi -= cq[q] * v[q];
+        basis_row<KMAX, LOADS>(v0, M, V, N, nv, i, [&](int q, double v) { wi -= cq[q] * v; });
         w[i] = wi;
         sq += wi * wi;
     }
     const double s = block_sum(sq, red);
     if (threadIdx.x == 0) C.red[lb] = s;
+    // (the store of alpha at the end: ahead of the coefficients' loads it makes
+    // them vector loads, two registers each, 256 in all and one wave per SIMD
+    // with 64 of them)
+    if (C.fold && lb == 0 && threadIdx.x < 64) {
+        const double a = fold_update(fold_alpha(C.alpha, C.invbeta, k, pass), C.coef, C.alpha, nv);
+        if (threadIdx.x == 0) C.alpha[k + 1] = a;
+    }
 }
 
 // grid ncells: beta = sqrt(sum of the cell's partials) into h[128] and
@@ -850,13 +847,13 @@ void launch_bmdot(const BCell *cells, int ncells, unsigned long long active, uns
                   int nblk_st, int pass, hipStream_t st)
 {
     const int nv = k + 1;
-#define P4D_BM(K) \
-    hipLaunchKernelGGL((k_bmdot<K>), dim3(nblk_st), dim3(kBlock), 0, st, cells, ncells, active, first, k)
-    if (nv <= 4) P4D_BM(4);
-    else if (nv <= 8) P4D_BM(8);
-    else if (nv <= 16) P4D_BM(16);
-    else if (nv <= 32) P4D_BM(32);
-    else P4D_BM(64);
+#define P4D_BM(K, HOW) \
+    hipLaunchKernelGGL((k_bmdot<K, HOW>), dim3(nblk_st), dim3(kBlock), 0, st, cells, ncells, active, first, k)
+    if (nv <= 4) P4D_BM(4, kBasisGroups);
+    else if (nv <= 8) P4D_BM(8, kBasisGroups);
+    else if (nv <= 16) P4D_BM(16, kBasisGroups);
+    else if (nv <= 32) P4D_BM(32, kBasisGroups);
+    else P4D_BM(64, kBasisEights);
 #undef P4D_BM
     hipLaunchKernelGGL(k_bmdot_final, dim3(nv, ncells), dim3(kBlock), 0, st, cells, active, k, pass);
 }
@@ -865,13 +862,13 @@ void launch_borth(const BCell *cells, int ncells, unsigned long long active, uns
                   int nblk_st, int pass, hipStream_t st)
 {
     const int nv = k + 1;
-#define P4D_BR(K) \
-    hipLaunchKernelGGL((k_borth<K>), dim3(nblk_st), dim3(kBlock), 0, st, cells, ncells, active, first, k, pass)
-    if (nv <= 4) P4D_BR(4);
-    else if (nv <= 8) P4D_BR(8);
-    else if (nv <= 16) P4D_BR(16);
-    else if (nv <= 32) P4D_BR(32);
-    else P4D_BR(64);
+#define P4D_BR(K, HOW) \
+    hipLaunchKernelGGL((k_borth<K, HOW>), dim3(nblk_st), dim3(kBlock), 0, st, cells, ncells, active, first, k, pass)
+    if (nv <= 4) P4D_BR(4, kBasisGroups);
+    else if (nv <= 8) P4D_BR(8, kBasisGroups);
+    else if (nv <= 16) P4D_BR(16, kBasisGroups);
+    else if (nv <= 32) P4D_BR(32, kBasisGroups);
+    else P4D_BR(64, kBasisGroups);
 #undef P4D_BR
 }
 

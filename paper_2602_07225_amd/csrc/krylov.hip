@@ -8,7 +8,16 @@
 
 namespace p4d {
 
-constexpr int kPStride = 64;   // partial-sum stride per workgroup
+// Entries from which up to eight vectors are loaded one after another
+// (kBasisEach).  Long vectors come from HBM, which serves a few streams at a
+// time better than all of them; short ones come from the caches, and the time
+// is that of the loads waited for.  One after another against in groups, us,
+// for 4 and 8 vectors: dots of 2.2 M entries 20, 34 / 20, 32; 3.7 M 28, 48 / 26,
+// 44; 5.5 M 37, 80 / 40, 85; 15.3 M 82, 164 / 87, 175 (means over 1..4 and 5..8
+// in a solve); updates of 0.9 M 10.1, 15.8 / 9.5, 14.6; 2.2 M 18.9, 28.2 / 20.4,
+// 30.8; 15.3 M 90, 177 / 99, 197.  From nine vectors on the groups win at every
+// length (9 of 15.3 M: 223 and 257 against 315 and 332).
+constexpr long long kLongDot = 1LL << 22, kLongUpdate = 1LL << 21;
 
 int stream_blocks(long long n)
 {
@@ -16,11 +25,12 @@ int stream_blocks(long long n)
     return (int)(b < kRedBlocks ? (b < 1 ? 1 : b) : kRedBlocks);
 }
 
-template <int KMAX>
-__global__ __launch_bounds__(kBlock) void k_mdot(long long n, const double *__restrict__ w,
-                                                 const double *__restrict__ V,
-                                                 const double *__restrict__ v0, FoldMap M, long long ldv,
-                                                 int nv, double *__restrict__ partial)
+template <int KMAX, int LOADS>
+__global__ __launch_bounds__(kBlock, basis_waves(LOADS)) void k_mdot(long long n, const double *__restrict__ w,
+                                                                     const double *__restrict__ V,
+                                                                     const double *__restrict__ v0, FoldMap M,
+                                                                     long long ldv, int nv,
+                                                                     double *__restrict__ partial)
 {
     __shared__ double red[4][KMAX];
     double acc[KMAX];
@@ -29,10 +39,7 @@ __global__ __launch_bounds__(kBlock) void k_mdot(long long n, const double *__re
     const long long stride = (long long)gridDim.x * kBlock;
     for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) {
         const double wi = w[i];
-        double v[KMAX];
-        basis_row<KMAX>(v0, M, V, ldv, nv, i, v);
-#pragma unroll
-        for (int q = 0; q < KMAX; q++) acc[q] += wi * v[q];
+        basis_row<KMAX, LOADS>(v0, M, V, ldv, nv, i, [&](int q, double v) { acc[q] += wi * v; });
     }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
@@ -53,13 +60,16 @@ __global__ __launch_bounds__(kBlock) void k_mdot(long long n, const double *__re
 void launch_mdot(long long n, const double *w, const double *V, const double *v0, const FoldMap &M, long long ldv,
                  int nv, double *partial, int nblk, hipStream_t st)
 {
-#define P4D_MD(K) \
-    hipLaunchKernelGGL((k_mdot<K>), dim3(nblk), dim3(kBlock), 0, st, n, w, V, v0, M, ldv, nv, partial)
-    if (nv <= 4) P4D_MD(4);
-    else if (nv <= 8) P4D_MD(8);
-    else if (nv <= 16) P4D_MD(16);
-    else if (nv <= 32) P4D_MD(32);
-    else P4D_MD(64);
+#define P4D_MD(K, HOW) \
+    hipLaunchKernelGGL((k_mdot<K, HOW>), dim3(nblk), dim3(kBlock), 0, st, n, w, V, v0, M, ldv, nv, partial)
+    const bool each = n >= kLongDot;
+    if (nv <= 4 && each) P4D_MD(4, kBasisEach);
+    else if (nv <= 4) P4D_MD(4, kBasisGroups);
+    else if (nv <= 8 && each) P4D_MD(8, kBasisEach);
+    else if (nv <= 8) P4D_MD(8, kBasisGroups);
+    else if (nv <= 16) P4D_MD(16, kBasisGroups);
+    else if (nv <= 32) P4D_MD(32, kBasisGroups);
+    else P4D_MD(64, kBasisEights);
 #undef P4D_MD
 }
 
@@ -89,12 +99,13 @@ void launch_mdot_final(int nv, const double *partial, int nblk, const double *in
     hipLaunchKernelGGL(k_mdot_final, dim3(nv), dim3(kBlock), 0, st, nv, partial, nblk, invbeta, h, c, F);
 }
 
-template <int KMAX>
-__global__ __launch_bounds__(kBlock) void k_orth(long long n, double *__restrict__ w,
-                                                 const double *__restrict__ V,
-                                                 const double *__restrict__ v0, FoldMap M, long long ldv,
-                                                 int nv, const double *__restrict__ c,
-                                                 double *__restrict__ partial, Fold F)
+template <int KMAX, int LOADS>
+__global__ __launch_bounds__(kBlock, basis_waves(LOADS)) void k_orth(long long n, double *__restrict__ w,
+                                                                     const double *__restrict__ V,
+                                                                     const double *__restrict__ v0, FoldMap M,
+                                                                     long long ldv, int nv,
+                                                                     const double *__restrict__ c,
+                                                                     double *__restrict__ partial, Fold F)
 {
     __shared__ double red[4];
     // the folded rows: alpha_{k+1}, which no other workgroup of this launch reads
@@ -109,10 +120,7 @@ __global__ __launch_bounds__(kBlock) void k_orth(long long n, double *__restrict
     const long long stride = (long long)gridDim.x * kBlock;
     for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) {
         double wi = w[i];
-        double v[KMAX];
-        basis_row<KMAX>(v0, M, V, ldv, nv, i, v);
-#pragma unroll
-        for (int q = 0; q < KMAX; q++) wi -= cq[q] * v[q];
+        basis_row<KMAX, LOADS>(v0, M, V, ldv, nv, i, [&](int q, double v) { wi -= cq[q] * v; });
         w[i] = wi;
         sq += wi * wi;
     }
@@ -123,13 +131,16 @@ __global__ __launch_bounds__(kBlock) void k_orth(long long n, double *__restrict
 void launch_orth(long long n, double *w, const double *V, const double *v0, const FoldMap &M, long long ldv, int nv,
                  const double *c, double *partial, int nblk, const Fold &F, hipStream_t st)
 {
-#define P4D_OR(K) \
-    hipLaunchKernelGGL((k_orth<K>), dim3(nblk), dim3(kBlock), 0, st, n, w, V, v0, M, ldv, nv, c, partial, F)
-    if (nv <= 4) P4D_OR(4);
-    else if (nv <= 8) P4D_OR(8);
-    else if (nv <= 16) P4D_OR(16);
-    else if (nv <= 32) P4D_OR(32);
-    else P4D_OR(64);
+#define P4D_OR(K, HOW) \
+    hipLaunchKernelGGL((k_orth<K, HOW>), dim3(nblk), dim3(kBlock), 0, st, n, w, V, v0, M, ldv, nv, c, partial, F)
+    const bool each = n >= kLongUpdate;
+    if (nv <= 4 && each) P4D_OR(4, kBasisEach);
+    else if (nv <= 4) P4D_OR(4, kBasisGroups);
+    else if (nv <= 8 && each) P4D_OR(8, kBasisEach);
+    else if (nv <= 8) P4D_OR(8, kBasisGroups);
+    else if (nv <= 16) P4D_OR(16, kBasisGroups);
+    else if (nv <= 32) P4D_OR(32, kBasisGroups);
+    else P4D_OR(64, kBasisGroups);
 #undef P4D_OR
 }
 

@@ -69,25 +69,54 @@ __device__ inline long long fold_at(const FoldMap &M, long long i)
 {
     return i < M.nm ? i : i + (i < M.na ? M.d0 : M.d1);
 }
-// Entry i of the vectors 0..nv-1 (vector q at V + q ldv, vector 0 at v0).  Four
-// vectors' loads to a (uniform) branch, the last ones' repeated, and no use of
-// a value in between, so that they are all in flight together; with a test per
-// vector each load waited for the one before.  Dot products with 9..16 vectors
-// of 0.9 M entries 29.3 -> 20.7 us and the update 23.2 -> 17.9; 1.8 M entries
-// 47 -> 34 and 40 -> 33 (5.0 TB/s; a large copy reaches 4.8).
-template <int KMAX>
+// Entry i of the vectors 0..nv-1 (vector q at V + q ldv, vector 0 at v0) to
+// use(q, value), q ascending.  How they are loaded:
+//  kBasisGroups  four vectors' loads to a (uniform) branch, the last ones'
+//    repeated (to uses q >= nv, without effect), and no use in between, so that
+//    they are all in flight together: dot products with 9..16 vectors of 0.9 M
+//    entries 29.3 -> 20.7 us and the update 23.2 -> 17.9 against a test per
+//    vector; 1.8 M entries 47 -> 34 and 40 -> 33.
+//  kBasisEach  a test per vector, each load waited for: for few long vectors
+//    (long_basis).
+//  kBasisEights  groups of four, eight vectors used before the next are loaded:
+//    for the dot products of more than 32 vectors, whose sums take 128
+//    registers; with all loads ahead of the sums the kernel needed 256 and one
+//    wave per SIMD.  48 vectors of 0.15 / 0.9 / 3.7 / 8 M entries: 36 / 118 /
+//    291 / 564 us, all ahead 64 / 193 / 365 / 619, a test per vector 44 / 183 /
+//    571 / 1164.
+enum BasisLoads { kBasisGroups, kBasisEach, kBasisEights };
+// waves per SIMD asked for: a load at a time wants all eight (at seven the
+// 2048 workgroups of a long vector no longer run at once, half as fast again)
+constexpr int basis_waves(int loads) { return loads == kBasisEach ? 8 : 1; }
+template <int KMAX, int LOADS, typename Use>
 __device__ inline void basis_row(const double *v0, const FoldMap &M, const double *V, long long ldv, int nv, long long i,
-                                 double (&v)[KMAX])
+                                 Use use)
 {
     const double *Vi = V + i;
-    v[0] = v0[fold_at(M, i)];
+    if constexpr (LOADS == kBasisEach) {
+        use(0, v0[fold_at(M, i)]);
 #pragma unroll
-    for (int g = 0; g < KMAX; g += 4) {
+        for (int q = 1; q < KMAX; q++)
+            if (q < nv) use(q, Vi[(long long)q * ldv]);
+    } else {
+        constexpr int C = LOADS == kBasisEights ? 8 : KMAX;
 #pragma unroll
-        for (int u = g ? 0 : 1; u < 4; u++) v[g + u] = 0.0;
-        if ((g ? g : 1) < nv) {
+        for (int c = 0; c < KMAX; c += C) {
+            if (LOADS == kBasisEights && c >= nv) continue;
+            double v[C];
+            if (c == 0) v[0] = v0[fold_at(M, i)];
 #pragma unroll
-            for (int u = g ? 0 : 1; u < 4; u++) v[g + u] = Vi[(long long)(g + u < nv ? g + u : nv - 1) * ldv];
+            for (int g = c; g < c + C; g += 4) {
+#pragma unroll
+                for (int u = g ? 0 : 1; u < 4; u++) v[g - c + u] = 0.0;
+                if ((g ? g : 1) < nv) {
+#pragma unroll
+                    for (int u = g ? 0 : 1; u < 4; u++)
+                        v[g - c + u] = Vi[(long long)(g + u < nv ? g + u : nv - 1) * ldv];
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < C; q++) use(c + q, v[q]);
         }
     }
 }
