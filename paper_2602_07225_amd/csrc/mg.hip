@@ -157,15 +157,16 @@ __device__ inline int opaque(int v)
 // Tail of the V-cycle, one 512-thread workgroup per box (see TailArgs).  A
 // stage of these levels as a launch of its own costs 4-5 us, nearly all of it
 // the launch and one dependent memory latency; here it is one pass over LDS
-// and two barriers.  The upper level's couplings stay in registers, so that
-// their sizes are what they leave room for: two nodes of the upper and one of
-// the lower per thread (162 of the 256 VGPRs that 8 waves have in FP64; one
-// and one with 16 waves and 128 spilled 82;
-// four in FP32 took five times as long).  The iterates have a one-node halo in LDS, so that a neighbour is one
+// and two barriers.  The couplings of both levels stay in registers, so that
+// their sizes are what these leave room for: two nodes of the upper and one of
+// the lower per thread (all 256 VGPRs that 8 waves have; 174 with one and one;
+// one and one with 16 waves and 128 spilled 82; four in FP32 took five times as
+// long).  The iterates have a one-node halo in LDS, so that a neighbour is one
 // uniform offset away.
 // Measured: levels of 325 and 63 nodes 18.7 -> 10.9 us (the earlier kernel read
-// the couplings from LDS); levels of 729, 125 and 27 nodes 21.5 us, where the
-// first took six launches (27 us) before the tail of the others (17 us).
+// the couplings from LDS), 12.5 beside two boxes of 150 and 36 nodes; levels of
+// 729, 125 and 27 nodes 21.5 us, where the first took six launches (27 us)
+// before the tail of the others (17 us).
 // Indices are taken through opaque(): what a stage derives from them is formed
 // anew there, not kept in registers across the others.
 // The stages' code is one loop per level (steps 2..deg, residual and coarse

@@ -777,17 +777,30 @@ static void vcycle_level(p4d_ctx *c, VState<T> &vs, int l, hipStream_t st)
     if (l >= 1 && !c->rec) {
         // boxes whose levels from l down are one or two smoothed levels that
         // fit the LDS of one workgroup run the rest of their cycle in the tail
-        // kernel
+        // kernel.  With two levels left a box enters only if every box does:
+        // the launches of level l are then saved; made for another box, they
+        // take this one along at no cost, and the tail of two levels is the
+        // longer one (electrodes of 891 and 150 nodes beside a whole cell of
+        // 2025 and 325: 25 us with the electrodes' two levels, 13 with one).
+        auto below = [&](int b) { return c->box[b].nlev - 2 - l; };   // smoothed levels below l
+        auto fits = [&](int b) {
+            const Box &B = c->box[b];
+            const Level &E = B.lev[l], &F = B.lev[l + 1];
+            const bool two = below(b) == 1;
+            return below(b) <= 1 && tail_fits(E.nx, E.ny, E.nz, two ? F.nx : 0, two ? F.ny : 0, two ? F.nz : 0,
+                                              B.lev[B.nlev - 1].n);
+        };
+        bool every = true;
+        for (int q = 0; q < na; q++) every = every && fits(act[q]);
         TailBatch<T> &tb = vs.tb;
         tb.deg = deg;
         int rest[4], nr = 0, tmask = 0;
         for (int q = 0; q < na; q++) {
             Box &B = c->box[act[q]];
             Level &E = B.lev[l];
-            const int below = B.nlev - 2 - l;   // smoothed levels below l
-            Level *F = below == 1 ? &B.lev[l + 1] : nullptr;
+            Level *F = below(act[q]) == 1 ? &B.lev[l + 1] : nullptr;
             const Level &Cl = B.lev[B.nlev - 1];
-            if (below > 1 || !tail_fits(E.nx, E.ny, E.nz, F ? F->nx : 0, F ? F->ny : 0, F ? F->nz : 0, Cl.n)) {
+            if (!fits(act[q]) || (F && !every)) {
                 rest[nr++] = act[q];
                 continue;
             }
