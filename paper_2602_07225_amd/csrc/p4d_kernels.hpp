@@ -1049,11 +1049,16 @@ __device__ inline void newton_terms(const Geom &g, const TX *x, long long n, int
     } else {
         const long long layer = (long long)g.nx * g.ny;
         for (int e = 0; e < 8; e++) {
-            if (!E.has(e)) continue;
-            const int id = E.id(e);
+            // (the element from the node again: E indexed by a variable leaves the
+            // registers, in the whole kernel; the transposed operator, also
+            // without these terms, then took 79 us for 54 over the electrode-level
+            // unknowns of 64 x 64 x 192 nodes)
+            const int ei = i - 1 + (e & 1), ej = j - 1 + ((e >> 1) & 1), ek = k - 1 + (e >> 2);
+            if (ei < 0 || ej < 0 || ek < 0 || ei >= g.nx - 1 || ej >= g.ny - 1 || ek >= g.nz - 1) continue;
+            const int id = ei + (g.nx - 1) * (ej + (g.ny - 1) * ek);
             const double A = g.nwa[id], B = g.nwb[id], C = g.nwc[id];
             // corner b of the element
-            const long long c0 = (i - 1 + (e & 1)) + (long long)g.nx * (j - 1 + ((e >> 1) & 1)) + layer * (k - 1 + (e >> 2));
+            const long long c0 = ei + (long long)g.nx * ej + layer * ek;
             auto node = [&](int b) { return c0 + (b & 1) + (long long)g.nx * ((b >> 1) & 1) + layer * ((b >> 2) & 1); };
             double t = 0.0;
             for (int a = 0; a < 8; a++) {
