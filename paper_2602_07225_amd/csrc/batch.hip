@@ -82,7 +82,11 @@ __device__ inline UnitRef unit_of(const StageRun &run)
     return UnitRef{si, unit};
 }
 
-template <typename T, int NRMAX>
+// pc SCHUR on whole vectors comes with an FP32 Z only (an FP64 Z: folded)
+template <typename TZ>
+constexpr bool kWholeSchur = sizeof(TZ) < sizeof(double);
+
+template <typename T, typename TZ, int NRMAX>
 __global__ __launch_bounds__(kBlock) void k_bstage_radf(StageRun run)
 {
     const UnitRef u = unit_of(run);
@@ -95,7 +99,7 @@ __global__ __launch_bounds__(kBlock) void k_bstage_radf(StageRun run)
     const RadArgs R = Cm.R;
     const double *r = Cm.V + (long long)run.k * g.N;
     const double rs = Cm.invbeta[run.k];
-    if (Cm.schur) {
+    if (kWholeSchur<TZ> && Cm.schur) {
         if (run.transpose) rad_fwd_block<T, NRMAX, true, true>(g, R, r, rs, u.unit);
         else rad_fwd_block<T, NRMAX, false, true>(g, R, r, rs, u.unit);
     } else {
@@ -115,7 +119,7 @@ __global__ __launch_bounds__(kBlock) void k_bstage_radb(StageRun run)
     const double *r = Cm.V + (long long)run.k * g.N;
     const double rs = Cm.invbeta[run.k];
     TZ *z = (TZ *)Cm.Z + (long long)run.k * g.N;
-    if (Cm.schur) {
+    if (kWholeSchur<TZ> && Cm.schur) {
         if (run.transpose) rad_back_block<T, TZ, NRMAX, true, true>(g, R, r, rs, z, u.unit);
         else rad_back_block<T, TZ, NRMAX, false, true>(g, R, r, rs, z, u.unit);
     } else {
@@ -238,7 +242,7 @@ void launch_batch_stage(const StageRun &run, int family, int nrmax, int kinds, h
             hipLaunchKernelGGL((k_bstage_fwd_fold<T>), grid, block, 0, st, run);
             break;
         }
-#define P4D_BF(NR) hipLaunchKernelGGL((k_bstage_radf<T, NR>), grid, block, 0, st, run)
+#define P4D_BF(NR) hipLaunchKernelGGL((k_bstage_radf<T, TZ, kWholeSchur<TZ> ? NR : 8>), grid, block, 0, st, run)
         P4D_NR_SWITCH(nrmax, P4D_BF)
 #undef P4D_BF
         break;
@@ -296,7 +300,7 @@ __device__ inline void persist_unit(const PersistRun &run, Ctab<PStage<T>> &S, i
         const RadArgs R = Cm.R;
         const double *r = Cm.V + (long long)run.k * g.N;
         const double rs = Cm.invbeta[run.k];
-        if (Cm.schur) {
+        if (kWholeSchur<TZ> && Cm.schur) {
             if (run.transpose) rad_fwd_block<T, NRMAX, true, true>(g, R, r, rs, unit);
             else rad_fwd_block<T, NRMAX, false, true>(g, R, r, rs, unit);
         } else {
@@ -314,7 +318,7 @@ __device__ inline void persist_unit(const PersistRun &run, Ctab<PStage<T>> &S, i
         const double *r = Cm.V + (long long)run.k * g.N;
         const double rs = Cm.invbeta[run.k];
         TZ *z = (TZ *)Cm.Z + (long long)run.k * g.N;
-        if (Cm.schur) {
+        if (kWholeSchur<TZ> && Cm.schur) {
             if (run.transpose) rad_back_block<T, TZ, NRMAX, true, true>(g, R, r, rs, z, unit);
             else rad_back_block<T, TZ, NRMAX, false, true>(g, R, r, rs, z, unit);
         } else {
@@ -399,7 +403,10 @@ hipError_t launch_batch_persist(const PersistRun &run, int nrmax, int grid, hipS
     return hipLaunchCooperativeKernel(f, dim3(grid), dim3(kBlock), args, 0, st);
 }
 
-// workgroups of the cooperative kernel resident at once (its grid size)
+// The cooperative kernel's grid: a workgroup per CU (0: cannot be launched).
+// The grid barrier costs more the more workgroups meet at it (as many as fit,
+// two or three per CU: 21 to 36 ms for 8 cells of 16 to 48 nodes a side, 19 with
+// one), and a grid between would leave CUs with fewer than others.
 template <typename T, typename TZ>
 int batch_persist_slots(int nrmax)
 {
@@ -413,7 +420,7 @@ int batch_persist_slots(int nrmax)
         hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, f, kBlock, 0) != hipSuccess || per < 1)
         return 0;
-    return per * ncu;
+    return ncu;
 }
 #define P4D_INST(T, TZ)                                                                           \
     template hipError_t launch_batch_persist<T, TZ>(const PersistRun &, int, int, hipStream_t);  \
