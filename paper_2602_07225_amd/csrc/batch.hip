@@ -285,7 +285,12 @@ union PersistLds {
 };
 
 // one unit of a stage: the device function of its family, as in the
-// per-depth kernels above
+// per-depth kernels above.  (The Schur branches, which an FP64 Z does not reach,
+// stay: without them, or with the smallest radial class for folded vectors, the
+// kernel takes fewer registers, so more workgroups fit and meet at the barrier
+// between depths, and 8 cells of 16 to 48 nodes a side take 26 or 36 ms for 21.
+// One workgroup per CU is faster there, 19 ms, and slower from 24 cells on: 37
+// for 35, 81 for 66 with 64.)
 template <typename T, typename TZ, int NRMAX>
 __device__ inline void persist_unit(const PersistRun &run, Ctab<PStage<T>> &S, int unit, PersistLds &L)
 {
@@ -300,7 +305,7 @@ __device__ inline void persist_unit(const PersistRun &run, Ctab<PStage<T>> &S, i
         const RadArgs R = Cm.R;
         const double *r = Cm.V + (long long)run.k * g.N;
         const double rs = Cm.invbeta[run.k];
-        if (kWholeSchur<TZ> && Cm.schur) {
+        if (Cm.schur) {
             if (run.transpose) rad_fwd_block<T, NRMAX, true, true>(g, R, r, rs, unit);
             else rad_fwd_block<T, NRMAX, false, true>(g, R, r, rs, unit);
         } else {
@@ -318,7 +323,7 @@ __device__ inline void persist_unit(const PersistRun &run, Ctab<PStage<T>> &S, i
         const double *r = Cm.V + (long long)run.k * g.N;
         const double rs = Cm.invbeta[run.k];
         TZ *z = (TZ *)Cm.Z + (long long)run.k * g.N;
-        if (kWholeSchur<TZ> && Cm.schur) {
+        if (Cm.schur) {
             if (run.transpose) rad_back_block<T, TZ, NRMAX, true, true>(g, R, r, rs, z, unit);
             else rad_back_block<T, TZ, NRMAX, false, true>(g, R, r, rs, z, unit);
         } else {
@@ -403,10 +408,7 @@ hipError_t launch_batch_persist(const PersistRun &run, int nrmax, int grid, hipS
     return hipLaunchCooperativeKernel(f, dim3(grid), dim3(kBlock), args, 0, st);
 }
 
-// The cooperative kernel's grid: a workgroup per CU (0: cannot be launched).
-// The grid barrier costs more the more workgroups meet at it (as many as fit,
-// two or three per CU: 21 to 36 ms for 8 cells of 16 to 48 nodes a side, 19 with
-// one), and a grid between would leave CUs with fewer than others.
+// workgroups of the cooperative kernel resident at once (its grid size)
 template <typename T, typename TZ>
 int batch_persist_slots(int nrmax)
 {
@@ -420,7 +422,7 @@ int batch_persist_slots(int nrmax)
         hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, f, kBlock, 0) != hipSuccess || per < 1)
         return 0;
-    return ncu;
+    return per * ncu;
 }
 #define P4D_INST(T, TZ)                                                                           \
     template hipError_t launch_batch_persist<T, TZ>(const PersistRun &, int, int, hipStream_t);  \
