@@ -127,7 +127,10 @@ typedef struct {
 
 typedef struct {
     int32_t pc;            /* p4d_pc_type                                         */
-    int32_t pc_prec;       /* p4d_prec of the preconditioner (radial + V-cycle)   */
+    int32_t pc_prec;       /* p4d_prec of the preconditioner: the V-cycles, and the
+                              particle eliminations, except in solves over all
+                              unknowns with pc SCHUR and an FP64 Z, which need
+                              none per step and form them in FP64             */
     int32_t restart;       /* FGMRES restart length m, 1..64                      */
     int32_t maxit;         /* cap on total inner iterations                       */
     int32_t cheb_degree;   /* Chebyshev smoothing degree, 1..4 (default 2)        */

@@ -785,8 +785,9 @@ __global__ __launch_bounds__(kBlock) void k_zline(LineBatch lb, int colour)
     // Both substitutions are recurrences d_k = b_k + f_k d_(k-1).  A line's
     // rows are dealt in runs to 32 lanes; a lane composes its run into one
     // map d -> B + F d, five shuffles give each lane the value that enters
-    // its run, and the run is gone through again with it.  (|f| < 1 for the
-    // dominant rows of these boxes, so the products shrink.)
+    // its run, and the run is gone through again with it.  (Products of the
+    // factors stay bounded: over a run they are at most 1 for dominant rows in
+    // one direction, and in the other that times the ratio of two pivots.)
     const int sub = threadIdx.x & 31, m = (nz + 31) >> 5;
     for (int ll = threadIdx.x >> 5; ll < w; ll += kBlock / 32) {
         const int q0 = ll * nzp;
@@ -1222,9 +1223,9 @@ __global__ __launch_bounds__(1024) void k_invert_w64(InvBatch ib)
 //   k_inv_rank:  A_ij -= C_i A_pj, A_ip = -C_i D, A_pp = D
 // One workgroup that passed the whole matrix through memory for every pivot
 // took 3.68 ms for four matrices of 100 to 244 unknowns; here the matrix is
-// passed once for 32 pivots, by a workgroup per 32 x 32 tile: 0.19 ms.  C and D
-// lie in the result's memory, which is written last (32 n + 1024 values, fewer
-// than n^2 from n = 49 on).
+// passed once for 32 pivots, by a workgroup per 32 x 32 tile: 0.20 ms.  C and D
+// lie in the result's memory, which is written last (32 n + 1024 values, no
+// more than n^2 from n = 52 on).
 constexpr int kInvB = 32;
 static_assert(kInvLds * kInvB + kInvB * kInvB <= kInvLds * kInvLds, "room for C and D");
 __global__ __launch_bounds__(1024) void k_inv_diag(InvBatch ib, int p0)
