@@ -2639,7 +2639,8 @@ struct p4d_batch {
     double *hb_h = nullptr, *yb_h = nullptr;
     int *kused_h = nullptr;
     // recorded schedule
-    int recorded = 0, rec_prec = -1, rec_fold = 0;
+    int recorded = 0, rec_prec = -1;
+    int fold = 0;                   // 1: the solve at hand folds its vectors
     int nstages = 0, nrmax = 8;
     struct WorkList {
         int family, nr;             // stage family, radial size class
@@ -2649,9 +2650,9 @@ struct p4d_batch {
         int item0, nitems;          // units
         int depth;                  // stage depth
     };
-    std::vector<WorkList> lists;    // in launch order
+    std::vector<WorkList> lists[2]; // in launch order, whole and folded vectors
     int tile_cz = 0;                // level-0 tile depth of the batch (0: chosen at recording)
-    std::vector<double> pc_bytes;   // per cell: level-0 and particle bytes of one application
+    std::vector<double> pc_bytes[2];   // per cell: level-0 and particle bytes of one application
     int pc_mode = 0;                // 0: batched stage launches, 1: per-cell launches,
                                     // 2: one persistent launch per application
     // persistent application: first item of every stage depth, grid size
@@ -2770,11 +2771,11 @@ static int batch_default_cz(p4d_batch *B)
 // depth.  Per depth, one list per stage family (per radial size class for
 // the particle stages), larger cells first.
 template <typename T>
-static p4d_status batch_record(p4d_batch *B, bool fold)
+static p4d_status batch_record(p4d_batch *B)
 {
     const int n = B->n;
     std::vector<std::vector<PStage<T>>> per(n);
-    B->pc_bytes.assign(n, 0.0);
+    for (int f = 0; f < 2; f++) B->pc_bytes[f].assign(n, 0.0);
     B->nrmax = 8;
     const int cz = B->tile_cz > 0 ? B->tile_cz : batch_default_cz<T>(B);
     for (int i = 0; i < n; i++) {
@@ -2792,7 +2793,8 @@ static p4d_status batch_record(p4d_batch *B, bool fold)
         c->tile_cz = keep;
         if ((int)per[i].size() > kMaxStagesPerCell)
             return bfail(B, P4D_ERR_INVALID_ARG, "too many preconditioner stages in a cell");
-        for (const PStage<T> &S : per[i]) B->pc_bytes[i] += stage_bytes(S, c->g, fold);
+        for (int f = 0; f < 2; f++)
+            for (const PStage<T> &S : per[i]) B->pc_bytes[f][i] += stage_bytes(S, c->g, f);
         const int nr = rad_nrmax(c->g);
         B->nrmax = nr > B->nrmax ? nr : B->nrmax;
     }
@@ -2825,12 +2827,13 @@ static p4d_status batch_record(p4d_batch *B, bool fold)
     std::stable_sort(bysize.begin(), bysize.end(),
                      [&](int a, int b) { return B->cell[a]->g.N > B->cell[b]->g.N; });
     std::vector<int> order, ustart;
-    B->lists.clear();
+    for (int f = 0; f < 2; f++) B->lists[f].clear();
     long long items = 0;
     for (int d = 0; d < depth; d++)
         for (int fam = SF_RADF; fam <= SF_MISC; fam++) {
-            // (folded vectors: no particle columns, one list for all sizes)
-            const bool radial = !fold && (fam == SF_RADF || fam == SF_RADB);
+            const bool radial = fam == SF_RADF || fam == SF_RADB;
+            std::vector<p4d_batch::WorkList> &whole = B->lists[0], &folded = B->lists[1];
+            size_t before = whole.size();
             for (int ci = 0; ci < (radial ? kNrClasses : 1); ci++) {
                 p4d_batch::WorkList W{fam, radial ? kNrClass[ci] : 8, 0, (int)order.size(), 0, (int)items, 0, d};
                 for (int i : bysize) {
@@ -2845,9 +2848,18 @@ static p4d_status batch_record(p4d_batch *B, bool fold)
                 }
                 W.npos = (int)order.size() - W.pos0;
                 W.nitems = (int)(items - W.item0);
-                if (W.npos > 0) B->lists.push_back(W);
+                if (W.npos > 0) whole.push_back(W);
                 if (items >= (1LL << 31) - (1LL << 20))
                     return bfail(B, P4D_ERR_INVALID_ARG, "work list too long");
+            }
+            // (folded vectors: no particle columns, one list for all sizes,
+            // which follow each other)
+            if (before < whole.size()) {
+                folded.push_back(whole[before]);
+                while (++before < whole.size()) {
+                    folded.back().npos += whole[before].npos;
+                    folded.back().nitems += whole[before].nitems;
+                }
             }
         }
     BHIPCHK(B, hipMemcpy(B->stages, all.data(), sizeof(PStage<T>) * all.size(), hipMemcpyHostToDevice));
@@ -2856,9 +2868,9 @@ static p4d_status batch_record(p4d_batch *B, bool fold)
     // the persistent application walks the same items depth by depth: the
     // first item of every depth (the work lists are in depth order)
     std::vector<int> dstart(depth + 1, (int)items);
-    for (int d = depth - 1, li = (int)B->lists.size() - 1; d >= 0; d--) {
+    for (int d = depth - 1, li = (int)B->lists[0].size() - 1; d >= 0; d--) {
         dstart[d] = dstart[d + 1];
-        for (; li >= 0 && B->lists[li].depth == d; li--) dstart[d] = B->lists[li].item0;
+        for (; li >= 0 && B->lists[0][li].depth == d; li--) dstart[d] = B->lists[0][li].item0;
     }
     BHIPCHK(B, hipMemcpy(B->dstart, dstart.data(), 4 * dstart.size(), hipMemcpyHostToDevice));
     B->npos = (int)order.size();
@@ -2867,7 +2879,6 @@ static p4d_status batch_record(p4d_batch *B, bool fold)
     B->nstages = (int)all.size();
     B->recorded = 1;
     B->rec_prec = B->cell[0]->prec;
-    B->rec_fold = fold;
     return P4D_OK;
 }
 
@@ -2989,7 +3000,7 @@ static void batch_apply_pc(p4d_batch *B, int transpose, int k, unsigned long lon
         pr.transpose = transpose;
         pr.k = k;
         pr.active = active;
-        pr.fold = B->rec_fold;
+        pr.fold = B->fold;
         pr.first = first;
         B->plaunch = launch_batch_persist<T, TZ>(pr, B->nrmax, B->pgrid, st);
         return;
@@ -3002,9 +3013,9 @@ static void batch_apply_pc(p4d_batch *B, int transpose, int k, unsigned long lon
     run.transpose = transpose;
     run.k = k;
     run.active = active;
-    run.fold = B->rec_fold;
+    run.fold = B->fold;
     run.first = first;
-    for (const p4d_batch::WorkList &W : B->lists) {
+    for (const p4d_batch::WorkList &W : B->lists[B->fold]) {
         run.pos0 = W.pos0;
         run.npos = W.npos;
         run.item0 = W.item0;
@@ -3025,6 +3036,7 @@ static p4d_status batch_tune_t(p4d_batch *B, hipStream_t st)
     const unsigned long long all = B->n == 64 ? ~0ULL : ((1ULL << B->n) - 1);
     static const int czs[9] = {2, 3, 4, 5, 6, 8, 10, 12, 16};
     const bool fold = sizeof(TZ) == sizeof(double) && B->cell[0]->pc.pc == P4D_PC_SCHUR;
+    B->fold = fold;
     hipEvent_t e0, e1;
     BHIPCHK(B, hipEventCreate(&e0));
     if (hipEventCreate(&e1) != hipSuccess) {
@@ -3036,7 +3048,7 @@ static p4d_status batch_tune_t(p4d_batch *B, hipStream_t st)
     p4d_status s = P4D_OK;
     for (int q = 0; q < 9 && s == P4D_OK; q++) {
         B->tile_cz = czs[q];
-        s = batch_record<T>(B, fold);
+        s = batch_record<T>(B);
         if (s == P4D_OK) s = batch_tables(B, B->ws_opts.restart, fold, nullptr, nullptr, bc, G, st);
         if (s != P4D_OK) break;
         batch_apply_pc<T, TZ>(B, 0, 0, all, 0, st);   // warm-up
@@ -3069,6 +3081,7 @@ static p4d_status batch_fgmres(p4d_batch *B, int transpose, const double *const 
 {
     const int n = B->n, m = o.restart;
     const bool fold = fold_rows(o);
+    B->fold = fold;
     // the stages of a z-line cycle are not recorded: such a batch applies its
     // preconditioner cell after cell
     bool stages = B->pc_mode != 1;
@@ -3171,7 +3184,7 @@ static p4d_status batch_fgmres(p4d_batch *B, int transpose, const double *const 
             {
                 double bytes = 0.0;
                 for (int i = 0; i < n; i++)
-                    if ((act >> i) & 1ULL) bytes += B->pc_bytes[i];
+                    if ((act >> i) & 1ULL) bytes += B->pc_bytes[fold][i];
                 ProfScope pr(B->prof, P4D_K_BATCH_PC, bytes, st);
                 if (stages) {
                     batch_apply_pc<T, TZ>(B, transpose, k, act, zero, st);
@@ -3509,9 +3522,8 @@ p4d_status p4d_batch_solve(p4d_batch *B, const double *const *d_b, double *const
             return bfail(B, P4D_ERR_OOM, "workspace sized for a smaller restart or an FP32 Z basis");
     }
     hipStream_t st = (hipStream_t)stream;
-    const bool fold = fold_rows(o);
-    if (!B->recorded || B->rec_prec != c0->prec || B->rec_fold != (int)fold) {
-        const p4d_status s = c0->prec ? batch_record<float>(B, fold) : batch_record<double>(B, fold);
+    if (!B->recorded || B->rec_prec != c0->prec) {
+        const p4d_status s = c0->prec ? batch_record<float>(B) : batch_record<double>(B);
         if (s != P4D_OK) return s;
     }
     if (c0->prec) {
